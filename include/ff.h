@@ -431,30 +431,30 @@ ff_status ff_dot_batched_backward(const float *g_hi, const float *g_lo,
  *                     accumulation, k ascending, of Mul22(A_ik, B_kj)
  *                     (section 4.1).  Bit-identical to that definition.
  * FF_GEMM_SLICED_I8   matrix-core path: each row of A and column of B is
- *                     scaled by a power of two and cut into 7 signed 8-bit
- *                     digits; the 28 digit-pair products that carry weight
- *                     above 2^-56 of the row/column scales run as exact
- *                     integer GEMMs (int8 inputs, int32 accumulation) and
- *                     are recombined exactly; one final rounding to
- *                     float-float.  No binary64 arithmetic.
- * FF_GEMM_SLICED_BF16 as above with the digits held in BF16 (exact for
- *                     |d| <= 128) and FP32 matrix-core accumulation, whose
- *                     partial sums are moved to integer accumulators before
- *                     they can exceed 2^24 (so they stay exact).
+ *                     scaled by a power of two and rounded to 54-bit fixed
+ *                     point; the integer product runs exactly modulo sixteen
+ *                     coprime integers up to 256 (int8 residues, int32
+ *                     accumulation), is put together exactly to 128-bit
+ *                     integers, and rounded once to float-float.  No binary64
+ *                     arithmetic.
+ * FF_GEMM_SLICED_BF16 as above with the residues held in BF16 (exact for
+ *                     |r| <= 128) and FP32 matrix-core accumulation, whose
+ *                     partial sums are reduced before they can exceed 2^24
+ *                     (so they stay exact).
  * Sliced accuracy: |C_ij - exact| <= 2^-44 * (|A| |B|)_ij when the rows of
  * A and columns of B do not span extreme dynamic ranges (normal(0,1) data at
  * 4096^3: 2^-51.6 at worst).  In general, with 2^e_i the power of two above
  * row i's largest |A_ik| and 2^f_j the one above column j's largest |B_kj|:
  *   |C_ij - exact| <= 2^(e_i - 54) sum_k |B_kj|
  *                   + 2^(f_j - 54) sum_k (|A_ik| + 2^(e_i - 54))
- *                   + K 2^(e_i + f_j - 47) + 2^-47 |C_ij|
- * (digit rounding, dropped digit pairs, final rounding).  Rows and columns
- * spanning 40 binades measured 2^-11.3 normwise, inside this bound; the FMA
- * loop has no such limit.
+ *                   + 2^-47 |C_ij|
+ * (fixed-point rounding, final rounding).  Rows and columns spanning 40
+ * binades measured 2^-11.3 normwise, inside this bound; the FMA loop has no
+ * such limit.
  * Inputs must be finite float-float numbers with |lo| <= ulp(hi).
- * Workspace: 0 bytes for the FMA loop; digit planes (7 (M+N) K bytes for
- * int8, twice that for BF16, rounded up to 64-row / 64-byte tiles) plus
- * scales for the sliced paths.
+ * Workspace: 0 bytes for the FMA loop; residue planes (16 (M+N) K bytes for
+ * int8, twice that for BF16, and 16 M N bytes for the product, M, N and K
+ * rounded up to tiles) plus scales for the sliced paths.
  * Errors: FF_ERR_SIZE, FF_ERR_NULL, FF_ERR_ALIGN, FF_ERR_ARG (algo),
  * FF_ERR_WORKSPACE, FF_ERR_HIP.
  */

@@ -799,11 +799,12 @@ def ff_gemm(A: torch.Tensor, B: torch.Tensor, algo: int = GEMM_SLICED_I8, out=No
     """C = A B for float-float matrices A (2, M, K) and B (2, K, N).
 
     GEMM_SLICED_I8 (default) and GEMM_SLICED_BF16 scale each row of A and
-    column of B by a power of two and cut it into 7 signed 8-bit digits, so
-    an entry keeps the bits above 2^-56 of its row's (column's) largest
-    entry: |C - exact| <= 2^-44 |A||B| elementwise for rows and columns of
-    moderate dynamic range (normal(0,1) data at 4096^3: 2^-51.6), with the
-    general bound in include/ff.h otherwise.  For rows or columns whose
+    column of B by a power of two and round it to 54-bit fixed point (an
+    entry keeps the bits above 2^-54 of its row's or column's largest entry),
+    then form the integer product exactly, modulo sixteen integers:
+    |C - exact| <= 2^-44 |A||B| elementwise for rows and columns of moderate
+    dynamic range (normal(0,1) data at 4096^3: 2^-51.6), with the general bound
+    in include/ff.h otherwise.  For rows or columns whose
     small entries matter 2^40 below their largest, use GEMM_FMA_LOOP (the
     plain Add22/Mul22 loop, about 17 times slower at 4096^3)."""
     M, K, lda = _check_matrix(A)

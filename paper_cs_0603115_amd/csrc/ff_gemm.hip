@@ -11,34 +11,35 @@
 // Sliced (the fast path; the paper has no GEMM): every entry of A and B is
 // turned into a signed fixed-point integer relative to a power of two of its
 // row (A) or column (B):
-//     X_ik = round(A_ik 2^(P - e_i)),  2^e_i > max_k |A_ik|,  P = 8S - 2,
-// and X is written as S = 7 signed 8-bit digits, X = sum_t d_t 256^(S-1-t).
-// A_ik B_kj then expands into digit products d_t d'_u of weight
-// 256^(2S-2-t-u); the pairs with t + u <= S - 1 (28 of 49) are kept.  Each
-// pair is an integer GEMM on matrix cores:
-//   * int8 digits, v_mfma_i32_32x32x32_i8, int32 accumulation;
-//   * BF16 digits (integers |d| <= 128 are exact in BF16),
-//     v_mfma_f32_32x32x16_bf16, FP32 accumulation folded every 128 k,
-//     before any partial sum can exceed 2^24, into one exact 96-bit integer
-//     per output, T += sum_D S_D 256^(6-D).
-// All partial sums are exact integers, so the hardware's accumulation order
-// does not matter.  Pairs on the same anti-diagonal D = t + u share one
-// accumulator (same weight): |S_D| <= 7 K 2^14 < 2^31 for K <= 16384 (longer
-// K is split into chunks summed with Add22).  The epilogue forms the exact
-// 128-bit integer T = sum_D S_D 256^(6-D) and rounds it once to float-float:
-//     C_ij ~ T 2^(e_i + f_j - 2P + 48).
-// No binary64 arithmetic is used anywhere.  Error sources: rounding of X (at
-// most one unit of 2^(e_i - P) per entry), the dropped pairs (< 2^-47 of
-// 2^(e_i + f_j) K), and the final rounding (2^-48 |C_ij|).
+//     X_ik = round(A_ik 2^(54 - e_i)),  2^e_i > max_k |A_ik|,
+// and the integer product X Y is formed exactly in a residue number system:
+// modulo sixteen pairwise coprime integers m up to 256 (ff_gemm_residue.h),
+// whose product P = 2^125.37 exceeds twice the largest sum of 16384 products.
+// Each modulus is one plain integer GEMM on matrix cores,
+//   * int8 residues, v_mfma_i32_32x32x32_i8, int32 accumulation;
+//   * BF16 residues (integers |r| <= 128 are exact in BF16),
+//     v_mfma_f32_32x32x16_bf16, FP32 accumulation reduced mod m every 512 k,
+//     before any partial sum can exceed 2^24,
+// its sums are reduced mod m to one byte per output and modulus, and a last
+// pass puts the sixteen bytes of an output together to the 128-bit integer
+// T = sum_k X_ik Y_kj and rounds it once to float-float:
+//     C_ij ~ T 2^(e_i + f_j - 108).
+// K beyond 16384 is split into chunks summed with Add22.  No binary64
+// arithmetic is used anywhere.  Error sources: rounding of X (at most one
+// unit of 2^(e_i - 54) per entry) and the final rounding (2^-48 |C_ij|).
 //
-// Data layout of the digit planes (workspace): for each slice t and tile of
-// 64 rows of A (or 64 columns of B) by one K-stage of 32 bytes (32 int8 or 16
-// BF16 digits: one matrix-core K-step), the 2 KiB tile is contiguous, so a
-// stage is copied into LDS with straight 1 KiB wavefront loads; within a row
-// the two 16-byte chunks are swapped on a row pattern (tile_swizzle) so that
-// the operand reads hit distinct LDS banks.  B is stored transposed (K
-// contiguous per column).
+// Why residues: sixteen products instead of the 28 digit-pair products that
+// seven 8-bit digits per operand need for the same 54 bits (and those drop
+// the 21 pairs below 2^-56).  The matrix products are bound by the power that
+// the matrix cores draw (the chip clocks down to 1.7-1.8 GHz under either
+// form), so fewer products is what counts: at 4096^3 the product kernel takes
+// 0.91 ms against 1.55 ms for the digit pairs, and the other passes over the
+// planes 0.36 against 0.20 ms.
+//
+// Four launches per chunk of K: partial maxima, residue planes, products,
+// reconstruction (the first two once per call).
 #include "ff_device.h"
+#include "ff_gemm_residue.h"
 #include "ff_host.h"
 
 namespace ffk {
@@ -121,13 +122,11 @@ __global__ __launch_bounds__(256) void gemm_fma_loop(int64_t M, int64_t N, int64
 
 // ---------------------------------------------------------------- sliced
 
-constexpr int kS = 7;                 // digits per operand
-constexpr int kP = 8 * kS - 2;        // fixed-point bits: |X| <= 2^kP
-constexpr int kTile = 64;             // rows (A) / columns (B) per tile
-constexpr int kRowBytes = 32;         // digit bytes of one tile row per K-stage
-constexpr int kTileBytes = kTile * kRowBytes;       // 2 KiB
-constexpr int kEpiShift = 8 * (kS - 1) - 2 * kP;   // C = T 2^(e + f + kEpiShift)
-constexpr int64_t kMaxKChunk = 16384; // int32 accumulators stay exact below this
+constexpr int kP = 54;                // fixed-point bits: |X| <= 2^kP
+constexpr int64_t kMaxKChunk = 16384; // sums of this many products stay below P / 2
+constexpr int kBlk = 32;              // rows (or columns) of one matrix-core operand
+constexpr int kFragBytes = 1024;      // one operand: 32 rows by 32 bytes of K
+constexpr int kStageFrags = 2;        // operands per block of rows and stage
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
@@ -136,18 +135,18 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
 typedef const __attribute__((address_space(1))) void *global_void_ptr;
 
-struct DigitsI8 {
+struct ResiduesI8 {
+    using Acc = i32x16;
     static constexpr int kEsize = 1;
-    static constexpr int kStageK = kRowBytes;      // 32 digits: one i8 MFMA K-step
-    static constexpr int kExtractStages = 0;       // int32 accumulation: never
+    static constexpr int kFragK = 32;      // K of one operand
+    static constexpr int kFoldStages = 0;  // int32 sums: |S| <= 2^14 K <= 2^28
 };
-struct DigitsBF16 {
+struct ResiduesBF16 {
+    using Acc = f32x16;
     static constexpr int kEsize = 2;
-    static constexpr int kStageK = kRowBytes / 2;  // 16 digits: one BF16 MFMA K-step
-    static constexpr int kExtractStages = 8;       // drain FP32 every 128 k
+    static constexpr int kFragK = 16;
+    static constexpr int kFoldStages = 16; // FP32 sums folded every 512 k: |S| <= 2^23 + 128
 };
-
-__device__ __forceinline__ uint32_t f32_bits(float v) { return __float_as_uint(v); }
 
 // Smallest e with |x| < 2^e for every x with |x| <= the value of bits ub.
 __device__ __forceinline__ int exponent_bound(uint32_t ub)
@@ -158,662 +157,598 @@ __device__ __forceinline__ int exponent_bound(uint32_t ub)
     return be == 0 ? -126 : be - 126;
 }
 
-// round(v * 2^scale_exp) as an integer (ties away from zero), saturating
-// far outside the digit range.
-__device__ __forceinline__ int64_t fixed_round(float v, int scale_exp)
-{
-    const uint32_t b = f32_bits(v);
-    int be = static_cast<int>((b >> 23) & 255u);
-    int64_t mant = b & 0x7fffffu;
-    if (be == 0) {
-        if (mant == 0)
-            return 0;
-        be = 1;
-    } else {
-        mant |= 0x800000;
-    }
-    const int sh = be - 150 + scale_exp;      // v = mant * 2^(be - 150)
-    int64_t m;
-    if (sh >= 0)
-        m = mant << (sh < 38 ? sh : 38);
-    else if (sh > -40)
-        m = (mant + (int64_t(1) << (-sh - 1))) >> (-sh);
-    else
-        m = 0;
-    return (b >> 31) ? -m : m;
-}
+// Partial maxima of |hi| (as bits): workgroups [0, row_groups) take four rows
+// of A each by a 4096-k segment, one wavefront per row; the others take 64
+// columns of B by a band of kColBand rows, four row groups of threads.
+constexpr int kRowSegment = 4096;
+constexpr int kColBand = 128;
 
-// Digits of one float-float entry: d[0] most significant.
-__device__ __forceinline__ void entry_digits(float hi, float lo, int e, int d[kS])
-{
-    const int se = kP - e;
-    int64_t X = fixed_round(hi, se) + fixed_round(lo, se);
-    const int64_t lim = int64_t(127) << (8 * (kS - 1));
-    X = X > lim ? lim : (X < -lim ? -lim : X);
-#pragma unroll
-    for (int t = kS - 1; t >= 0; --t) {
-        const int64_t dt = ((X + 128) & 255) - 128;
-        d[t] = static_cast<int>(dt);
-        X = (X - dt) >> 8;
-    }
-}
-
-// Bit pattern of digit d in the plane's element type.
-template <class Dg>
-__device__ __forceinline__ uint32_t digit_bits(int d)
-{
-    if constexpr (Dg::kEsize == 1)
-        return static_cast<uint32_t>(d) & 0xffu;
-    else
-        // |d| <= 128 has at most 8 significant bits: the BF16 pattern is the
-        // upper half of the binary32 pattern, exactly.
-        return f32_bits(static_cast<float>(d)) >> 16;
-}
-
-// Byte offset of (row, 16-byte chunk) inside a 2 KiB tile.  Rows are 32
-// bytes; the two chunks of a row are swapped when bit 2 xor bit 3 of the row
-// is set.  The operand reads take 16 consecutive rows at one logical chunk
-// per 256-byte LDS cycle (64 banks of 4 bytes on gfx950): rows r and r + 8
-// share a bank group unless their chunks differ, which this swizzle
-// guarantees -- and 8-row groups stay conflict-free as well.
-__device__ __forceinline__ int tile_swizzle(int row, int chunk)
-{
-    return row * kRowBytes + ((chunk ^ (((row >> 2) ^ (row >> 3)) & 1)) * 16);
-}
-
-__device__ __forceinline__ int64_t tile_base(int t, int bi, int bk, int nB, int nBK)
-{
-    return ((static_cast<int64_t>(t) * nB + bi) * nBK + bk) * kTileBytes;
-}
-
-__global__ __launch_bounds__(256) void fill_u32(uint32_t *p, int64_t n)
-{
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * 256)
-        p[i] = 0u;
-}
-
-// rowmax[i] = max_k |A_hi[i, k]| (as bits).  One wavefront per (row, 4096-k
-// segment), 16-byte loads when the rows are 16-byte aligned; integer
-// atomicMax, so the result does not depend on order.
 template <bool VEC>
-__global__ __launch_bounds__(256) void absmax_rows(int64_t M, int64_t K,
-                                                   const float *__restrict__ Ah, int64_t lda,
-                                                   uint32_t *__restrict__ rowmax)
+__global__ __launch_bounds__(256) void absmax_partials(
+    int64_t M, int64_t N, int64_t K, const float *__restrict__ Ah, int64_t lda,
+    const float *__restrict__ Bh, int64_t ldb, int64_t row_groups, int64_t col_groups,
+    uint32_t *__restrict__ rowpart, uint32_t *__restrict__ colpart)
 {
-    const int64_t row = static_cast<int64_t>(blockIdx.y) * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (row >= M)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t rgrid = row_groups * ((K + kRowSegment - 1) / kRowSegment);
+    int64_t b = blockIdx.x;
+    if (b < rgrid) {
+        const int64_t seg = b / row_groups;
+        const int64_t row = (b % row_groups) * 4 + wave;
+        if (row >= M)
+            return;
+        const int64_t k0 = seg * kRowSegment;
+        const int64_t k1 = (k0 + kRowSegment < K) ? k0 + kRowSegment : K;
+        const float *a = Ah + row * lda;
+        uint32_t m = 0;
+        int64_t k = k0;
+        if (VEC) {
+            const int64_t kv = k0 + ((k1 - k0) & ~int64_t(255));   // whole 256-entry steps
+            for (k = k0 + 4 * lane; k < kv; k += 256) {
+                const float4 v = *reinterpret_cast<const float4 *>(a + k);
+                m = max(m, max(max(__float_as_uint(v.x) & 0x7fffffffu,
+                                   __float_as_uint(v.y) & 0x7fffffffu),
+                               max(__float_as_uint(v.z) & 0x7fffffffu,
+                                   __float_as_uint(v.w) & 0x7fffffffu)));
+            }
+            k = kv;
+        }
+#pragma unroll 4
+        for (k += lane; k < k1; k += 64)
+            m = max(m, __float_as_uint(a[k]) & 0x7fffffffu);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1)
+            m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), off, 64)));
+        if (lane == 0)
+            rowpart[seg * M + row] = m;
         return;
-    const int64_t k0 = static_cast<int64_t>(blockIdx.x) * 4096;
-    const int64_t k1 = (k0 + 4096 < K) ? k0 + 4096 : K;
-    const float *a = Ah + row * lda;
+    }
+    __shared__ uint32_t part[4][64];
+    b -= rgrid;
+    const int64_t band = b / col_groups;
+    const int64_t j = (b % col_groups) * 64 + lane;
+    const int64_t k0 = band * kColBand + wave * (kColBand / 4);
     uint32_t m = 0;
-    if (VEC) {
-        const int64_t kv = k0 + ((k1 - k0) & ~int64_t(255));   // whole 256-entry steps
-        for (int64_t k = k0 + 4 * lane; k < kv; k += 256) {
-            const float4 v = *reinterpret_cast<const float4 *>(a + k);
-            m = max(m, max(max(f32_bits(v.x) & 0x7fffffffu, f32_bits(v.y) & 0x7fffffffu),
-                           max(f32_bits(v.z) & 0x7fffffffu, f32_bits(v.w) & 0x7fffffffu)));
-        }
-        for (int64_t k = kv + lane; k < k1; k += 64)
-            m = max(m, f32_bits(a[k]) & 0x7fffffffu);
-    } else {
-        for (int64_t k = k0 + lane; k < k1; k += 64)
-            m = max(m, f32_bits(a[k]) & 0x7fffffffu);
+    if (j < N) {
+        const float *p = Bh + k0 * ldb + j;
+#pragma unroll 8
+        for (int k = 0; k < kColBand / 4; ++k)
+            if (k0 + k < K)
+                m = max(m, __float_as_uint(p[k * ldb]) & 0x7fffffffu);
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), off, 64)));
-    if (lane == 0 && m)
-        atomicMax(&rowmax[row], m);
+    part[wave][lane] = m;
+    __syncthreads();
+    if (wave == 0 && j < N)
+        colpart[band * N + j] = max(max(part[0][lane], part[1][lane]),
+                                    max(part[2][lane], part[3][lane]));
 }
 
-// colmax[j] = max_k |B_hi[k, j]|: thread per column, 64-row bands, eight
-// independent loads in flight per thread.
-__global__ __launch_bounds__(256) void absmax_cols(int64_t K, int64_t N,
-                                                   const float *__restrict__ Bh, int64_t ldb,
-                                                   uint32_t *__restrict__ colmax)
-{
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (j >= N)
-        return;
-    const int64_t k0 = static_cast<int64_t>(blockIdx.y) * 64;
-    const int64_t k1 = (k0 + 64 < K) ? k0 + 64 : K;
-    uint32_t m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int64_t k = k0;
-    for (; k + 8 <= k1; k += 8) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            m[u] = max(m[u], f32_bits(Bh[(k + u) * ldb + j]) & 0x7fffffffu);
-    }
-    for (; k < k1; ++k)
-        m[0] = max(m[0], f32_bits(Bh[k * ldb + j]) & 0x7fffffffu);
-    uint32_t r = 0;
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-        r = max(r, m[u]);
-    if (r)
-        atomicMax(&colmax[j], r);
-}
+// Residue planes.  Plane i of an operand holds its residues mod m_i as the
+// matrix cores read them: for each block of 32 rows of A (columns of B) and
+// each K-step of 32 bytes one contiguous 1 KiB operand, in which lane l of a
+// wavefront finds its 16 bytes at 16 l: row l % 32, the K bytes 16 (l / 32)
+// onwards.  Copying an operand into LDS and reading it back are then both
+// straight 1 KiB accesses, free of bank conflicts without a swizzle.
+// A workgroup writes kResidueFrags consecutive operands of one block in all
+// sixteen planes; a thread takes four K-neighbours of one row, so that a
+// wavefront's store covers 256 (int8) or 512 (BF16) consecutive bytes.
+// Rows beyond M (columns beyond N) and entries beyond K are zero.
+constexpr int kResidueFrags = 4;
 
-// One 16-byte chunk of every slice for the entries (r, k0 .. k0 + per - 1)
-// of a row (A) or column (B): packs the digits into four 32-bit words per
-// slice and stores them at the swizzled tile position.
-template <class Dg, class Load>
-__device__ __forceinline__ void slice_chunk(Load load, bool row_ok, int64_t k0, int64_t K, int e,
-                                            uint8_t *__restrict__ planes, int64_t plane_tile0,
-                                            int64_t slice_stride, int in_tile)
+template <class Dg>
+__device__ __forceinline__ void store_residues(const float (&hi)[4], const float (&lo)[4], int e,
+                                               uint8_t *__restrict__ dst, int64_t plane)
 {
-    constexpr int kPer = 16 / Dg::kEsize;         // digits per chunk
-    constexpr int kPerWord = 4 / Dg::kEsize;      // digits per 32-bit word
-    uint32_t w[kS][4];
+    uint32_t dl[4], dh[4];
 #pragma unroll
-    for (int t = 0; t < kS; ++t)
+    for (int q = 0; q < 4; ++q)
+        entry_digits(hi[q], lo[q], e, dl[q], dh[q]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            w[t][q] = 0u;
+    for (int i = 0; i < kModuli; ++i) {
+        constexpr ResidueTables tab = kResidue;
+        const int m = kModulus[i];
+        const float inv = 1.0f / static_cast<float>(m);
+        if constexpr (Dg::kEsize == 1) {
+            uint32_t r[4];
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        const int64_t k = k0 + q;
-        int d[kS];
-        if (row_ok && k < K) {
-            float hi, lo;
-            load(k, hi, lo);
-            entry_digits(hi, lo, e, d);
+            for (int q = 0; q < 4; ++q) {
+                if (m == 256)
+                    r[q] = dl[q];   // the lowest digit
+                else
+                    r[q] = reduce_low_byte(
+                        dot4(dh[q], tab.digit_hi[i], dot4(dl[q], tab.digit_lo[i], 0)), m, inv);
+            }
+            *reinterpret_cast<uint32_t *>(dst + i * plane) =
+                pack_low_bytes(r[0], r[1], r[2], r[3]);
         } else {
+            // |r| <= 128 has at most 8 significant bits: its BF16 pattern is
+            // the upper half of the binary32 pattern, exactly
+            uint32_t r[4];
 #pragma unroll
-            for (int t = 0; t < kS; ++t)
-                d[t] = 0;
-        }
-#pragma unroll
-        for (int t = 0; t < kS; ++t)
-            w[t][q / kPerWord] |= digit_bits<Dg>(d[t]) << (8 * Dg::kEsize * (q % kPerWord));
-    }
-#pragma unroll
-    for (int t = 0; t < kS; ++t)
-        *reinterpret_cast<uint4 *>(planes + plane_tile0 + t * slice_stride + in_tile) =
-            make_uint4(w[t][0], w[t][1], w[t][2], w[t][3]);
-}
-
-// A digit planes: workgroup = (64-row tile, K stage), 128 threads, thread =
-// (row, chunk).
-// Digit planes of A.  A workgroup covers 32 rows by 8 consecutive 16-byte
-// chunks (4 K-stages) of each row; a thread converts one chunk: kPer
-// consecutive entries of its row, read with 16-byte loads when the rows are
-// 16-byte aligned (adjacent threads read adjacent 64- or 32-byte pieces of
-// the row).  Rows at or beyond M and entries at or beyond K give zero
-// digits (the tiles are padded).
-template <class Dg>
-__global__ __launch_bounds__(256) void slice_rows(int64_t M, int64_t K,
-                                                  const float *__restrict__ Ah,
-                                                  const float *__restrict__ Al, int64_t lda,
-                                                  const uint32_t *__restrict__ rowmax, int nBI,
-                                                  int nBK, uint8_t *__restrict__ planes, int vec)
-{
-    constexpr int kPer = 16 / Dg::kEsize;                 // entries per chunk
-    constexpr int kChunks = Dg::kStageK / kPer;           // chunks per K-stage (2)
-    const int c = threadIdx.x & 7;
-    const int64_t i = static_cast<int64_t>(blockIdx.y) * 32 + (threadIdx.x >> 3);
-    const int64_t kc = static_cast<int64_t>(blockIdx.x) * 8 + c;
-    const int bk = static_cast<int>(kc / kChunks), chunk = static_cast<int>(kc % kChunks);
-    if (bk >= nBK || i >= static_cast<int64_t>(nBI) * kTile)
-        return;
-    const bool ok = i < M;
-    const int e = ok ? exponent_bound(rowmax[i]) : 0;
-    const int64_t k0 = kc * kPer;
-    const int bi = static_cast<int>(i / kTile), row = static_cast<int>(i % kTile);
-    const int64_t slice_stride = static_cast<int64_t>(nBI) * nBK * kTileBytes;
-    const int in_tile = tile_swizzle(row, chunk);
-    if (vec && ok && k0 + kPer <= K) {
-        float hv[kPer], lv[kPer];
-#pragma unroll
-        for (int q = 0; q < kPer; q += 4) {
-            const float4 h4 = *reinterpret_cast<const float4 *>(Ah + i * lda + k0 + q);
-            const float4 l4 = *reinterpret_cast<const float4 *>(Al + i * lda + k0 + q);
-            hv[q] = h4.x; hv[q + 1] = h4.y; hv[q + 2] = h4.z; hv[q + 3] = h4.w;
-            lv[q] = l4.x; lv[q + 1] = l4.y; lv[q + 2] = l4.z; lv[q + 3] = l4.w;
-        }
-        auto load = [&](int64_t k, float &hi, float &lo) {
-            hi = hv[k - k0];
-            lo = lv[k - k0];
-        };
-        slice_chunk<Dg>(load, true, k0, K, e, planes, tile_base(0, bi, bk, nBI, nBK),
-                        slice_stride, in_tile);
-    } else {
-        auto load = [&](int64_t k, float &hi, float &lo) {
-            hi = Ah[i * lda + k];
-            lo = Al[i * lda + k];
-        };
-        slice_chunk<Dg>(load, ok, k0, K, e, planes, tile_base(0, bi, bk, nBI, nBK),
-                        slice_stride, in_tile);
-    }
-}
-template <class Dg>
-__global__ __launch_bounds__(128) void slice_cols(int64_t K, int64_t N,
-                                                  const float *__restrict__ Bh,
-                                                  const float *__restrict__ Bl, int64_t ldb,
-                                                  const uint32_t *__restrict__ colmax, int nBJ,
-                                                  int nBK, uint8_t *__restrict__ planes)
-{
-    const int bk = blockIdx.x, bj = blockIdx.y;
-    const int col = threadIdx.x & 63, chunk = threadIdx.x >> 6;
-    const int64_t j = static_cast<int64_t>(bj) * kTile + col;
-    const bool ok = j < N;
-    const int e = ok ? exponent_bound(colmax[j]) : 0;
-    const int64_t k0 = static_cast<int64_t>(bk) * Dg::kStageK + chunk * (16 / Dg::kEsize);
-    auto load = [&](int64_t k, float &hi, float &lo) {
-        hi = Bh[k * ldb + j];
-        lo = Bl[k * ldb + j];
-    };
-    slice_chunk<Dg>(load, ok, k0, K, e, planes, tile_base(0, bj, bk, nBJ, nBK),
-                    static_cast<int64_t>(nBJ) * nBK * kTileBytes, tile_swizzle(col, chunk));
-}
-
-// Round the integer t to 24 bits, nearest-even: t ~ mant 2^E (E >= 0).
-__device__ __forceinline__ void round_i128(__int128 t, int &neg, uint32_t &mant, int &E)
-{
-    neg = t < 0;
-    const unsigned __int128 u = neg ? static_cast<unsigned __int128>(-t)
-                                    : static_cast<unsigned __int128>(t);
-    const uint64_t hi = static_cast<uint64_t>(u >> 64), lo = static_cast<uint64_t>(u);
-    const int nbits = hi ? 128 - __builtin_clzll(hi) : (lo ? 64 - __builtin_clzll(lo) : 0);
-    if (nbits <= 24) {
-        mant = static_cast<uint32_t>(lo);
-        E = 0;
-        return;
-    }
-    int sh = nbits - 24;
-    unsigned __int128 m = u >> sh;
-    const unsigned __int128 rem = u - (m << sh);
-    const unsigned __int128 half = static_cast<unsigned __int128>(1) << (sh - 1);
-    if (rem > half || (rem == half && (m & 1))) {
-        m += 1;
-        if (m >> 24) {
-            m >>= 1;
-            sh += 1;
+            for (int q = 0; q < 4; ++q) {
+                float f;
+                if (m == 256) {
+                    f = static_cast<float>(static_cast<int8_t>(dl[q]));
+                } else {
+                    const float s = static_cast<float>(
+                        dot4(dh[q], tab.digit_hi[i], dot4(dl[q], tab.digit_lo[i], 0)));
+                    const float n = __builtin_fmaf(s, inv, kRoundMagic) - kRoundMagic;
+                    f = __builtin_fmaf(n, -static_cast<float>(m), s);
+                }
+                r[q] = __float_as_uint(f);
+            }
+            *reinterpret_cast<uint2 *>(dst + i * plane) =
+                make_uint2(__builtin_amdgcn_perm(r[1], r[0], 0x07060302u),
+                           __builtin_amdgcn_perm(r[3], r[2], 0x07060302u));
         }
     }
-    mant = static_cast<uint32_t>(m);
-    E = sh;
 }
 
-// (hi, lo) = (RN(T), RN(T - RN(T))) * 2^scale.
-__device__ __forceinline__ void i128_to_ff(__int128 T, int scale, float &hi, float &lo)
+template <class Dg, bool VEC>
+__global__ __launch_bounds__(256) void residue_planes(
+    int64_t M, int64_t N, int64_t K, const float *__restrict__ Ah, const float *__restrict__ Al,
+    int64_t lda, const float *__restrict__ Bh, const float *__restrict__ Bl, int64_t ldb, int nRB,
+    int nCB, int nKB, const uint32_t *__restrict__ rowpart, const uint32_t *__restrict__ colpart,
+    int nseg, int nband, int *__restrict__ rowexp, int *__restrict__ colexp,
+    uint8_t *__restrict__ Ap, uint8_t *__restrict__ Bp)
 {
-    int neg, E;
-    uint32_t mant;
-    round_i128(T, neg, mant, E);
-    const __int128 top = static_cast<__int128>(mant) << E;
-    const __int128 rem = T - (neg ? -top : top);
-    const float h = __builtin_ldexpf(static_cast<float>(mant), E + scale);
-    hi = neg ? -h : h;
-    int rneg, rE;
-    uint32_t rmant;
-    round_i128(rem, rneg, rmant, rE);
-    const float l = __builtin_ldexpf(static_cast<float>(rmant), rE + scale);
-    lo = rneg ? -l : l;
+    constexpr int kQ = 16 / Dg::kEsize / 4;          // threads per row and 16-byte piece
+    constexpr int kFragThreads = 2 * kBlk * kQ;      // threads per operand
+    constexpr int kAtOnce = 256 / kFragThreads;
+    __shared__ uint32_t part[8][kBlk];
+    __shared__ int exps[kBlk];
+    const int t = threadIdx.x;
+    const int groups = (nKB + kResidueFrags - 1) / kResidueFrags;
+    const int64_t b = blockIdx.x;
+    const int64_t blk_all = b / groups;
+    const int kb0 = static_cast<int>(b % groups) * kResidueFrags;
+    const bool is_a = blk_all < nRB;
+    const int64_t blk = is_a ? blk_all : blk_all - nRB;
+    const int64_t limit = is_a ? M : N;
+    {
+        // the block's 32 exponents from the partial maxima
+        const int64_t r = blk * kBlk + (t & 31);
+        const uint32_t *src = is_a ? rowpart : colpart;
+        const int n = is_a ? nseg : nband;
+        uint32_t m = 0;
+        if (r < limit)
+            for (int s = t >> 5; s < n; s += 8)
+                m = max(m, src[s * limit + r]);
+        part[t >> 5][t & 31] = m;
+        __syncthreads();
+        if (t < kBlk) {
+            for (int s = 1; s < 8; ++s)
+                m = max(m, part[s][t]);
+            const int e = exponent_bound(m);
+            exps[t] = e;
+            if (kb0 == 0 && r < limit)
+                (is_a ? rowexp : colexp)[r] = e;
+        }
+        __syncthreads();
+    }
+    const int in_frag = t % kFragThreads;
+    const int half = in_frag / (kBlk * kQ), row = in_frag / kQ % kBlk, q = in_frag % kQ;
+    const int64_t r = blk * kBlk + row;
+    const int e = exps[row];
+    const int64_t plane =
+        static_cast<int64_t>(is_a ? nRB : nCB) * nKB * kFragBytes;
+    uint8_t *const base = (is_a ? Ap : Bp) + blk * nKB * kFragBytes + in_frag * (4 * Dg::kEsize);
+#pragma unroll 1
+    for (int f = t / kFragThreads; f < kResidueFrags; f += kAtOnce) {
+        const int kb = kb0 + f;
+        if (kb >= nKB)
+            break;
+        const int64_t k = static_cast<int64_t>(kb) * Dg::kFragK + half * (Dg::kFragK / 2) + 4 * q;
+        float hi[4] = {0, 0, 0, 0}, lo[4] = {0, 0, 0, 0};
+        if (r < limit) {
+            if (is_a) {
+                const float *h = Ah + r * lda + k, *l = Al + r * lda + k;
+                if (VEC && k + 4 <= K) {
+                    const float4 h4 = *reinterpret_cast<const float4 *>(h);
+                    const float4 l4 = *reinterpret_cast<const float4 *>(l);
+                    hi[0] = h4.x; hi[1] = h4.y; hi[2] = h4.z; hi[3] = h4.w;
+                    lo[0] = l4.x; lo[1] = l4.y; lo[2] = l4.z; lo[3] = l4.w;
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (k + u < K) {
+                            hi[u] = h[u];
+                            lo[u] = l[u];
+                        }
+                }
+            } else {
+                const float *h = Bh + k * ldb + r, *l = Bl + k * ldb + r;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (k + u < K) {
+                        hi[u] = h[u * ldb];
+                        lo[u] = l[u * ldb];
+                    }
+            }
+        }
+        store_residues<Dg>(hi, lo, e, base + static_cast<int64_t>(kb) * kFragBytes, plane);
+    }
 }
 
-__device__ __forceinline__ i32x16 mma(const uint4 &a, const uint4 &b, const i32x16 &c, DigitsI8)
+__device__ __forceinline__ i32x16 mma(const uint4 &a, const uint4 &b, const i32x16 &c)
 {
     return __builtin_amdgcn_mfma_i32_32x32x32_i8(*reinterpret_cast<const i32x4 *>(&a),
                                                  *reinterpret_cast<const i32x4 *>(&b), c, 0, 0,
                                                  0);
 }
-__device__ __forceinline__ f32x16 mma(const uint4 &a, const uint4 &b, const f32x16 &c,
-                                      DigitsBF16)
+__device__ __forceinline__ f32x16 mma(const uint4 &a, const uint4 &b, const f32x16 &c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(&a),
                                                    *reinterpret_cast<const bf16x8 *>(&b), c, 0,
                                                    0, 0);
 }
 
-template <class Dg> struct AccOf;
-template <> struct AccOf<DigitsI8> { using T = i32x16; };
-template <> struct AccOf<DigitsBF16> { using T = f32x16; };
-
-// One LDS slot of the stage ring.  Each slot is a distinct LDS variable, so
-// the compiler can tell a slot being read from one being filled by DMA.
-template <int BYTES, int I>
-__device__ __forceinline__ uint8_t *lds_slot()
+// One LDS DMA: 16 bytes per lane from `from + lane_off` to LDS bytes `to +
+// 16 lane` (global_load_lds_dwordx4).  In assembly, so that the compiler does
+// not track the LDS it writes and put waits for every DMA in flight before
+// the reads of other stages: the waits are the kernel's own.  It has no
+// register result, and a wait the compiler places for a load of its own can
+// only become stricter by the operations it does not count.
+__device__ __forceinline__ void lds_dma16(const uint8_t *from, uint32_t lane_off, uint32_t to)
 {
-    __shared__ uint4 slot[BYTES / 16];
-    return reinterpret_cast<uint8_t *>(slot);
+    asm volatile("s_mov_b32 m0, %0\n\t"
+                 "s_nop 0\n\t"
+                 "global_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(to), "v"(lane_off), "s"(from)
+                 : "memory");
 }
-
-// Epilogue of a wavefront's 32 x 32 block: lane holds
-// C[8*(r/4) + 4*(lane/32) + (r%4)][lane%32] for r = 0..15 as S diagonal sums;
-// T = sum_D S_D 256^(S-1-D) is formed exactly and rounded once to
-// float-float, then scaled by the row and column powers of two (and added
-// to C with Add22 for the later K-chunks).
-template <class Dg, int WM, int WN, class Acc>
-__device__ __forceinline__ void store_block(const Acc (&acc)[kS], const i32x16 (&iacc)[kS],
-                                            int64_t M, int64_t N, int bi, int bj, int wm, int wn,
-                                            int lane, const uint32_t *__restrict__ rowmax,
-                                            const uint32_t *__restrict__ colmax,
-                                            float *__restrict__ Ch, float *__restrict__ Cl,
-                                            int64_t ldc, int accumulate)
-{
-    const int64_t j = static_cast<int64_t>(bj) * (32 * WN) + wn * 32 + (lane & 31);
-    const int fj = j < N ? exponent_bound(colmax[j]) : 0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int m = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int64_t i = static_cast<int64_t>(bi) * (32 * WM) + wm * 32 + m;
-        if (i >= M || j >= N)
-            continue;
-        __int128 T = 0;
-#pragma unroll
-        for (int d = 0; d < kS; ++d) {
-            int sd;
-            if constexpr (Dg::kExtractStages > 0)
-                sd = iacc[d][r];
-            else
-                sd = acc[d][r];
-            T = (T << 8) + static_cast<__int128>(sd);
-        }
-        float h, l;
-        i128_to_ff(T, exponent_bound(rowmax[i]) + fj + kEpiShift, h, l);
-        if (accumulate)
-            ffd::add22(Ch[i * ldc + j], Cl[i * ldc + j], h, l, h, l);
-        Ch[i * ldc + j] = h;
-        Cl[i * ldc + j] = l;
-    }
-}
-
-// As store_block, with T already formed (96-bit two's complement words).
-template <int WM, int WN>
-__device__ __forceinline__ void store_block_t96(const uint32_t (&t96)[16][3], int64_t M,
-                                                int64_t N, int bi, int bj, int wm, int wn,
-                                                int lane, const uint32_t *__restrict__ rowmax,
-                                                const uint32_t *__restrict__ colmax,
-                                                float *__restrict__ Ch, float *__restrict__ Cl,
-                                                int64_t ldc, int accumulate)
-{
-    const int64_t j = static_cast<int64_t>(bj) * (32 * WN) + wn * 32 + (lane & 31);
-    const int fj = j < N ? exponent_bound(colmax[j]) : 0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int m = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int64_t i = static_cast<int64_t>(bi) * (32 * WM) + wm * 32 + m;
-        if (i >= M || j >= N)
-            continue;
-        __int128 T = static_cast<__int128>(static_cast<int32_t>(t96[r][2]));
-        T = (T << 64) | (static_cast<__int128>(t96[r][1]) << 32) |
-            static_cast<__int128>(t96[r][0]);
-        float h, l;
-        i128_to_ff(T, exponent_bound(rowmax[i]) + fj + kEpiShift, h, l);
-        if (accumulate)
-            ffd::add22(Ch[i * ldc + j], Cl[i * ldc + j], h, l, h, l);
-        Ch[i * ldc + j] = h;
-        Cl[i * ldc + j] = l;
-    }
-}
-
-// Launch shape of the sliced product: WM x WN = 4 x 2 wavefronts (2 per
-// SIMD), each owning a 32 x 32 block of C as S diagonal accumulators, for a
-// 128 x 64 block per workgroup; a ring of 3 K-stages of 42 KiB in LDS.
-template <class Dg> struct SlicedShape {
-    static constexpr int WM = 4, WN = 2;
-};
 
 // s_waitcnt immediate that waits until at most n vector-memory operations of
 // this wavefront are outstanding (export and LDS counters left at maximum).
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
-// Workgroup barrier without a memory fence: the LDS DMA of the next stage
-// keeps flying across it (a __syncthreads fence would wait for it).  The
-// "memory" clobber keeps the compiler from moving LDS accesses across.
-__device__ __forceinline__ void barrier_no_fence() { asm volatile("s_barrier" ::: "memory"); }
-
 // s_waitcnt immediate that waits until at most n LDS operations of this
 // wavefront are outstanding.
 constexpr int lgkmcnt_imm(int n) { return 15 | (3 << 14) | (7 << 4) | ((n & 15) << 8); }
 
-// The sliced product with a ping-pong schedule (int8 digits, and BF16 digits
-// with exact 96-bit per-output drains).  The 8 wavefronts form two
-// groups (waves 0-3 and 4-7: one of each on every SIMD) that run half a
-// K-stage apart: while one group reads a stage's fragments from LDS, the
-// other runs the MFMAs of the fragments it read before, so the LDS reads
-// land under the matrix-core work of the other group.  Two barriers per
-// stage k:
-//   phase 1: group 0 reads stage k, then issues its share of the DMA of
-//            stage k + 2;  group 1 multiplies stage k - 1
-//   phase 2: group 0 multiplies stage k;  group 1 reads stage k, then
-//            issues its share of the DMA of stage k + 2
-// Three LDS slots: the DMA of stage k + 2 fills the slot of stage k - 1,
-// which both groups finished reading before the last barrier (group 1
-// waits for its reads to land before that barrier).  A wavefront waits for
-// its previous DMA share at the start of its next read phase, one stage
-// after issuing it, and so before the barrier that precedes any read of it.
-template <class Dg, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_sliced_pp(
-    int64_t M, int64_t N, int nBI, int nBJ, int nBK, int bk0, int bk1,
-    const uint8_t *__restrict__ Ap, const uint8_t *__restrict__ Bp,
-    const uint32_t *__restrict__ rowmax, const uint32_t *__restrict__ colmax,
-    float *__restrict__ Ch, float *__restrict__ Cl, int64_t ldc, int accumulate)
+// Workgroup barrier without a memory fence: the LDS DMA of the next stages
+// keeps flying across it (a __syncthreads fence would wait for it).  The
+// "memory" clobber keeps the compiler from moving LDS accesses across.
+__device__ __forceinline__ void barrier_no_fence() { asm volatile("s_barrier" ::: "memory"); }
+
+// Modulus i, from bytes (uniform across the workgroup).
+__device__ __forceinline__ int modulus_of(int i)
 {
-    using Acc = typename AccOf<Dg>::T;
-    constexpr bool kDrain = Dg::kExtractStages > 0;
-    constexpr int kWaves = WM * WN;
-    static_assert(kWaves == 8, "two groups of four wavefronts");
-    constexpr int kTA = WM / 2, kTB = WN / 2;
-    constexpr int kSlotBytes = kS * (kTA + kTB) * kTileBytes;
-    constexpr int kHalves = 2 * kS * (kTA + kTB);
-    constexpr int kQ = kHalves / kWaves, kR = kHalves % kWaves;
-    uint8_t *const slot0 = lds_slot<kSlotBytes, 0>();
-    uint8_t *const slot1 = lds_slot<kSlotBytes, 1>();
-    uint8_t *const slot2 = lds_slot<kSlotBytes, 2>();
-
-    const int bj = blockIdx.x, bi = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63;
-    // wavefront index as a scalar, so that the group test is a uniform branch
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
-    const int64_t a_slice = static_cast<int64_t>(nBI) * nBK * kTileBytes;
-    const int64_t b_slice = static_cast<int64_t>(nBJ) * nBK * kTileBytes;
-
-    Acc acc[kS];
-#pragma unroll
-    for (int d = 0; d < kS; ++d)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            acc[d][r] = 0;
-    // BF16 digits: the FP32 stage sums are exact only up to 2^24, so every
-    // kExtractStages stages they are folded into one exact integer per
-    // output, T += sum_D S_D 256^(S-1-D), kept as 96 bits (three words,
-    // two's complement): |T| < 7 K 2^14 2^49 < 2^78 for K <= 16384.
-    uint32_t t96[kDrain ? 16 : 1][3];
-#pragma unroll
-    for (int r = 0; r < (kDrain ? 16 : 1); ++r)
-        t96[r][0] = t96[r][1] = t96[r][2] = 0u;
-    auto drain = [&]() {
-        if constexpr (kDrain) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                __int128 t = 0;
-#pragma unroll
-                for (int d = 0; d < kS; ++d)
-                    t = (t << 8) + static_cast<__int128>(static_cast<int>(acc[d][r]));
-                __int128 T = static_cast<__int128>(static_cast<int32_t>(t96[r][2]));
-                T = (T << 64) | (static_cast<__int128>(t96[r][1]) << 32) |
-                    static_cast<__int128>(t96[r][0]);
-                T += t;
-                t96[r][0] = static_cast<uint32_t>(T);
-                t96[r][1] = static_cast<uint32_t>(T >> 32);
-                t96[r][2] = static_cast<uint32_t>(T >> 64);
-            }
-#pragma unroll
-            for (int d = 0; d < kS; ++d)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[d][r] = 0.0f;
-        }
+    constexpr auto word = [](int w) {
+        return static_cast<uint32_t>(kModulus[4 * w] - 1) |
+               static_cast<uint32_t>(kModulus[4 * w + 1] - 1) << 8 |
+               static_cast<uint32_t>(kModulus[4 * w + 2] - 1) << 16 |
+               static_cast<uint32_t>(kModulus[4 * w + 3] - 1) << 24;
     };
-    auto drain_due = [&](int bk) {
-        return kDrain && ((bk - bk0 + 1) % (kDrain ? Dg::kExtractStages : 1) == 0 || bk + 1 == bk1);
-    };
-
-    auto fetch = [&](int bk, uint8_t *slot) {
-#pragma unroll
-        for (int j = 0; j < kQ + (kR ? 1 : 0); ++j) {
-            const int h = wave + j * kWaves;
-            if (h < kHalves) {
-                const int tile = h >> 1, half = h & 1;
-                const uint8_t *src;
-                if (tile < kS * kTA) {
-                    const int t = tile / kTA, tt = tile % kTA;
-                    src = Ap + t * a_slice + tile_base(0, bi * kTA + tt, bk, nBI, nBK);
-                } else {
-                    const int tb = tile - kS * kTA;
-                    const int t = tb / kTB, tt = tb % kTB;
-                    src = Bp + t * b_slice + tile_base(0, bj * kTB + tt, bk, nBJ, nBK);
-                }
-                src += half * 1024 + lane * 16;
-                uint8_t *dst = slot + tile * kTileBytes + half * 1024;
-                __builtin_amdgcn_global_load_lds((global_void_ptr)(const void *)src,
-                                                 (lds_void_ptr)(void *)dst, 16, 0, 0);
-            }
-        }
-    };
-
-    const int ta = wm >> 1, rla = 32 * (wm & 1) + (lane & 31);
-    const int tb = wn >> 1, rlb = 32 * (wn & 1) + (lane & 31);
-    const int oa = ta * kTileBytes + tile_swizzle(rla, lane >> 5);
-    const int ob = kS * kTA * kTileBytes + tb * kTileBytes + tile_swizzle(rlb, lane >> 5);
-
-    uint4 fa[kS], fb[kS];
-    auto read_frags = [&](const uint8_t *slot) {
-        fb[0] = *reinterpret_cast<const uint4 *>(slot + ob);
-#pragma unroll
-        for (int t = 0; t < kS; ++t)
-            fa[t] = *reinterpret_cast<const uint4 *>(slot + t * kTA * kTileBytes + oa);
-#pragma unroll
-        for (int u = 1; u < kS; ++u)
-            fb[u] = *reinterpret_cast<const uint4 *>(slot + u * kTB * kTileBytes + ob);
-    };
-    // The 28 digit pairs (t, u) in an order that keeps the updates of each
-    // diagonal accumulator t + u at least three instructions apart, so that
-    // no MFMA waits for the one before it (in a phase the SIMD's other
-    // wavefront issues no MFMAs that could fill such a gap).
-    auto mfmas = [&]() {
-        constexpr int kOrder[28][2] = {
-            {0, 6}, {0, 5}, {0, 4}, {0, 3}, {1, 5}, {1, 4}, {1, 3}, {1, 2}, {2, 4}, {2, 3},
-            {2, 2}, {2, 1}, {3, 3}, {3, 2}, {3, 1}, {3, 0}, {4, 2}, {4, 1}, {4, 0}, {0, 2},
-            {5, 1}, {5, 0}, {1, 1}, {0, 1}, {6, 0}, {2, 0}, {1, 0}, {0, 0}};
-        static_assert(kS == 7, "the order lists the 28 pairs of 7 digits");
-#pragma unroll
-        for (int q = 0; q < 28; ++q) {
-            const int t = kOrder[q][0], u = kOrder[q][1];
-            acc[t + u] = mma(fa[t], fb[u], acc[t + u], Dg{});
-            if ((q & 3) == 3)
-                __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    // A read phase: this wavefront's previous DMA share (stage bk + 1) has
-    // landed, the fragments of stage bk are read, and the share of stage
-    // bk + 2 goes out.
-    auto read_phase = [&](const uint8_t *slot, uint8_t *dma_slot, int bk) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        read_frags(slot);
-        __builtin_amdgcn_sched_barrier(0);
-        if (bk + 2 < bk1)
-            fetch(bk + 2, dma_slot);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-
-    // stages bk0 and bk0 + 1 in flight; stage bk0 landed everywhere
-    if (bk0 < bk1)
-        fetch(bk0, slot0);
-    if (bk0 + 1 < bk1)
-        fetch(bk0 + 1, slot1);
-    if (bk0 + 1 < bk1) {
-        if (kR != 0 && wave < kR)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(kQ + 1));
-        else
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(kQ));
-    } else {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    }
-    barrier_no_fence();
-
-    if (wave < 4) {
-        auto stage0 = [&](const uint8_t *slot, uint8_t *dma_slot, int bk) {
-            read_phase(slot, dma_slot, bk);
-            barrier_no_fence();
-            mfmas();
-            if (drain_due(bk))
-                drain();
-            __builtin_amdgcn_sched_barrier(0);
-            barrier_no_fence();
-        };
-        for (int bk = bk0; bk < bk1; bk += 3) {
-            stage0(slot0, slot2, bk);
-            if (bk + 1 < bk1)
-                stage0(slot1, slot0, bk + 1);
-            if (bk + 2 < bk1)
-                stage0(slot2, slot1, bk + 2);
-        }
-    } else {
-        auto stage1 = [&](const uint8_t *slot, uint8_t *dma_slot, int bk) {
-            if (bk > bk0) {
-                mfmas();
-                if (drain_due(bk - 1))
-                    drain();
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            barrier_no_fence();
-            read_phase(slot, dma_slot, bk);
-            // reads landed before the barrier: the DMA of the next stage
-            // overwrites the slot of the stage before this one
-            __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(0));
-            barrier_no_fence();
-        };
-        for (int bk = bk0; bk < bk1; bk += 3) {
-            stage1(slot0, slot2, bk);
-            if (bk + 1 < bk1)
-                stage1(slot1, slot0, bk + 1);
-            if (bk + 2 < bk1)
-                stage1(slot2, slot1, bk + 2);
-        }
-        if (bk0 < bk1) {
-            mfmas();   // the last stage
-            drain();   // (always due after the last stage)
-        }
-    }
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    if constexpr (kDrain)
-        store_block_t96<WM, WN>(t96, M, N, bi, bj, wm, wn, lane, rowmax, colmax, Ch, Cl, ldc,
-                                accumulate);
-    else
-        store_block<Dg, WM, WN>(acc, acc, M, N, bi, bj, wm, wn, lane, rowmax, colmax, Ch, Cl,
-                                ldc, accumulate);
+    constexpr uint32_t w0 = word(0), w1 = word(1), w2 = word(2), w3 = word(3);
+    const uint32_t w = i < 8 ? (i < 4 ? w0 : w1) : (i < 12 ? w2 : w3);
+    return static_cast<int>((w >> (8 * (i & 3))) & 255u) + 1;
 }
 
-struct SliceGeom {
-    int nBI, nBJ, nBK;
-    size_t plane_a, plane_b;   // bytes of all A / B digit planes
-    size_t off_rowmax, off_colmax, off_a, off_b, total;
+// The products of the residue planes: workgroup = (modulus, 64 T x 64 T tile
+// of C), four wavefronts of T x T matrix-core blocks (32 x 32) each.
+//
+// T = 4 (256 x 256 tiles, one wavefront per SIMD with all 256 accumulation
+// registers): an operand read from LDS feeds four MFMAs, 64 LDS bytes per
+// cycle and compute unit of the 128 it can deliver.  A wavefront keeps its
+// matrix core busy by itself: operands are read one K-step ahead into a
+// second register set, four stages of 64 K-bytes ring through LDS, and LDS
+// reads and DMA are issued between MFMAs (an MFMA occupies the matrix core
+// for 32 cycles and the issue port for 4).  One barrier per stage.  Measured
+// at 4096^3 (int8): 0.906 ms, 2.43 POP/s, matrix cores busy 69 % of the
+// cycles at 1.68 GHz.
+// T = 2, T = 1 (128 x 128 and 64 x 64 tiles) when there are too few larger
+// tiles to fill 256 compute units: 60 us against 102 us for the digit pairs at
+// 1000 x 1531 x 2047, 4.7 against 31 us at 200 x 300 x 257.
+//
+// Workgroups run modulus by modulus, so that the planes in use are one
+// modulus's; within it each XCD takes a contiguous run of tiles ordered in
+// strips of four tile rows, so that 32 neighbouring tiles share L2.
+template <class Dg, int T>
+__global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
+    const uint8_t *__restrict__ Ap, const uint8_t *__restrict__ Bp, int64_t plane_a,
+    int64_t plane_b, int nKB, int kb0, int kb1, int nTI, int nTJ, uint8_t *__restrict__ Cr,
+    int exact)
+{
+    using Acc = typename Dg::Acc;
+    constexpr int kChunk = kStageFrags * kFragBytes;      // a block's bytes per stage
+    constexpr int kSlotBytes = 4 * T * kChunk;
+    constexpr int kDma = T * kStageFrags;                 // DMA instructions per wave and stage
+    constexpr int kRead = 2 * T;                          // operands per K-step and wave
+    constexpr int kSlots = 4;
+    __shared__ uint4 ring[kSlots * kSlotBytes / 16];
+    uint8_t *const lds = reinterpret_cast<uint8_t *>(ring);
+    const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
+        (__attribute__((address_space(3))) uint8_t *)lds));
+
+    const int tiles = nTI * nTJ;
+    const int mod = blockIdx.x / tiles;
+    int ti, tj;
+    {
+        int j = blockIdx.x % tiles;
+        if (tiles % 8 == 0)                       // XCD j % 8 takes a contiguous run
+            j = (j % 8) * (tiles / 8) + j / 8;
+        const int group = j / (4 * nTJ), rows = nTI - 4 * group < 4 ? nTI - 4 * group : 4;
+        const int in = j - group * 4 * nTJ;
+        ti = 4 * group + in % rows;
+        tj = in / rows;
+    }
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+
+    // this wavefront's DMA share: T of the 4 T chunks (2 T of A, 2 T of B)
+    const uint8_t *src;
+    {
+        const bool of_a = wave < 2;
+        const int64_t blk = static_cast<int64_t>(of_a ? ti : tj) * (2 * T) + (wave & 1) * T;
+        src = (of_a ? Ap + mod * plane_a : Bp + mod * plane_b) + (blk * nKB + kb0) * kFragBytes;
+    }
+    const int64_t blk_stride = static_cast<int64_t>(nKB) * kFragBytes;
+    const int nst = (kb1 - kb0) / kStageFrags;
+    // DMA q of stage st; past the end the last stage again, so that every
+    // stage sends the same number and the waits below need no cases
+    const uint32_t lane16 = lane * 16;
+    auto dma = [&](int st, int q) {
+        const int c = q / kStageFrags, h = q % kStageFrags;
+        lds_dma16(src + c * blk_stride + static_cast<int64_t>(st < nst ? st : nst - 1) * kChunk +
+                      h * kFragBytes,
+                  lane16,
+                  lds_base + (st % kSlots) * kSlotBytes + (wave * T + c) * kChunk + h * kFragBytes);
+    };
+
+    Acc acc[T][T];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                acc[i][j][r] = 0;
+
+    const int m = modulus_of(mod);
+    const float inv = 1.0f / static_cast<float>(m);
+    auto fold = [&]() {
+        if constexpr (Dg::kFoldStages > 0) {
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = 0; j < T; ++j) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float c = acc[i][j][r];
+                        const float n = __builtin_fmaf(c, inv, kRoundMagic) - kRoundMagic;
+                        acc[i][j][r] = __builtin_fmaf(n, -static_cast<float>(m), c);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // one block's registers at a time
+                }
+        }
+    };
+
+    uint4 f0[kRead], f1[kRead];
+    const int oa = wm * T * kChunk + lane * 16, ob = (2 + wn) * T * kChunk + lane * 16;
+    // operand q (T of A, then T of B) of K-step kk in the slot at byte `at`
+    auto read = [&](uint4 (&f)[kRead], int at, int kk, int q) {
+        f[q] = *reinterpret_cast<const uint4 *>(
+            lds + at + (q < T ? oa + q * kChunk : ob + (q - T) * kChunk) + kk * kFragBytes);
+    };
+    // MFMA q of a K-step
+    auto mfma = [&](const uint4 (&f)[kRead], int q) {
+        const int i = q / T, j = q % T;
+        acc[i][j] = mma(f[i], f[T + j], acc[i][j]);
+    };
+    constexpr int kSteps = T * T > kRead ? T * T : kRead;
+
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s)
+#pragma unroll
+        for (int q = 0; q < kDma; ++q)
+            dma(s, q);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * kDma));
+    barrier_no_fence();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < kRead; ++q)
+        read(f0, 0, 0, q);
+    // Stage st, whose first K-step has been read into f0: multiplies it while
+    // the second K-step is read; then, once stage st + 1 has landed everywhere
+    // and everyone has read this slot, reads that stage's first K-step and
+    // sends stage st + 4 into this slot under the second K-step's MFMAs.
+    auto stage = [&](int st) {
+        const int at = (st % kSlots) * kSlotBytes, next = ((st + 1) % kSlots) * kSlotBytes;
+#pragma unroll
+        for (int q = 0; q < kSteps; ++q) {
+            if (q < kRead)
+                read(f1, at, 1, q);
+            if (q < T * T)
+                mfma(f0, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kDma) & lgkmcnt_imm(0));
+        barrier_no_fence();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < kSteps; ++q) {
+            if (q < kRead)
+                read(f0, next, 0, q);
+            if (q < T * T)
+                mfma(f1, q);
+            if (q < kDma)
+                dma(st + 4, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    int st = 0;
+    do {
+        // int8 residues: all stages; BF16: up to the next fold
+        const int end = Dg::kFoldStages > 0 && st + Dg::kFoldStages < nst ? st + Dg::kFoldStages
+                                                                           : nst;
+#pragma unroll 1
+        do
+            stage(st);
+        while (++st < end);
+        fold();
+    } while (Dg::kFoldStages > 0 && st < nst);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no DMA outlives the workgroup
+
+    // Residue planes of C: per modulus and 32 x 32 block 1 KiB, word w of
+    // lane l (rows 8 w + 4 (l / 32) + 0..3 of column l % 32) at 256 w + 4 l.
+    const int64_t nCB = static_cast<int64_t>(nTJ) * (2 * T);
+    uint8_t *const out = Cr + static_cast<int64_t>(mod) * nTI * (2 * T) * nCB * kFragBytes;
+    auto store = [&](auto low_byte) {
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int j = 0; j < T; ++j) {
+                const int64_t rb = static_cast<int64_t>(ti) * (2 * T) + wm * T + i;
+                const int64_t cb = static_cast<int64_t>(tj) * (2 * T) + wn * T + j;
+                uint8_t *const dst = out + (rb * nCB + cb) * kFragBytes + lane * 4;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    uint32_t r[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        r[u] = low_byte(acc[i][j][4 * w + u]);
+                    *reinterpret_cast<uint32_t *>(dst + 256 * w) =
+                        pack_low_bytes(r[0], r[1], r[2], r[3]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+    };
+    // (the empty assembly keeps the compiler from computing the part common to
+    // the two reductions for all 256 sums ahead of the branch, which would
+    // hold them in as many registers again)
+    if constexpr (Dg::kFoldStages > 0)
+        store([&](float c) { return static_cast<uint32_t>(static_cast<int>(c)); });
+    else if (exact || m > 244)
+        store([&](int c) {
+            asm volatile("; two steps" : "+v"(c));
+            return reduce_low_byte(reduce_once(c, m, inv), m, inv);
+        });
+    else
+        store([&](int c) {
+            asm volatile("; one step" : "+v"(c));
+            return reduce_low_byte(c, m, inv);
+        });
+}
+
+// C from its residues: workgroup = 32 x 32 block of C, wavefront w its rows
+// 8 w + 4 (lane / 32) + 0..3 at column lane % 32.
+__global__ __launch_bounds__(256) void combine_residues(
+    int64_t M, int64_t N, int64_t nBJ, const uint8_t *__restrict__ Cr, int64_t nCB, int64_t plane,
+    const int *__restrict__ rowexp, const int *__restrict__ colexp, float *__restrict__ Ch,
+    float *__restrict__ Cl, int64_t ldc, int accumulate)
+{
+    constexpr ResidueTables tab = kResidue;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t bi = blockIdx.x / nBJ, bj = blockIdx.x % nBJ;
+    const uint8_t *src = Cr + (bi * nCB + bj) * kFragBytes + wave * 256 + lane * 4;
+    uint32_t v[kModuli];
+#pragma unroll
+    for (int i = 0; i < kModuli; ++i)
+        v[i] = *reinterpret_cast<const uint32_t *>(src + i * plane);
+    const int64_t i0 = bi * kBlk + 8 * wave + 4 * (lane >> 5), j = bj * kBlk + (lane & 31);
+    if (j >= N)
+        return;
+    const int fj = colexp[j] - 2 * kP;
+    uint32_t o[4][4];   // residue bytes of output u: o[g][u], moduli 4 g .. 4 g + 3
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const uint32_t in[4] = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+        transpose_bytes(in, o[g]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t i = i0 + u;
+        if (i >= M)
+            break;
+        auto column = [&](const uint32_t (&c)[4], int s) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                s = dot4(o[g][u], c[g], s);
+            return s;
+        };
+        // T / P is within 0.39 of an integer q = round(sum_i r_i R_i / P);
+        // the rounded fractions are off by at most 2^-6 in all
+        const int q = ((column(tab.frac1, 0) << 8) + column(tab.frac0, 0) + 32768) >> 16;
+        const uint32_t qd = static_cast<uint32_t>((q + 128) ^ 128) & 0xffffu;
+        uint32_t t[4];
+        int64_t carry = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            int c[4];
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+                c[d] = column(tab.recon[4 * w + d], dot4(qd, tab.minus_p[4 * w + d], 0));
+            const int low = c[0] + (c[1] << 8), high = c[2] + (c[3] << 8);
+            carry += low + (static_cast<int64_t>(high) << 16);
+            t[w] = static_cast<uint32_t>(carry);
+            carry >>= 32;
+        }
+        float h, l;
+        int128_to_ff(t, rowexp[i] + fj, h, l);
+        float *const ph = Ch + i * ldc + j, *const pl = Cl + i * ldc + j;
+        if (accumulate)
+            ffd::add22(*ph, *pl, h, l, h, l);
+        *ph = h;
+        *pl = l;
+    }
+}
+
+__global__ __launch_bounds__(256) void zero_matrix(int64_t M, int64_t N, float *__restrict__ Ch,
+                                                   float *__restrict__ Cl, int64_t ldc)
+{
+    const int64_t n = M * N;
+    for (int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; e < n;
+         e += static_cast<int64_t>(gridDim.x) * 256) {
+        Ch[e / N * ldc + e % N] = 0.0f;
+        Cl[e / N * ldc + e % N] = 0.0f;
+    }
+}
+
+struct ResidueGeom {
+    int tile;                  // 32 x 32 blocks per wavefront and dimension: 1, 2 or 4
+    int64_t nTI, nTJ;          // tiles of 64 * tile
+    int64_t nRB, nCB, nKB;     // 32-row blocks, 32-column blocks, K-steps (padded)
+    int64_t nseg, nband;       // partial maxima per row / column
+    int64_t plane_a, plane_b, plane_c;
+    size_t off_colpart, off_rowexp, off_colexp, off_a, off_b, off_c, total;
 };
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-inline SliceGeom slice_geom(int64_t M, int64_t N, int64_t K, int stage_k)
+inline ResidueGeom residue_geom(int64_t M, int64_t N, int64_t K, int frag_k)
 {
-    SliceGeom g;
-    // tile counts padded to even numbers: a workgroup covers up to two
-    // 64-row (or 64-column) tiles; the padding tiles hold zero digits
-    g.nBI = 2 * static_cast<int>((M + 2 * kTile - 1) / (2 * kTile));
-    g.nBJ = 2 * static_cast<int>((N + 2 * kTile - 1) / (2 * kTile));
-    g.nBK = static_cast<int>((K + stage_k - 1) / stage_k);
-    g.plane_a = static_cast<size_t>(kS) * g.nBI * g.nBK * kTileBytes;
-    g.plane_b = static_cast<size_t>(kS) * g.nBJ * g.nBK * kTileBytes;
-    g.off_rowmax = 0;
-    g.off_colmax = align256(sizeof(uint32_t) * M);
-    g.off_a = g.off_colmax + align256(sizeof(uint32_t) * N);
-    g.off_b = g.off_a + align256(g.plane_a);
-    g.total = g.off_b + align256(g.plane_b);
+    ResidueGeom g;
+    // the largest tile that still gives every compute unit four (T = 4) or two
+    // (T = 2) workgroups: fewer leave part of the chip idle in the last round
+    const int64_t tiles256 = ffh::cdiv(M, 256) * ffh::cdiv(N, 256) * kModuli;
+    const int64_t tiles128 = ffh::cdiv(M, 128) * ffh::cdiv(N, 128) * kModuli;
+    g.tile = tiles256 >= 1024 ? 4 : tiles128 >= 512 ? 2 : 1;
+    g.nTI = ffh::cdiv(M, 64 * g.tile);
+    g.nTJ = ffh::cdiv(N, 64 * g.tile);
+    g.nRB = g.nTI * 2 * g.tile;
+    g.nCB = g.nTJ * 2 * g.tile;
+    g.nKB = ffh::cdiv(K, static_cast<int64_t>(frag_k) * kStageFrags) * kStageFrags;
+    g.nseg = ffh::cdiv(K, kRowSegment);
+    g.nband = ffh::cdiv(K, kColBand);
+    g.plane_a = g.nRB * g.nKB * kFragBytes;
+    g.plane_b = g.nCB * g.nKB * kFragBytes;
+    g.plane_c = g.nRB * g.nCB * kFragBytes;
+    size_t off = align256(sizeof(uint32_t) * g.nseg * M);
+    auto take = [&](size_t bytes) {
+        const size_t at = off;
+        off += align256(bytes);
+        return at;
+    };
+    g.off_colpart = take(sizeof(uint32_t) * g.nband * N);
+    g.off_rowexp = take(sizeof(int) * M);
+    g.off_colexp = take(sizeof(int) * N);
+    g.off_a = take(static_cast<size_t>(kModuli) * g.plane_a);
+    g.off_b = take(static_cast<size_t>(kModuli) * g.plane_b);
+    g.off_c = take(static_cast<size_t>(kModuli) * g.plane_c);
+    g.total = off;
     return g;
 }
 
@@ -822,58 +757,63 @@ ff_status sliced_gemm(int64_t M, int64_t N, int64_t K, const float *Ah, const fl
                       int64_t lda, const float *Bh, const float *Bl, int64_t ldb, float *Ch,
                       float *Cl, int64_t ldc, void *ws, size_t ws_bytes, hipStream_t st)
 {
-    const SliceGeom g = slice_geom(M, N, K, Dg::kStageK);
+    const ResidueGeom g = residue_geom(M, N, K, Dg::kFragK);
     if (!ws)
         return FF_ERR_NULL;
     if (ws_bytes < g.total)
         return FF_ERR_WORKSPACE;
     if (!ffh::aligned(ws, 256))
         return FF_ERR_ALIGN;
-    if (g.nBI > 32767 || g.nBJ > 65535 || ffh::cdiv(M, 4) > 65535 || ffh::cdiv(K, 64) > 65535)
+    if (M > int64_t(65535) * 4 || N > int64_t(65535) * 64 || K > int64_t(65535) * 64)
         return FF_ERR_SIZE;
+    const int64_t row_groups = ffh::cdiv(M, 4), col_groups = ffh::cdiv(N, 64);
+    const int64_t max_grid = row_groups * g.nseg + col_groups * g.nband;
+    const int64_t res_grid = (g.nRB + g.nCB) * ffh::cdiv(g.nKB, kResidueFrags);
+    const int64_t gemm_grid = kModuli * g.nTI * g.nTJ;
+    const int64_t nBJ = ffh::cdiv(N, kBlk);
+    const int64_t out_grid = ffh::cdiv(M, kBlk) * nBJ;
+    if (max_grid > INT32_MAX || res_grid > INT32_MAX || gemm_grid > INT32_MAX ||
+        out_grid > INT32_MAX)
+        return FF_ERR_SIZE;
+    if (K == 0) {
+        const int64_t blocks = ffh::cdiv(M * N, 256);
+        hipLaunchKernelGGL(zero_matrix, dim3(static_cast<unsigned>(blocks < 4096 ? blocks : 4096)),
+                           dim3(256), 0, st, M, N, Ch, Cl, ldc);
+        return ffh::launch_status();
+    }
     char *base = static_cast<char *>(ws);
-    uint32_t *rowmax = reinterpret_cast<uint32_t *>(base + g.off_rowmax);
-    uint32_t *colmax = reinterpret_cast<uint32_t *>(base + g.off_colmax);
+    uint32_t *rowpart = reinterpret_cast<uint32_t *>(base);
+    uint32_t *colpart = reinterpret_cast<uint32_t *>(base + g.off_colpart);
+    int *rowexp = reinterpret_cast<int *>(base + g.off_rowexp);
+    int *colexp = reinterpret_cast<int *>(base + g.off_colexp);
     uint8_t *Ap = reinterpret_cast<uint8_t *>(base + g.off_a);
     uint8_t *Bp = reinterpret_cast<uint8_t *>(base + g.off_b);
-
-    const int64_t nfill = static_cast<int64_t>(g.off_a / sizeof(uint32_t));
-    const int64_t fill_blocks = ffh::cdiv(nfill, 256);
-    hipLaunchKernelGGL(fill_u32, dim3(static_cast<unsigned>(fill_blocks < 4096 ? fill_blocks : 4096)),
-                       dim3(256), 0, st, rowmax, nfill);
-    if (K > 0) {
-        const bool rows_vec = lda % 4 == 0 && ffh::aligned(Ah, 16) && ffh::aligned(Al, 16);
-        const dim3 rgrid(static_cast<unsigned>(ffh::cdiv(K, 4096)),
-                         static_cast<unsigned>(ffh::cdiv(M, 4)));
-        if (rows_vec)
-            hipLaunchKernelGGL(absmax_rows<true>, rgrid, dim3(256), 0, st, M, K, Ah, lda, rowmax);
-        else
-            hipLaunchKernelGGL(absmax_rows<false>, rgrid, dim3(256), 0, st, M, K, Ah, lda, rowmax);
-        hipLaunchKernelGGL(absmax_cols,
-                           dim3(static_cast<unsigned>(ffh::cdiv(N, 256)),
-                                static_cast<unsigned>(ffh::cdiv(K, 64))),
-                           dim3(256), 0, st, K, N, Bh, ldb, colmax);
-        constexpr int kChunks = Dg::kStageK / (16 / Dg::kEsize);
-        hipLaunchKernelGGL((slice_rows<Dg>),
-                           dim3(static_cast<unsigned>(ffh::cdiv(static_cast<int64_t>(g.nBK) * kChunks, 8)),
-                                static_cast<unsigned>(g.nBI * (kTile / 32))),
-                           dim3(256), 0, st, M, K, Ah, Al, lda, rowmax, g.nBI, g.nBK, Ap,
-                           rows_vec ? 1 : 0);
-        hipLaunchKernelGGL((slice_cols<Dg>), dim3(g.nBK, g.nBJ), dim3(128), 0, st, K, N, Bh, Bl,
-                           ldb, colmax, g.nBJ, g.nBK, Bp);
+    uint8_t *Cr = reinterpret_cast<uint8_t *>(base + g.off_c);
+    const bool vec = lda % 4 == 0 && ffh::aligned(Ah, 16) && ffh::aligned(Al, 16);
+    auto absmax = vec ? absmax_partials<true> : absmax_partials<false>;
+    hipLaunchKernelGGL(absmax, dim3(static_cast<unsigned>(max_grid)), dim3(256), 0, st, M, N, K,
+                       Ah, lda, Bh, ldb, row_groups, col_groups, rowpart, colpart);
+    auto residues = vec ? residue_planes<Dg, true> : residue_planes<Dg, false>;
+    hipLaunchKernelGGL(residues, dim3(static_cast<unsigned>(res_grid)), dim3(256), 0, st, M, N, K,
+                       Ah, Al, lda, Bh, Bl, ldb, static_cast<int>(g.nRB),
+                       static_cast<int>(g.nCB), static_cast<int>(g.nKB), rowpart, colpart,
+                       static_cast<int>(g.nseg), static_cast<int>(g.nband), rowexp, colexp, Ap,
+                       Bp);
+    auto product = g.tile == 4   ? gemm_residues<Dg, 4>
+                   : g.tile == 2 ? gemm_residues<Dg, 2>
+                                 : gemm_residues<Dg, 1>;
+    const int64_t chunk = kMaxKChunk / Dg::kFragK;
+    for (int64_t kb0 = 0; kb0 < g.nKB; kb0 += chunk) {
+        const int64_t kb1 = kb0 + chunk < g.nKB ? kb0 + chunk : g.nKB;
+        hipLaunchKernelGGL(product, dim3(static_cast<unsigned>(gemm_grid)), dim3(256), 0, st, Ap,
+                           Bp, g.plane_a, g.plane_b, static_cast<int>(g.nKB),
+                           static_cast<int>(kb0), static_cast<int>(kb1),
+                           static_cast<int>(g.nTI), static_cast<int>(g.nTJ), Cr,
+                           (kb1 - kb0) * Dg::kFragK > 4096 ? 1 : 0);
+        hipLaunchKernelGGL(combine_residues, dim3(static_cast<unsigned>(out_grid)), dim3(256), 0,
+                           st, M, N, nBJ, Cr, g.nCB, g.plane_c, rowexp, colexp, Ch, Cl, ldc,
+                           kb0 > 0 ? 1 : 0);
     }
-    using Sh = SlicedShape<Dg>;
-    const int stages_per_chunk = static_cast<int>(kMaxKChunk / Dg::kStageK);
-    const dim3 grid(static_cast<unsigned>(g.nBJ / (Sh::WN / 2)),
-                    static_cast<unsigned>(g.nBI / (Sh::WM / 2)));
-    int bk0 = 0;
-    do {
-        const int bk1 = (bk0 + stages_per_chunk < g.nBK) ? bk0 + stages_per_chunk : g.nBK;
-        hipLaunchKernelGGL((gemm_sliced_pp<Dg, Sh::WM, Sh::WN>), grid, dim3(64 * Sh::WM * Sh::WN),
-                           0, st, M, N, g.nBI, g.nBJ, g.nBK, bk0, bk1, Ap, Bp, rowmax, colmax, Ch,
-                           Cl, ldc, bk0 > 0 ? 1 : 0);
-        bk0 = bk1;
-    } while (bk0 < g.nBK);
     return ffh::launch_status();
 }
 
@@ -889,8 +829,8 @@ size_t ff_gemm_workspace_size(int64_t M, int64_t N, int64_t K, int32_t algo)
         return 0;
     switch (algo) {
     case FF_GEMM_FMA_LOOP: return 0;
-    case FF_GEMM_SLICED_BF16: return slice_geom(M, N, K, DigitsBF16::kStageK).total;
-    case FF_GEMM_SLICED_I8: return slice_geom(M, N, K, DigitsI8::kStageK).total;
+    case FF_GEMM_SLICED_BF16: return residue_geom(M, N, K, ResiduesBF16::kFragK).total;
+    case FF_GEMM_SLICED_I8: return residue_geom(M, N, K, ResiduesI8::kFragK).total;
     default: return 0;
     }
 }
@@ -924,10 +864,10 @@ ff_status ff_gemm(int64_t M, int64_t N, int64_t K, const float *A_hi, const floa
                            ldc);
         return ffh::launch_status();
     case FF_GEMM_SLICED_BF16:
-        return sliced_gemm<DigitsBF16>(M, N, K, A_hi, A_lo, lda, B_hi, B_lo, ldb, C_hi, C_lo, ldc,
+        return sliced_gemm<ResiduesBF16>(M, N, K, A_hi, A_lo, lda, B_hi, B_lo, ldb, C_hi, C_lo, ldc,
                                        ws, ws_bytes, st);
     default:
-        return sliced_gemm<DigitsI8>(M, N, K, A_hi, A_lo, lda, B_hi, B_lo, ldb, C_hi, C_lo, ldc,
+        return sliced_gemm<ResiduesI8>(M, N, K, A_hi, A_lo, lda, B_hi, B_lo, ldb, C_hi, C_lo, ldc,
                                      ws, ws_bytes, st);
     }
 }

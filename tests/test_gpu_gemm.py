@@ -295,3 +295,39 @@ def test_strided_operands_and_output(algo):
         check_entries(Ac, Bc, C.contiguous(), range(M), range(N), f"{algo} strided")
         Cref = ff.ff_gemm(Ac, Bc, algo=_algo(algo))
         assert torch.equal(Cref.view(torch.int32), C.contiguous().view(torch.int32))
+
+
+def _constant_operands(M, N, K, seed):
+    """Every row of A and column of B holds one value throughout, of 48
+    random bits: a modulus then sees K equal residue products, up to the
+    largest sum it can meet, and C_ij = K a_i b_j exactly."""
+    a = fi.random_ff(M, seed, 0, 0, max_gap=0)
+    b = fi.random_ff(N, seed + 1, 0, 0, max_gap=0)
+    A = a[:, :, None].expand(2, M, K).contiguous()
+    B = b[:, None, :].expand(2, K, N).contiguous()
+    return a, b, A, B
+
+
+@pytest.mark.parametrize("algo,M,N,K", [
+    ("i8", 130, 190, 31), ("i8", 64, 64, 65), ("i8", 192, 128, 4096),     # small tiles
+    ("i8", 192, 128, 4097), ("i8", 700, 650, 449),                        # middle tiles
+    ("i8", 2049, 1800, 4096), ("i8", 1900, 2050, 4160),                   # large tiles
+    ("bf16", 130, 190, 31), ("bf16", 64, 64, 513), ("bf16", 192, 128, 1537),
+    ("bf16", 700, 650, 1024), ("bf16", 2049, 1800, 1000), ("bf16", 1900, 2050, 1600)])
+def test_largest_residue_sums_and_tile_edges(algo, M, N, K):
+    # C_ij = K a_i b_j: the fixed point (54 bits from the row's power of two)
+    # holds a_i and b_j exactly, the integer product is exact, so the only
+    # error is the final rounding, at most 2^-48 |C_ij|
+    _announce(f"[gpu] gemm constant rows and columns {M}x{N}x{K} ({algo})")
+    a, b, A, B = _constant_operands(M, N, K, 8100 + K)
+    C = _ff().ff_gemm(A.cuda(), B.cuda(), algo=_algo(algo)).cpu().numpy()
+    a, b = a.numpy(), b.numpy()
+    rng = np.random.default_rng(K)
+    rows = np.unique(np.concatenate([[0, M // 2, M - 1], rng.integers(0, M, 60)]))
+    cols = np.unique(np.concatenate([[0, N // 2, N - 1], rng.integers(0, N, 60)]))
+    for i in rows:
+        ai = K * (frac(a[0, i]) + frac(a[1, i]))
+        for j in cols:
+            exact = ai * (frac(b[0, j]) + frac(b[1, j]))
+            err = abs(frac(C[0, i, j]) + frac(C[1, i, j]) - exact)
+            assert err <= abs(exact) / (1 << 48), (i, j)
