@@ -134,6 +134,58 @@ __device__ __forceinline__ int reduce_once(int s, int m, float inv)
     return static_cast<int>(reduce_low_byte(s, m, inv) + (static_cast<uint32_t>(m) << 22));
 }
 
+// A sum s of digit products, |s| < 2^17, read from the integer that an
+// accumulation starting at the bits of the binary32 number `base` leaves: as a
+// float it is base + s exactly.  base is a multiple of 256 m near 1.5 2^23, so
+// that base / m is an integer and the low byte is that of s.
+struct BiasedModulus {
+    int bits;         // of base
+    float base;
+    float inv;        // 1 / m
+    float offset;     // 1.5 2^23 - base / m, an integer
+    int neg_m;
+};
+
+struct BiasedTable {
+    BiasedModulus of[kModuli];
+};
+
+constexpr BiasedTable make_biased_table()
+{
+    BiasedTable b{};
+    for (int i = 0; i < kModuli; ++i) {
+        const int m = kModulus[i], units = 49152 / m;   // base = 256 m units
+        const int base = 256 * m * units;
+        b.of[i].bits = 0x4b000000 + (base - (1 << 23));  // of a float in [2^23, 2^24)
+        b.of[i].base = static_cast<float>(base);
+        b.of[i].inv = 1.0f / static_cast<float>(m);
+        b.of[i].offset = kRoundMagic - static_cast<float>(256 * units);
+        b.of[i].neg_m = -m;
+    }
+    return b;
+}
+
+constexpr BiasedTable kBiased = make_biased_table();
+
+// s minus a multiple of m, in the low byte: the residue nearest zero, or the
+// next one where the rounding of 1 / m (up to 2^-24 of base / m, 0.75 / m)
+// moves a quotient over one half.  It stays within [-128, 127]: only 255 has no
+// room above its largest balanced residue, and 1 / 255 rounds up, which moves
+// quotients up and residues down.
+__device__ __forceinline__ uint32_t residue_from_biased(int v, const BiasedModulus &b)
+{
+    const float t = __builtin_fmaf(__int_as_float(v), b.inv, b.offset);
+    return static_cast<uint32_t>(v) + static_cast<uint32_t>(times24(t, b.neg_m));
+}
+
+// The same residue as a float.
+__device__ __forceinline__ float residue_float_from_biased(int v, const BiasedModulus &b)
+{
+    const float s = __int_as_float(v) - b.base;
+    const float n = __builtin_fmaf(__int_as_float(v), b.inv, b.offset) - kRoundMagic;
+    return __builtin_fmaf(n, static_cast<float>(b.neg_m), s);
+}
+
 // Bytes 0 of four words, packed.
 __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
 {
@@ -184,69 +236,60 @@ __device__ __forceinline__ void entry_digits(float hi, float lo, int e, uint32_t
     d_hi = static_cast<uint32_t>(b >> 32) ^ 0x00808080u;
 }
 
-// (hi, lo) = (RN(T), RN(T - RN(T))) 2^scale for the 128-bit two's complement
-// integer T = sum_k t[k] 2^(32 k).
-__device__ __forceinline__ int normalise(uint32_t (&n)[4])
+// Leading bits equal to the sign bit, counting it; -1 for 0 and -1
+// (v_ffbh_i32, which no builtin names).
+extern "C" __device__ int sign_bits(int x) __asm("llvm.amdgcn.sffbh.i32");
+
+// Shifts the two's complement number n[3] .. n[0] left by 24 as long as its
+// leading word holds 28 sign bits or more (a number of few bits: rare, so the
+// wavefront tests for it together).  Returns the shift.
+__device__ __forceinline__ int shift_out_signs(uint32_t (&n)[4])
 {
-    // shifts the leading one bit to bit 31 of n[3]; returns the shift
     int sh = 0;
-    if (n[3] == 0) {
-        n[3] = n[2]; n[2] = n[1]; n[1] = n[0]; n[0] = 0;
-        sh = 32;
+    for (int pass = 0; pass < 5; ++pass) {
+        const bool few =
+            static_cast<unsigned>(sign_bits(static_cast<int>(n[3]))) >= 28u;
+        if (!__any(few))
+            break;
+        if (few) {
+            n[3] = __builtin_amdgcn_alignbit(n[3], n[2], 8);
+            n[2] = __builtin_amdgcn_alignbit(n[2], n[1], 8);
+            n[1] = __builtin_amdgcn_alignbit(n[1], n[0], 8);
+            n[0] <<= 24;
+            sh += 24;
+        }
     }
-    if (n[3] == 0) {
-        n[3] = n[2]; n[2] = n[1]; n[1] = 0;
-        sh = 64;
-    }
-    if (n[3] == 0) {
-        n[3] = n[2]; n[2] = 0;
-        sh = 96;
-    }
-    const int z = n[3] ? __builtin_clz(n[3]) : 0;
-    // funnel shifts right by 32 - z, of which the low five bits count: z = 0
-    // is a shift by 0 of the lower word pair, so it takes its own select
-    const uint32_t a3 = z ? __builtin_amdgcn_alignbit(n[3], n[2], 32 - z) : n[3];
-    const uint32_t a2 = z ? __builtin_amdgcn_alignbit(n[2], n[1], 32 - z) : n[2];
-    const uint32_t a1 = z ? __builtin_amdgcn_alignbit(n[1], n[0], 32 - z) : n[1];
-    n[0] <<= z;
-    n[3] = a3;
-    n[2] = a2;
-    n[1] = a1;
-    return sh + z;
+    return sh;
 }
 
-__device__ __forceinline__ void negate(uint32_t (&n)[4])
-{
-    const uint64_t lo = ~(static_cast<uint64_t>(n[1]) << 32 | n[0]) + 1;
-    uint64_t hi = ~(static_cast<uint64_t>(n[3]) << 32 | n[2]);
-    hi += lo == 0 ? 1 : 0;
-    n[0] = static_cast<uint32_t>(lo);
-    n[1] = static_cast<uint32_t>(lo >> 32);
-    n[2] = static_cast<uint32_t>(hi);
-    n[3] = static_cast<uint32_t>(hi >> 32);
-}
-
+// (hi, lo) = (RN(T), RN(T - RN(T))) 2^scale for the 128-bit two's complement
+// integer T = sum_k t[k] 2^(32 k), |T| < 2^124.  Signed words throughout: a
+// leading word with a sticky bit for all that follows it converts to the
+// nearest binary32 of the whole in two's complement too (the truncated part
+// is positive and the rounding points are even).
 __device__ __forceinline__ void int128_to_ff(uint32_t (&t)[4], int scale, float &hi, float &lo)
 {
-    const bool neg = static_cast<int32_t>(t[3]) < 0;
-    if (neg)
-        negate(t);
-    const int s1 = normalise(t);
-    // the top 32 bits with a sticky bit for the rest convert to the nearest
-    // binary32 of the whole (32 >= 24 + 2)
-    const uint32_t top = t[3];
-    const float f = static_cast<float>(top | ((t[2] | t[1] | t[0]) ? 1u : 0u));
-    // rounded up: the remainder is the low 104 bits minus 2^104
-    const bool up = static_cast<uint32_t>(f * 0.00390625f) != top >> 8;
-    t[3] = up ? (top & 255u) - 256u : top & 255u;
-    if (up)
-        negate(t);
-    const int s2 = normalise(t);
-    const float g = static_cast<float>(t[3] | ((t[2] | t[1] | t[0]) ? 1u : 0u));
-    const float h = __builtin_ldexpf(f, scale + 96 - s1);
-    const float l = __builtin_ldexpf(g, scale + 96 - s1 - s2);
-    hi = neg ? -h : h;
-    lo = (neg != up ? -l : l) + 0.0f;   // an exact zero comes back +0
+    scale += 96 - shift_out_signs(t);
+    // two sign bits left, so |top| <= 2^30 and its rounding converts back;
+    // T has at least four, so the funnel shifts are by 2 to 30
+    const int z = sign_bits(static_cast<int>(t[3])) - 2;
+    const int top = static_cast<int>(__builtin_amdgcn_alignbit(t[3], t[2], 32 - z));
+    const uint32_t n2 = __builtin_amdgcn_alignbit(t[2], t[1], 32 - z);
+    const uint32_t n1 = __builtin_amdgcn_alignbit(t[1], t[0], 32 - z);
+    const uint32_t n0 = t[0] << (z & 31);
+    const float f = static_cast<float>(top | static_cast<int>(min(n2 | n1 | n0, 1u)));
+    const uint32_t d = static_cast<uint32_t>(top - static_cast<int>(f));   // |d| <= 32
+    // T - hi = d 2^96 + ..., its leading word 24 bits up: at most 2^29
+    uint32_t r[4] = {n0 << 24, __builtin_amdgcn_alignbit(n1, n0, 8),
+                     __builtin_amdgcn_alignbit(n2, n1, 8), __builtin_amdgcn_alignbit(d, n2, 8)};
+    const int sh = shift_out_signs(r);
+    const int y = sign_bits(static_cast<int>(r[3])) - 1;      // 1 to 26
+    const int low = static_cast<int>(__builtin_amdgcn_alignbit(r[3], r[2], 32 - y));
+    const uint32_t rest = r[2] << (y & 31) | r[1] | r[0];
+    const float g = static_cast<float>(low | static_cast<int>(min(rest, 1u)));
+    scale -= z;
+    hi = __builtin_ldexpf(f, scale);
+    lo = __builtin_ldexpf(g, scale - 24 - sh - y);
 }
 
 } // namespace ffk
