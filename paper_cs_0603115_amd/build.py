@@ -50,6 +50,14 @@ HIPCC_FLAGS = [
     "-I", CSRC,
 ] + NUMERIC_FLAGS
 
+# Further flags of single sources.  ff_gemm.hip: a loop-carried vector of 16
+# accumulators stays one value; broken into elements (the default) the 256
+# accumulators of the large BF16 tile no longer stay in their registers and
+# spill in the loop.
+SOURCE_FLAGS = {
+    "ff_gemm.hip": ["-mllvm", "-amdgpu-codegenprepare-break-large-phis=false"],
+}
+
 
 def hipcc() -> str:
     path = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
@@ -64,7 +72,7 @@ def sources() -> list[str]:
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD_DIR, os.path.basename(src) + ".o")
-    cmd = [hipcc(), *HIPCC_FLAGS, "-c", src, "-o", obj]
+    cmd = [hipcc(), *HIPCC_FLAGS, *SOURCE_FLAGS.get(os.path.basename(src), []), "-c", src, "-o", obj]
     proc = subprocess.run(cmd, capture_output=True, text=True)
     if proc.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{proc.stdout}\n{proc.stderr}")
@@ -91,7 +99,8 @@ def build(jobs: int | None = None, verbose: bool = False) -> str:
 
 def device_asm(src: str, out: str) -> str:
     """gfx950 assembly of one source (for the instruction audit)."""
-    cmd = [hipcc(), *HIPCC_FLAGS, "--cuda-device-only", "-S", src, "-o", out]
+    cmd = [hipcc(), *HIPCC_FLAGS, *SOURCE_FLAGS.get(os.path.basename(src), []),
+           "--cuda-device-only", "-S", src, "-o", out]
     proc = subprocess.run(cmd, capture_output=True, text=True)
     if proc.returncode != 0:
         raise RuntimeError(f"hipcc -S failed for {src}:\n{proc.stderr}")

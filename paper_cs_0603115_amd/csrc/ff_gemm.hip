@@ -38,6 +38,8 @@
 //
 // Four launches per chunk of K: partial maxima, residue planes, products,
 // reconstruction (the first two once per call).
+#include <type_traits>
+
 #include "ff_device.h"
 #include "ff_gemm_residue.h"
 #include "ff_host.h"
@@ -145,7 +147,7 @@ struct ResiduesBF16 {
     using Acc = f32x16;
     static constexpr int kEsize = 2;
     static constexpr int kFragK = 16;
-    static constexpr int kFoldStages = 16; // FP32 sums folded every 512 k: |S| <= 2^23 + 128
+    static constexpr int kFoldStages = 20; // FP32 sums reduced every 640 k: |S| < 2^24
 };
 
 // Smallest e with |x| < 2^e for every x with |x| <= the value of bits ub.
@@ -518,8 +520,12 @@ __device__ __forceinline__ int modulus_of(int i)
 // second register set, four stages of 64 K-bytes ring through LDS, and LDS
 // reads and DMA are issued between MFMAs (an MFMA occupies the matrix core
 // for 32 cycles and the issue port for 4).  One barrier per stage.  Measured
-// at 4096^3 (int8): 0.906 ms, 2.43 POP/s, matrix cores busy 69 % of the
-// cycles at 1.68 GHz.
+// at 4096^3 (int8): 0.88 ms, 2.50 POP/s, matrix cores busy 69 % of the
+// cycles at 1.68 GHz.  BF16: the FP32 sums have to be reduced every 1023 k at
+// the latest; one block of sixteen sums per stage, between its MFMAs of the two
+// K-steps and one sum per MFMA of the other blocks, is hidden by the matrix
+// core: 1.61 ms at 4096^3 (1.37 PFLOP/s), against 2.07 ms reduced between
+// stages; 224 against 285 us at 2048^3.
 // T = 2, T = 1 (128 x 128 and 64 x 64 tiles) when there are too few larger
 // tiles to fill 256 compute units: 60 us against 102 us for the digit pairs at
 // 1000 x 1531 x 2047, 4.7 against 31 us at 200 x 300 x 257.
@@ -591,20 +597,12 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
 
     const int m = modulus_of(mod);
     const float inv = 1.0f / static_cast<float>(m);
-    auto fold = [&]() {
+    // BF16 residues: one FP32 sum reduced mod m
+    auto fold = [&](int block, int r) {
         if constexpr (Dg::kFoldStages > 0) {
-#pragma unroll
-            for (int i = 0; i < T; ++i)
-#pragma unroll
-                for (int j = 0; j < T; ++j) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float c = acc[i][j][r];
-                        const float n = __builtin_fmaf(c, inv, kRoundMagic) - kRoundMagic;
-                        acc[i][j][r] = __builtin_fmaf(n, -static_cast<float>(m), c);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);   // one block's registers at a time
-                }
+            const float c = acc[block / T][block % T][r];
+            const float n = __builtin_fmaf(c, inv, kRoundMagic) - kRoundMagic;
+            acc[block / T][block % T][r] = __builtin_fmaf(n, -static_cast<float>(m), c);
         }
     };
 
@@ -630,14 +628,16 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * kDma));
     barrier_no_fence();
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < kRead; ++q)
-        read(f0, 0, 0, q);
     // Stage st, whose first K-step has been read into f0: multiplies it while
     // the second K-step is read; then, once stage st + 1 has landed everywhere
     // and everyone has read this slot, reads that stage's first K-step and
     // sends stage st + 4 into this slot under the second K-step's MFMAs.
-    auto stage = [&](int st) {
+    // BF16: the sums of block `FOLD` are reduced between its MFMA of the first
+    // K-step and that of the second, one sum per MFMA of the other blocks.
+    auto stage = [&](int st, auto which, auto ahead) {
+        constexpr int FOLD = decltype(which)::value;
+        constexpr bool AHEAD = decltype(ahead)::value;
+        constexpr bool kFold = FOLD >= 0 && FOLD < T * T;
         const int at = (st % kSlots) * kSlotBytes, next = ((st + 1) % kSlots) * kSlotBytes;
 #pragma unroll
         for (int q = 0; q < kSteps; ++q) {
@@ -645,15 +645,28 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
                 read(f1, at, 1, q);
             if (q < T * T)
                 mfma(f0, q);
+            if (kFold && T == 4 && q > FOLD)
+                fold(FOLD, q - FOLD - 1);
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (kFold) {
+            if constexpr (T == 4) {
+                fold(FOLD, 15);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    fold(FOLD, r);
+            }
         }
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kDma) & lgkmcnt_imm(0));
         barrier_no_fence();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < kSteps; ++q) {
-            if (q < kRead)
+            if (q < kRead && AHEAD)
                 read(f0, next, 0, q);
+            if (kFold && T == 4 && q < FOLD)
+                fold(FOLD, 15 - FOLD + q);
             if (q < T * T)
                 mfma(f1, q);
             if (q < kDma)
@@ -662,16 +675,36 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
         }
     };
     int st = 0;
-    do {
-        // int8 residues: all stages; BF16: up to the next fold
-        const int end = Dg::kFoldStages > 0 && st + Dg::kFoldStages < nst ? st + Dg::kFoldStages
-                                                                           : nst;
+    if constexpr (Dg::kFoldStages == 0) {
+#pragma unroll
+        for (int q = 0; q < kRead; ++q)
+            read(f0, 0, 0, q);
 #pragma unroll 1
         do
-            stage(st);
-        while (++st < end);
-        fold();
-    } while (Dg::kFoldStages > 0 && st < nst);
+            stage(st, std::integral_constant<int, -1>{}, std::true_type{});
+        while (++st < nst);
+    } else {
+        // rounds of twenty stages; the sixteen blocks are folded in the stages
+        // away from the loop's edge, and no operands are read ahead across it:
+        // what is live there in ordinary registers was spilled
+        static_assert(Dg::kFoldStages == 20, "stages of a round");
+#define FF_STAGE(N)                                                                     \
+    stage(st, std::integral_constant<int, (N >= 2 && N < 18) ? N - 2 : -1>{},           \
+          std::integral_constant<bool, N != 19>{});                                     \
+    if (++st == nst)                                                                    \
+        break;
+#pragma unroll 1
+        for (;;) {
+#pragma unroll
+            for (int q = 0; q < kRead; ++q)
+                read(f0, st % kSlots * kSlotBytes, 0, q);
+            FF_STAGE(0) FF_STAGE(1) FF_STAGE(2) FF_STAGE(3) FF_STAGE(4)
+            FF_STAGE(5) FF_STAGE(6) FF_STAGE(7) FF_STAGE(8) FF_STAGE(9)
+            FF_STAGE(10) FF_STAGE(11) FF_STAGE(12) FF_STAGE(13) FF_STAGE(14)
+            FF_STAGE(15) FF_STAGE(16) FF_STAGE(17) FF_STAGE(18) FF_STAGE(19)
+        }
+#undef FF_STAGE
+    }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no DMA outlives the workgroup
 
     // Residue planes of C: per modulus and 32 x 32 block 1 KiB, word w of
@@ -702,7 +735,11 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
     // the two reductions for all 256 sums ahead of the branch, which would
     // hold them in as many registers again)
     if constexpr (Dg::kFoldStages > 0)
-        store([&](float c) { return static_cast<uint32_t>(static_cast<int>(c)); });
+        store([&](float c) {
+            const float t = __builtin_fmaf(c, inv, kRoundMagic);
+            return static_cast<uint32_t>(static_cast<int>(c)) +
+                   static_cast<uint32_t>(times24(t, -m));
+        });
     else if (exact || m > 244)
         store([&](int c) {
             asm volatile("; two steps" : "+v"(c));
@@ -863,11 +900,17 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 inline ResidueGeom residue_geom(int64_t M, int64_t N, int64_t K, int frag_k)
 {
     ResidueGeom g;
-    // the largest tile that still gives every compute unit four (T = 4) or two
-    // (T = 2) workgroups: fewer leave part of the chip idle in the last round
+    // The largest tile that still fills the chip.  T = 4 from four workgroups
+    // per compute unit on (fewer leave much of it idle in the last round) and
+    // K >= 512, below which the 64 KiB its four stages hold are mostly start-up:
+    // 200 against 209 us (T = 2) per call at 2048^3 and 553 against 614 at
+    // 3072^3, but 115 against 106 at 1536^3 and 118 against 106 at
+    // 2500 x 2500 x 300.  T = 2 from one workgroup per compute unit on: 27.0
+    // against 27.5 us (T = 1) at 512^3, 49 against 58 at 1024^3, and 17.2
+    // against 16.5 at 256^3.
     const int64_t tiles256 = ffh::cdiv(M, 256) * ffh::cdiv(N, 256) * kModuli;
     const int64_t tiles128 = ffh::cdiv(M, 128) * ffh::cdiv(N, 128) * kModuli;
-    g.tile = tiles256 >= 1024 ? 4 : tiles128 >= 512 ? 2 : 1;
+    g.tile = tiles256 >= 1024 && K >= 512 ? 4 : tiles128 >= 256 ? 2 : 1;
     g.nTI = ffh::cdiv(M, 64 * g.tile);
     g.nTJ = ffh::cdiv(N, 64 * g.tile);
     g.nRB = g.nTI * 2 * g.tile;
