@@ -89,7 +89,7 @@ const char *ff_last_error(void);
 /*     (r_hi[i], r_lo[i]) = OP((a_hi[i], a_lo[i]), (b_hi[i], b_lo[i]))      */
 /* All six planes (four in, two out) hold n binary32 values.  Results are  */
 /* bit-identical to the documented binary32 operation sequence, whatever   */
-/* the alignment and launch form (float4 groups below 2^22 elements when   */
+/* the alignment and launch form (float4 groups below 2^24 elements when   */
 /* every plane is 16-byte aligned, 4-byte accesses otherwise).  Errors:    */
 /* FF_ERR_SIZE (n < 0), FF_ERR_NULL (a NULL plane, n > 0), FF_ERR_ALIGN,   */
 /* FF_ERR_HIP.                                                              */
@@ -492,7 +492,7 @@ ff_status ff_gemm(int64_t M, int64_t N, int64_t K, const float *A_hi,
  *                    "Mad"; gfx950 has no unfused binary32 multiply-add)
  * All pointers: device, caller-owned, n binary32 words each; an output may
  * alias an input exactly (in place), partial overlap is undefined.  Below
- * 2^22 elements, when every pointer is 16-byte aligned, a float4 path runs;
+ * 2^24 elements, when every pointer is 16-byte aligned, a float4 path runs;
  * otherwise 4-byte accesses, one lane-contiguous element per lane and
  * plane at a time.  Results do not depend on the path.
  * Errors: FF_ERR_SIZE (n < 0), FF_ERR_NULL, FF_ERR_ALIGN (a pointer not
@@ -538,9 +538,11 @@ ff_status ff_f32_mad(const float *a, const float *b, const float *c, float *r,
  * Arguments: coef / coef_hi (non-null) and coef_lo (null: zero low words);
  * x / x_hi (non-null) and x_lo (null: binary32 points); y / y_hi, y_lo
  * (non-null).  All device pointers, caller-owned, 4-byte aligned; the float4
- * path runs when every point and result plane is 16-byte aligned.  A result
- * plane may alias a point plane exactly (in place); coefficients must not
- * alias a result.
+ * path runs above 2^17 points (binary32, compensated) or 2^18 (float-float),
+ * for binary32 also below degree 16, when every point and result plane is
+ * 16-byte aligned, one point per lane otherwise; results do not depend on it.
+ * A result plane may alias a point plane exactly (in place); coefficients
+ * must not alias a result.
  * Errors: FF_ERR_NULL, FF_ERR_SIZE (degree < 0 or n < 0), FF_ERR_ALIGN,
  * FF_ERR_HIP.  n = 0 is a no-op. */
 ff_status ff_horner_f32(const float *coef, int32_t degree, const float *x,

@@ -11,8 +11,8 @@
 // b0 + t + kBlock k (k < kPer) of every plane, so each wavefront access is
 // 256 contiguous bytes of a plane, issues all its non-temporal 4-byte loads
 // before any arithmetic, and stores non-temporally.  Any 4-byte alignment.
-// Below 2^22 elements (cache-resident) one float4 group per plane and thread
-// instead, when the planes are 16-byte aligned.
+// Below 2^24 elements (mostly cache-resident) one float4 group per plane and
+// thread instead, when the planes are 16-byte aligned.
 #include "ff_device.h"
 #include "ff_host.h"
 
@@ -42,8 +42,13 @@ struct Div22Accurate { static constexpr int op = ffd::OP_DIV_ACCURATE; };
 constexpr int kBlock = 128;   // 2 wavefronts of 64 lanes
 constexpr int kPer = 2;       // elements per thread per plane
 constexpr int64_t kSpan = static_cast<int64_t>(kBlock) * kPer;
-// The float4 path for cache-resident sizes keeps 1024-thread workgroups.
-constexpr int kVecBlock = 1024;
+// The float4 path for cache-resident sizes: 256-thread workgroups, so that a
+// small call spreads over the compute units (one workgroup of 1024 does 4096
+// elements on a single one).  us per launch, 256 against 1024 threads: Add22
+// 2.15 / 2.31 at 4096, 2.07 / 2.43 at 2^14, 4.14 / 4.70 at 2^20, 7.4 / 8.8 at
+// 2^21; Div22 2.15 / 2.56 at 4096.  64 and 512 threads are within 3 % of 256 up
+// to 2^18 and 10-15 % slower beyond.
+constexpr int kVecBlock = 256;
 
 template <typename T>
 __device__ __forceinline__ T ld_nt(const T *p) { return __builtin_nontemporal_load(p); }
@@ -91,25 +96,42 @@ __global__ __launch_bounds__(kBlock) void ew_stream(const float *ah, const float
     }
 }
 
-// Below kSmallN elements the data sit in the 256 MB Infinity Cache and the
-// launches are latency-bound; there one float4 group of every plane per
-// thread (four times fewer load instructions) is as fast or faster (Add22 at
-// 2^21: 7.6 against 8.6 us), while the lane-contiguous form wins from 2^22
-// on (16.5 against 17.2 us).  The tail of n that is not a whole float4
-// group runs in the lane-contiguous kernel.
-constexpr int64_t kSmallN = int64_t(1) << 22;
+// Below kSmallN elements (24 bytes each: the 256 MB Infinity Cache holds most
+// of them) one float4 group of every plane per thread, four times fewer memory
+// instructions: Add22 7.4 us against 8.6 lane-contiguous at 2^21, 14.8 against
+// 18.0 at 2^22, 30.9 against 33.0 at 2^23; equal at 2^24 (62.9 / 63.0, Div22
+// 63.6 / 61.8), and HBM prefers the lane-contiguous form beyond (130 / 126 at
+// 2^25).  The last thread takes the elements after the last whole group one by
+// one: a launch of their own cost 1.3 us on the device and a launch gap.
+constexpr int64_t kSmallN = int64_t(1) << 24;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <class Tag>
-__global__ __launch_bounds__(kVecBlock) void ew_vec(const f32x4 *ah, const f32x4 *al,
-                                                   const f32x4 *bh, const f32x4 *bl, f32x4 *rh,
-                                                   f32x4 *rl, int64_t nvec)
+__global__ __launch_bounds__(kVecBlock) void ew_vec(const float *ah, const float *al,
+                                                    const float *bh, const float *bl, float *rh,
+                                                    float *rl, int64_t n)
 {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kVecBlock + threadIdx.x;
-    if (i >= nvec)
+    const int64_t i = 4 * (static_cast<int64_t>(blockIdx.x) * kVecBlock + threadIdx.x);
+    if (i >= n)
         return;
-    const f32x4 xah = ld_nt(ah + i), xal = ld_nt(al + i), xbh = ld_nt(bh + i),
-                xbl = ld_nt(bl + i);
+    // the last lane repeats the last element instead of reading past it
+    const bool whole = i + 4 <= n;
+    f32x4 xah, xal, xbh, xbl;
+    if (whole) {
+        xah = ld_nt(reinterpret_cast<const f32x4 *>(ah + i));
+        xal = ld_nt(reinterpret_cast<const f32x4 *>(al + i));
+        xbh = ld_nt(reinterpret_cast<const f32x4 *>(bh + i));
+        xbl = ld_nt(reinterpret_cast<const f32x4 *>(bl + i));
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t e = i + k < n ? i + k : n - 1;
+            xah[k] = ld_nt(ah + e);
+            xal[k] = ld_nt(al + e);
+            xbh[k] = ld_nt(bh + e);
+            xbl[k] = ld_nt(bl + e);
+        }
+    }
     f32x4 oh, ol;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -118,8 +140,17 @@ __global__ __launch_bounds__(kVecBlock) void ew_vec(const f32x4 *ah, const f32x4
         oh[k] = h;
         ol[k] = l;
     }
-    st_nt(oh, rh + i);
-    st_nt(ol, rl + i);
+    if (whole) {
+        st_nt(oh, reinterpret_cast<f32x4 *>(rh + i));
+        st_nt(ol, reinterpret_cast<f32x4 *>(rl + i));
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (i + k < n) {
+            st_nt(oh[k], rh + i + k);
+            st_nt(ol[k], rl + i + k);
+        }
 }
 
 // The copy probe (bandwidth reference and counter calibration): one plane
@@ -167,26 +198,15 @@ ff_status elementwise(const float *ah, const float *al, const float *bh, const f
     bool vec = n < kSmallN;
     for (const void *p : ptrs)
         vec = vec && ffh::aligned(p, 16);
-    int64_t done = 0;
-    if (vec) {
-        const int64_t nvec = n / 4;
-        done = 4 * nvec;
-        if (nvec > 0)
-            hipLaunchKernelGGL(ew_vec<Tag>, dim3(static_cast<unsigned>(ffh::cdiv(nvec, kVecBlock))),
-                               dim3(kVecBlock), 0, stream, reinterpret_cast<const f32x4 *>(ah),
-                               reinterpret_cast<const f32x4 *>(al),
-                               reinterpret_cast<const f32x4 *>(bh),
-                               reinterpret_cast<const f32x4 *>(bl), reinterpret_cast<f32x4 *>(rh),
-                               reinterpret_cast<f32x4 *>(rl), nvec);
-    }
-    if (done < n) {
-        const int64_t blocks = ffh::cdiv(n - done, kSpan);
-        if (blocks > INT32_MAX)
-            return FF_ERR_SIZE;
+    const int64_t blocks = vec ? ffh::cdiv(n, 4 * kVecBlock) : ffh::cdiv(n, kSpan);
+    if (blocks > INT32_MAX)
+        return FF_ERR_SIZE;
+    if (vec)
+        hipLaunchKernelGGL(ew_vec<Tag>, dim3(static_cast<unsigned>(blocks)), dim3(kVecBlock), 0,
+                           stream, ah, al, bh, bl, rh, rl, n);
+    else
         hipLaunchKernelGGL(ew_stream<Tag>, dim3(static_cast<unsigned>(blocks)), dim3(kBlock), 0,
-                           stream, ah + done, al + done, bh + done, bl + done, rh + done,
-                           rl + done, n - done);
-    }
+                           stream, ah, al, bh, bl, rh, rl, n);
     return ffh::launch_status();
 }
 

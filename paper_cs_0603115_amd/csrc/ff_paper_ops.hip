@@ -10,14 +10,14 @@
 // by 4 for binary32 Add and Mul), all 4-byte
 // non-temporal loads issued before the arithmetic (plane by plane where the
 // kernel writes two planes), any 4-byte alignment; one float4 group per plane
-// and thread below 2^22 elements.  Bytes per element: 12 (add, mul), 16 (mad,
+// and thread below 2^24 elements.  Bytes per element: 12 (add, mul), 16 (mad,
 // Add12, Mul12); all HBM-bound at large n, launch-bound at the paper's sizes.
 #include "ff_device.h"
 #include "ff_host.h"
 
 namespace ffk {
 
-constexpr int kStreamBlock = 1024;   // workgroup of the float4 form (below 2^22)
+constexpr int kStreamBlock = 256;   // workgroup of the float4 form (below 2^24)
 
 // An operator maps IN binary32 inputs of one element to OUT outputs.
 struct OpAdd12 {
@@ -65,23 +65,35 @@ struct StreamPlanes {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Below kStreamSmallN elements (cache-resident, latency-bound launches) one
+// Below kStreamSmallN elements (mostly cache-resident) one
 // float4 group of every plane per thread is faster, as for the float-float
-// operators; the tail that is not a whole group and larger n run the
-// lane-contiguous kernel.
-constexpr int64_t kStreamSmallN = int64_t(1) << 22;
+// operators (the last thread takes the elements after the last whole group
+// one by one); larger n run the lane-contiguous kernel.  us, float4 against
+// lane-contiguous: Add 7.4 / 8.1 at 2^22 and 29.4 / 31.1 at 2^24, Add12 11.0 /
+// 12.3 and 43.2 / 40.8, Mad 9.4 / 10.2 and 42.2 / 40.4.
+constexpr int64_t kStreamSmallN = int64_t(1) << 24;
 
 template <class Op>
 __global__ __launch_bounds__(kStreamBlock) void stream_vec(StreamPlanes<Op::kIn, Op::kOut> p,
-                                                           int64_t nvec)
+                                                           int64_t n)
 {
-    const int64_t g = static_cast<int64_t>(blockIdx.x) * kStreamBlock + threadIdx.x;
-    if (g >= nvec)
+    const int64_t i = 4 * (static_cast<int64_t>(blockIdx.x) * kStreamBlock + threadIdx.x);
+    if (i >= n)
         return;
+    // the last lane repeats the last element instead of reading past it
+    const bool whole = i + 4 <= n;
     f32x4 x[Op::kIn], y[Op::kOut];
+    if (whole) {
 #pragma unroll
-    for (int k = 0; k < Op::kIn; ++k)
-        x[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.in[k]) + g);
+        for (int k = 0; k < Op::kIn; ++k)
+            x[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.in[k] + i));
+    } else {
+#pragma unroll
+        for (int k = 0; k < Op::kIn; ++k)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                x[k][c] = __builtin_nontemporal_load(p.in[k] + (i + c < n ? i + c : n - 1));
+    }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         float xi[Op::kIn], yo[Op::kOut];
@@ -93,9 +105,19 @@ __global__ __launch_bounds__(kStreamBlock) void stream_vec(StreamPlanes<Op::kIn,
         for (int k = 0; k < Op::kOut; ++k)
             y[k][c] = yo[k];
     }
+    if (whole) {
 #pragma unroll
-    for (int k = 0; k < Op::kOut; ++k)
-        __builtin_nontemporal_store(y[k], reinterpret_cast<f32x4 *>(p.out[k]) + g);
+        for (int k = 0; k < Op::kOut; ++k)
+            __builtin_nontemporal_store(y[k], reinterpret_cast<f32x4 *>(p.out[k] + i));
+        return;
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        if (i + c < n) {
+#pragma unroll
+            for (int k = 0; k < Op::kOut; ++k)
+                __builtin_nontemporal_store(y[k][c], p.out[k] + i + c);
+        }
 }
 
 // Launch shape of the lane-contiguous form, from sweeps at N = 2^28: the
@@ -179,27 +201,16 @@ ff_status stream_op(StreamPlanes<Op::kIn, Op::kOut> p, int64_t n, void *stream_p
         vec = vec && ffh::aligned(p.in[k], 16);
     for (int k = 0; k < Op::kOut; ++k)
         vec = vec && ffh::aligned(p.out[k], 16);
-    int64_t done = 0;
-    if (vec) {
-        const int64_t nvec = n / 4;
-        done = 4 * nvec;
-        if (nvec > 0)
-            hipLaunchKernelGGL(stream_vec<Op>,
-                               dim3(static_cast<unsigned>(ffh::cdiv(nvec, kStreamBlock))),
-                               dim3(kStreamBlock), 0, st, p, nvec);
-    }
-    if (done < n) {
-        StreamPlanes<Op::kIn, Op::kOut> rest = p;
-        for (int k = 0; k < Op::kIn; ++k)
-            rest.in[k] += done;
-        for (int k = 0; k < Op::kOut; ++k)
-            rest.out[k] += done;
-        const int64_t blocks = ffh::cdiv(n - done, StreamShape<Op>::kSpan);
-        if (blocks > INT32_MAX)
-            return FF_ERR_SIZE;
+    const int64_t blocks = vec ? ffh::cdiv(n, 4 * kStreamBlock)
+                               : ffh::cdiv(n, StreamShape<Op>::kSpan);
+    if (blocks > INT32_MAX)
+        return FF_ERR_SIZE;
+    if (vec)
+        hipLaunchKernelGGL(stream_vec<Op>, dim3(static_cast<unsigned>(blocks)), dim3(kStreamBlock),
+                           0, st, p, n);
+    else
         hipLaunchKernelGGL(stream_op_kernel<Op>, dim3(static_cast<unsigned>(blocks)),
-                           dim3(StreamShape<Op>::kBlock), 0, st, rest, n - done);
-    }
+                           dim3(StreamShape<Op>::kBlock), 0, st, p, n);
     return ffh::launch_status();
 }
 

@@ -42,9 +42,19 @@ struct PolyArgs {
     float *yl;          // low words of the float-float result, else unused
 };
 
+// Up to kFewPoints points, from degree kFewDegree on, one point per lane: with
+// too few wavefronts to keep the vector units busy, the four recurrences of a
+// lane only make each four times longer.  Measured (us, one point per lane
+// against four): float-float 3.2 / 6.5 at 1000 points and degree 25, 5.1 / 7.2
+// at 2^18; compensated 2.5 / 3.9 and 2.8 / 4.2 at 2^17, but 2.6 / 2.5 at 2^18
+// and degree 5; binary32 2.2 / 2.5 at 1000 and degree 25, but 2.2 / 2.2 at
+// degree 5 and 3.2 / 2.8 at 2^18.
+//
 // Horner's rule in binary32: s = (s (x) x) (+) c_i, two roundings per step.
 struct HornerF32 {
     static constexpr bool kFF = false;
+    static constexpr int64_t kFewPoints = int64_t(1) << 17;
+    static constexpr int kFewDegree = 16;
     struct State { float s; };
     __device__ __forceinline__ static void init(State &st, float ch, float) { st.s = ch; }
     __device__ __forceinline__ static void step(State &st, float x, float, float ch, float)
@@ -61,6 +71,8 @@ struct HornerF32 {
 // r = (r (x) x) (+) (pi (+) sigma); result s (+) r.
 struct HornerComp {
     static constexpr bool kFF = false;
+    static constexpr int64_t kFewPoints = int64_t(1) << 17;
+    static constexpr int kFewDegree = 0;
     struct State { float s, r; };
     __device__ __forceinline__ static void init(State &st, float ch, float)
     {
@@ -83,6 +95,8 @@ struct HornerComp {
 // Float-float Horner: s = Add22(Mul22(s, x), c_i).
 struct HornerFF {
     static constexpr bool kFF = true;
+    static constexpr int64_t kFewPoints = int64_t(1) << 18;
+    static constexpr int kFewDegree = 0;
     struct State { float h, l; };
     __device__ __forceinline__ static void init(State &st, float ch, float cl)
     {
@@ -102,17 +116,29 @@ struct HornerFF {
     }
 };
 
-// Four points per lane: the float4 group g of every plane.
+// Four points per lane: the float4 group of every plane, the last lane's
+// points after the last whole group one by one.
 template <class Alg, bool CLO, bool XLO>
-__global__ __launch_bounds__(kPolyBlock) void horner_vec(PolyArgs a, int64_t ngroups)
+__global__ __launch_bounds__(kPolyBlock) void horner_vec(PolyArgs a, int64_t n)
 {
-    const int64_t g = static_cast<int64_t>(blockIdx.x) * kPolyBlock + threadIdx.x;
-    if (g >= ngroups)
+    const int64_t k = 4 * (static_cast<int64_t>(blockIdx.x) * kPolyBlock + threadIdx.x);
+    if (k >= n)
         return;
-    const f32x4 xh = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(a.xh) + g);
-    f32x4 xl = {0.0f, 0.0f, 0.0f, 0.0f};
-    if constexpr (XLO)
-        xl = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(a.xl) + g);
+    const bool whole = k + 4 <= n;
+    f32x4 xh = {0.0f, 0.0f, 0.0f, 0.0f}, xl = xh;
+    if (whole) {
+        xh = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(a.xh + k));
+        if constexpr (XLO)
+            xl = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(a.xl + k));
+    } else {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (k + c < n) {
+                xh[c] = a.xh[k + c];
+                if constexpr (XLO)
+                    xl[c] = a.xl[k + c];
+            }
+    }
     typename Alg::State st[4];
     {
         const float th = a.ch[a.degree];
@@ -137,13 +163,22 @@ __global__ __launch_bounds__(kPolyBlock) void horner_vec(PolyArgs a, int64_t ngr
         yh[c] = h;
         yl[c] = l;
     }
-    __builtin_nontemporal_store(yh, reinterpret_cast<f32x4 *>(a.yh) + g);
-    if constexpr (Alg::kFF)
-        __builtin_nontemporal_store(yl, reinterpret_cast<f32x4 *>(a.yl) + g);
+    if (whole) {
+        __builtin_nontemporal_store(yh, reinterpret_cast<f32x4 *>(a.yh + k));
+        if constexpr (Alg::kFF)
+            __builtin_nontemporal_store(yl, reinterpret_cast<f32x4 *>(a.yl + k));
+    } else {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (k + c < n) {
+                a.yh[k + c] = yh[c];
+                if constexpr (Alg::kFF)
+                    a.yl[k + c] = yl[c];
+            }
+    }
 }
 
-// One point per lane: the tail after the float4 groups, and planes that are
-// not 16-byte aligned.
+// One point per lane: few points, and planes that are not 16-byte aligned.
 template <class Alg, bool CLO, bool XLO>
 __global__ __launch_bounds__(kPolyBlock) void horner_scalar(PolyArgs a, int64_t n)
 {
@@ -154,6 +189,7 @@ __global__ __launch_bounds__(kPolyBlock) void horner_scalar(PolyArgs a, int64_t 
         const float xl = XLO ? a.xl[k] : 0.0f;
         typename Alg::State st;
         Alg::init(st, a.ch[a.degree], CLO ? a.cl[a.degree] : 0.0f);
+#pragma unroll 8
         for (int32_t i = a.degree - 1; i >= 0; --i)
             Alg::step(st, xh, xl, a.ch[i], CLO ? a.cl[i] : 0.0f);
         float h, l = 0.0f;
@@ -167,30 +203,16 @@ __global__ __launch_bounds__(kPolyBlock) void horner_scalar(PolyArgs a, int64_t 
 template <class Alg, bool CLO, bool XLO>
 ff_status launch_horner(PolyArgs a, int64_t n, bool vec, hipStream_t st)
 {
-    int64_t done = 0;
+    const int64_t blocks = vec ? ffh::cdiv(n, 4 * kPolyBlock) : ffh::cdiv(n, kPolyBlock);
     if (vec) {
-        const int64_t ngroups = n / 4;
-        done = 4 * ngroups;
-        if (ngroups > 0) {
-            const int64_t blocks = ffh::cdiv(ngroups, kPolyBlock);
-            if (blocks > INT32_MAX)
-                return FF_ERR_SIZE;
-            hipLaunchKernelGGL((horner_vec<Alg, CLO, XLO>), dim3(static_cast<unsigned>(blocks)),
-                               dim3(kPolyBlock), 0, st, a, ngroups);
-        }
-    }
-    if (done < n) {
-        PolyArgs rest = a;
-        rest.xh += done;
-        if (XLO)
-            rest.xl += done;
-        rest.yh += done;
-        if (Alg::kFF)
-            rest.yl += done;
-        const int64_t blocks = ffh::cdiv(n - done, kPolyBlock);
+        if (blocks > INT32_MAX)
+            return FF_ERR_SIZE;
+        hipLaunchKernelGGL((horner_vec<Alg, CLO, XLO>), dim3(static_cast<unsigned>(blocks)),
+                           dim3(kPolyBlock), 0, st, a, n);
+    } else {
         hipLaunchKernelGGL((horner_scalar<Alg, CLO, XLO>),
                            dim3(static_cast<unsigned>(blocks < 65536 ? blocks : 65536)),
-                           dim3(kPolyBlock), 0, st, rest, n - done);
+                           dim3(kPolyBlock), 0, st, a, n);
     }
     return ffh::launch_status();
 }
@@ -206,7 +228,7 @@ ff_status horner(PolyArgs a, int64_t n, void *stream_ptr)
     if (!a.ch || !a.xh || !a.yh || (Alg::kFF && !a.yl))
         return FF_ERR_NULL;
     const void *planes[] = {a.ch, a.cl, a.xh, a.xl, a.yh, Alg::kFF ? a.yl : nullptr};
-    bool vec = true;
+    bool vec = n > Alg::kFewPoints || a.degree < Alg::kFewDegree;
     for (const void *p : planes) {
         if (!p)
             continue;

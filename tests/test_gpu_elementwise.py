@@ -212,3 +212,23 @@ def test_full_size_n2_28_bitexact(op):
     assert_parity(op, a, b, r, "full 2^28")
     del a, b, r
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("op", ["add", "div"])
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 1023, 1024, 1025, 1026, 1027, (1 << 22) + 3,
+                               (1 << 24) - 1, (1 << 24) + 1])
+def test_last_lane_of_the_float4_form(op, n):
+    # aligned planes: the elements after the last whole float4 group, at the
+    # edges of a workgroup and of the sizes that take this form; the words
+    # after the last element stay untouched
+    _announce(f"[gpu] elementwise float4 tail n={n} op={op}")
+    a, b, _ = fi.mixed_ff_pair(n, 1100 + n % 997)
+    ff = _ff()
+    da, db = ff.ff_empty((n,)), ff.ff_empty((n,))
+    da.copy_(a)
+    db.copy_(b)
+    base = torch.full((2, n + 8 - n % 4), 7.0, device="cuda")
+    out = base[:, :n]
+    gpu_op(op, da, db, out=out)
+    assert_parity(op, da, db, out, f"n={n}")
+    assert torch.all(base[:, n:] == 7.0)

@@ -170,3 +170,23 @@ def test_accuracy_against_condition_number():
         fmt = ["exact" if v is None else f"2^{v:.1f}" for v in lg]
         _announce(f"  n={n} cond 2^[{b},{b + 8}): max rel error Horner {fmt[0]}, "
                   f"CompHorner {fmt[1]}, ff Horner {fmt[2]}")
+
+
+@pytest.mark.parametrize("algo,n", [
+    (a, b + k) for a, b in (("f32", 1 << 17), ("comp", 1 << 17), ("ff", 1 << 18))
+    for k in (0, 1, 2, 3, 4, 5)] + [("f32", k) for k in (1, 2, 3, 6)])
+def test_four_points_per_lane_and_its_last_lane(algo, n):
+    # both sides of the point count from which a lane takes four points, with
+    # every number of points left for the last lane; low degree, where binary32
+    # takes four points from one point on
+    degree = 9
+    _announce(f"[gpu] horner {algo} n={n}")
+    coef = fi.random_poly(degree, 1901, ff=(algo == "ff"))
+    x = fi.horner_points(n, 1902, -1.2, 1.2)
+    pts = torch.stack([x, 1e-9 * x]) if algo == "ff" else x
+    dev = pts.cuda()
+    if algo == "ff":                       # aligned planes
+        dev = _ff().ff_empty((n,))
+        dev.copy_(pts)
+    got = _gpu(algo, coef.cuda(), dev)
+    _check(got, _want(algo, coef.numpy(), pts.numpy()), f"{algo} n={n}")
