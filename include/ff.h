@@ -191,8 +191,9 @@ ff_status ff_div_accurate(const float *a_hi, const float *a_lo,
  * paper defines no reduction; compensated summation is its stated future
  * work (section 7).
  *
- * Execution: four launches on `stream`: a planning launch (chunk counts and
- * their scan), one writing each chunk's element range, one reducing the
+ * Execution: two to four launches on `stream`: planning (chunk counts, their
+ * scan and each chunk's element range: in the next launch for up to 1024
+ * vectors, one launch up to 16384, two beyond), one reducing the
  * chunks -- one workgroup per chunk of block * unroll elements, launched in
  * chunk order so that the resident workgroups stream memory together; each
  * thread adds its `unroll` terms in order into a float-float accumulator,
@@ -208,9 +209,11 @@ ff_status ff_div_accurate(const float *a_hi, const float *a_lo,
  * at worst over a batch of 4096 vectors of 64 to 2^20 normal(0,1) terms).
  */
 
-/* Launch shape of the batched reductions.  Zero fields select the entry
- * point's default: 256 threads by 32 elements per thread (chunks of 8192
- * elements) for every input kind. */
+/* Launch shape of the batched reductions.  Zero fields select the default:
+ * 256 threads by 32 elements per thread (chunks of 8192 elements); with no
+ * field set, batches of few elements take 8 per thread (chunks of 2048): up
+ * to 2^21 elements, and for dots and float-float sums up to 2^25 if vectors
+ * average at most 2^17 elements, as long as ws_bytes holds their chunks. */
 typedef struct ff_dot_cfg {
     int32_t block;  /* threads per workgroup: 64, 128, 256 or 512            */
     int32_t chunk;  /* elements per chunk: 0 or block * unroll (with unroll
@@ -221,9 +224,9 @@ typedef struct ff_dot_cfg {
 } ff_dot_cfg;
 
 /* Bytes of device workspace the batched reductions need for nvec vectors
- * holding total_len elements in all, with this cfg (zero fields resolved
- * with the default chunk, 8192, which every entry point shares).  Returns 0
- * for invalid arguments. */
+ * holding total_len elements in all, with this cfg (for the default shape:
+ * enough for this total and any smaller one).  Returns 0 for invalid
+ * arguments. */
 size_t ff_dot_batched_workspace_size(int64_t total_len, int32_t nvec,
                                      const ff_dot_cfg *cfg);
 

@@ -2,10 +2,10 @@
 //
 // Data: vector v is [offsets[v], offsets[v+1]) of the concatenated inputs
 // (binary32 x, y, or float-float planes xh, xl, yh, yl).  A vector is cut
-// into chunks of `chunk` = block * unroll elements.  Four stream-ordered
-// launches:
-//   plan      one workgroup: chunk counts per vector and their exclusive scan
-//   records   one wavefront per vector: the element range of each chunk
+// into chunks of `chunk` = block * unroll elements.  Stream-ordered launches:
+//   plan      chunk counts per vector, their exclusive scan, and the element
+//             range of each chunk: within the partials launch for up to 1024
+//             vectors, one launch up to 16384, two (scan, ranges) beyond
 //   partials  one workgroup per chunk, launched in chunk order (which is
 //             memory order): thread t takes the chunk's elements t + block k
 //             (k < unroll) of every plane with 4-byte loads, all issued
@@ -55,11 +55,15 @@ inline int64_t chunk_capacity(int64_t total, int32_t nvec, int64_t chunk)
     return total / chunk + nvec;
 }
 
-inline size_t workspace_bytes(int64_t total, int32_t nvec, int64_t chunk)
+inline size_t workspace_bytes_for(int64_t cap, int32_t nvec)
 {
-    const int64_t cap = chunk_capacity(total, nvec, chunk);
     return align256(sizeof(int64_t) * (nvec + 1)) + align256(sizeof(longlong2) * cap) +
            align256(sizeof(float2) * cap);
+}
+
+inline size_t workspace_bytes(int64_t total, int32_t nvec, int64_t chunk)
+{
+    return workspace_bytes_for(chunk_capacity(total, nvec, chunk), nvec);
 }
 
 inline Workspace carve(void *ws, int64_t total, int32_t nvec, int64_t chunk)
@@ -73,6 +77,14 @@ inline Workspace carve(void *ws, int64_t total, int32_t nvec, int64_t chunk)
     p += align256(sizeof(longlong2) * w.cap);
     w.partials = reinterpret_cast<float2 *>(p);
     return w;
+}
+
+// A value that every lane holds, as a scalar.
+__device__ __forceinline__ int64_t uniform(int64_t x)
+{
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(x));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(x >> 32));
+    return static_cast<int64_t>(static_cast<uint64_t>(hi) << 32 | lo);
 }
 
 __device__ __forceinline__ int64_t clamp_offset(int64_t o, int64_t total)
@@ -173,6 +185,144 @@ __global__ __launch_bounds__(256) void dot_ranges(const int64_t *__restrict__ of
     }
 }
 
+// Scan and ranges in one launch for up to kMergedPlanMax vectors: a
+// workgroup of 1024 threads writes the records of kPlanGroup vectors and
+// counts the chunks of all vectors before them itself, four vectors per thread
+// and round in flight, which costs less than a launch between the two.
+constexpr int kPlanGroup = 64;
+constexpr int32_t kMergedPlanMax = 16384;
+
+__device__ __forceinline__ int64_t chunks_of(const int64_t *__restrict__ offsets, int64_t v,
+                                             int64_t total, int shift, int64_t &b, int64_t &e)
+{
+    b = clamp_offset(offsets[v], total);
+    e = clamp_offset(offsets[v + 1], total);
+    return e > b ? (e - b + (int64_t(1) << shift) - 1) >> shift : 0;
+}
+
+__global__ __launch_bounds__(kPlanBlock) void dot_plan_ranges(const int64_t *__restrict__ offsets,
+                                                              int32_t nvec, int64_t total,
+                                                              int shift, Workspace w)
+{
+    constexpr int kWaves = kPlanBlock / 64;
+    __shared__ int64_t wave_sum[kWaves], start[kPlanGroup + 1];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int64_t v0 = static_cast<int64_t>(blockIdx.x) * kPlanGroup;
+    int64_t before = 0, b, e;
+    // vectors past v0 - 1 are read (v0 < nvec) but not counted, so that the
+    // four loads need no branch
+    for (int64_t v = t; v < v0; v += 4 * kPlanBlock) {
+        int64_t n[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t at = v + k * kPlanBlock;
+            n[k] = chunks_of(offsets, at < v0 ? at : v0, total, shift, b, e);
+            n[k] = at < v0 ? n[k] : 0;
+        }
+        before += n[0] + n[1] + n[2] + n[3];
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1)
+        before += __shfl_xor(before, m, 64);
+    if (lane == 0)
+        wave_sum[wave] = before;
+    __syncthreads();
+    if (wave == 0) {
+        before = 0;
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q)
+            before += wave_sum[q];
+        const int64_t v = v0 + lane;
+        const int64_t mine = v < nvec ? chunks_of(offsets, v, total, shift, b, e) : 0;
+        const int64_t incl = before + wave_inclusive_scan(mine, lane);
+        start[lane + 1] = incl;
+        if (lane == 0)
+            start[0] = before;
+        if (v < nvec)
+            w.chunk_start[v] = incl - mine;
+        if (v == nvec - 1)
+            w.chunk_start[nvec] = incl;
+    }
+    __syncthreads();
+    for (int i = wave; i < kPlanGroup && v0 + i < nvec; i += kWaves) {
+        chunks_of(offsets, v0 + i, total, shift, b, e);
+        const int64_t c0 = start[i];
+        const int64_t c1 = start[i + 1] < w.cap ? start[i + 1] : w.cap;
+        for (int64_t c = c0 + lane; c < c1; c += 64) {
+            const int64_t rs = b + ((c - c0) << shift), next = rs + (int64_t(1) << shift);
+            w.ranges[c] = make_longlong2(rs, e < next ? e : next);
+        }
+    }
+}
+
+// Plan within the partials launch, for few vectors and chunks: every
+// workgroup scans the chunk counts and finds its own chunk; workgroup 0 also
+// stores the scan for the combine.  Returns false for a workgroup past the
+// last chunk.
+constexpr int32_t kInlinePlanVectors = 1024;
+constexpr int64_t kInlinePlanChunks = 8192;
+// vectors times workgroups: every workgroup scans all vectors, which pays as
+// long as that is less than the launches saved.  us, within / before: 61
+// vectors 7.0 / 11.7; 500 vectors and 4345 chunks 46.9 / 51.7; but 1000 vectors
+// and 4271 chunks 49.3 / 43.4.
+constexpr int64_t kInlinePlanWork = int64_t(1) << 22;
+
+template <int BLOCK>
+__device__ __forceinline__ bool inline_plan(const int64_t *__restrict__ offsets, int32_t nvec,
+                                            int64_t total, int shift, const Workspace &w,
+                                            int64_t &s, int64_t &e)
+{
+    constexpr int kWaves = BLOCK / 64;
+    __shared__ int wave_sum[kWaves];
+    __shared__ int64_t range[2];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int per = (nvec + BLOCK - 1) / BLOCK;
+    const int v0 = t * per, v1 = v0 + per < nvec ? v0 + per : nvec;
+    int mine = 0;
+    int64_t vb, ve;
+    for (int v = v0; v < v1; ++v)
+        mine += static_cast<int>(chunks_of(offsets, v, total, shift, vb, ve));
+    int incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(incl, d, 64);
+        if (lane >= d)
+            incl += o;
+    }
+    if (lane == 63)
+        wave_sum[wave] = incl;
+    __syncthreads();
+    int before = incl - mine, all = 0;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) {
+        if (q < wave)
+            before += wave_sum[q];
+        all += wave_sum[q];
+    }
+    const int c = static_cast<int>(blockIdx.x);
+    if (c == 0 || (before <= c && c < before + mine)) {
+        int first = before;
+        for (int v = v0; v < v1; ++v) {
+            const int n = static_cast<int>(chunks_of(offsets, v, total, shift, vb, ve));
+            if (c == 0)
+                w.chunk_start[v] = first;
+            if (first <= c && c < first + n) {
+                const int64_t rs = vb + (static_cast<int64_t>(c - first) << shift);
+                const int64_t next = rs + (int64_t(1) << shift);
+                range[0] = rs;
+                range[1] = ve < next ? ve : next;
+            }
+            first += n;
+        }
+    }
+    if (c == 0 && t == 0)
+        w.chunk_start[nvec] = all;
+    __syncthreads();
+    s = range[0];
+    e = range[1];
+    return c < all && c < w.cap;
+}
+
 // Accumulation policies.  A partial is a pair of binary32 words (h, l).
 // AccFF: float-float accumulation, every term and every partial added with
 // Add22 (section 4.1); the pair is the result.
@@ -236,7 +386,18 @@ __global__ __launch_bounds__(256) void dot_combine(int32_t nvec, Workspace w,
     int64_t c1 = w.chunk_start[v + 1];
     c1 = c1 < w.cap ? c1 : w.cap;
     float h = 0.0f, l = 0.0f;
-    for (int64_t c = c0 + lane; c < c1; c += 64) {
+    int64_t c = c0 + lane;
+    // eight loads in flight: one at a time a vector of 2048 chunks took 15 us
+    for (; c + 7 * 64 < c1; c += 8 * 64) {
+        float2 p[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            p[k] = w.partials[c + 64 * k];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            Acc::merge(h, l, p[k].x, p[k].y);
+    }
+    for (; c < c1; c += 64) {
         const float2 p = w.partials[c];
         Acc::merge(h, l, p.x, p.y);
     }
@@ -341,19 +502,18 @@ struct Terms<InSumFF> {
 // accumulator.  A butterfly over the wavefront, then the wavefronts' sums in
 // index order, give the chunk's partial.  The order is fixed by (BLOCK,
 // PER), so results are reproducible run to run.
+// A chunk of a short vector, or a vector's last, takes the number of loads
+// that its length needs (4096 vectors of 64 to 4096 elements: 21 us, against 28
+// with all 32 loads).
 template <class In, class Acc, int BLOCK, int PER>
-__global__ __launch_bounds__(BLOCK) void dot_chunks(In in, Workspace w, int32_t nvec)
+__device__ __forceinline__ void accumulate(const In &in, int64_t s, int64_t e, float &h, float &l)
 {
-    constexpr int kWaves = BLOCK / 64;
-    __shared__ float2 wave_part[kWaves];
-    const int64_t c = blockIdx.x;
-    int64_t nchunks = w.chunk_start[nvec];
-    if (nchunks > w.cap)
-        nchunks = w.cap;
-    if (c >= nchunks)
-        return;
-    const longlong2 r = w.ranges[c];
-    const int64_t s = r.x, e = r.y;   // s < e: recorded chunks are not empty
+    if constexpr (PER > 4) {
+        if (e - s <= BLOCK * (PER / 2)) {
+            accumulate<In, Acc, BLOCK, PER / 2>(in, s, e, h, l);
+            return;
+        }
+    }
     const int t = threadIdx.x;
     float v[PER][In::kPlanes];
 #pragma unroll
@@ -361,7 +521,6 @@ __global__ __launch_bounds__(BLOCK) void dot_chunks(In in, Workspace w, int32_t 
         const int64_t i = s + t + static_cast<int64_t>(BLOCK) * k;
         Terms<In>::load(in, i < e ? i : s, v[k]);   // past the end: a harmless in-range load
     }
-    float h = 0.0f, l = 0.0f;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int64_t i = s + t + static_cast<int64_t>(BLOCK) * k;
@@ -371,6 +530,36 @@ __global__ __launch_bounds__(BLOCK) void dot_chunks(In in, Workspace w, int32_t 
             Acc::add(h, l, ph, pl);
         }
     }
+}
+
+// INLINE: the chunk's range comes from inline_plan, otherwise from the
+// records of the plan launches.
+template <class In, class Acc, int BLOCK, int PER, bool INLINE>
+__global__ __launch_bounds__(BLOCK) void dot_chunks(In in, const int64_t *__restrict__ offsets,
+                                                    int32_t nvec, int64_t total, Workspace w)
+{
+    constexpr int kWaves = BLOCK / 64;
+    __shared__ float2 wave_part[kWaves];
+    const int64_t c = blockIdx.x;
+    int64_t s, e;   // s < e: recorded chunks are not empty
+    if constexpr (INLINE) {
+        if (!inline_plan<BLOCK>(offsets, nvec, total, __builtin_ctz(BLOCK * PER), w, s, e))
+            return;
+        s = uniform(s);
+        e = uniform(e);
+    } else {
+        int64_t nchunks = w.chunk_start[nvec];
+        if (nchunks > w.cap)
+            nchunks = w.cap;
+        if (c >= nchunks)
+            return;
+        const longlong2 r = w.ranges[c];
+        s = r.x;
+        e = r.y;
+    }
+    const int t = threadIdx.x;
+    float h = 0.0f, l = 0.0f;
+    accumulate<In, Acc, BLOCK, PER>(in, s, e, h, l);
     wave_allreduce<Acc>(h, l);
     if ((t & 63) == 0)
         wave_part[t >> 6] = make_float2(h, l);
@@ -389,14 +578,48 @@ struct Cfg {
     int64_t chunk;
 };
 
-// Default launch shape, the fastest measured on MI355X for every input kind
-// on the 4096-vector batch (438.9 M elements): 256 threads by 32 elements
-// (chunks of 8192), 0.84 of the HBM peak for both dots and the float-float
+// Default launch shape: 256 threads by 32 elements (chunks of 8192), the
+// fastest measured on MI355X for every input kind on the 4096-vector batch
+// (438.9 M elements): 0.84 of the HBM peak for both dots and the float-float
 // sum and 0.80 for the binary32 sum, against 0.75-0.83 at 128-512 threads by
-// 4-16 elements.
-template <class In> struct DefaultShape {
-    static constexpr int kBlock = 256, kUnroll = 32;
-};
+// 4-16 elements.  Batches that leave too few of those chunks to fill the chip
+// take 8 elements (chunks of 2048): up to 2^21 elements, and where an element
+// has two words or more up to 2^25 as long as a vector averages at most 64
+// chunks (its partials are combined by one wavefront).  us, 8 against 32
+// elements: float-float dots of 500 vectors 11.7 / 18.3 at 1.5 M elements,
+// 20.2 / 26.2 at 4.7 M, 47.6 / 51.8 at 15.8 M; binary32 dots 9.8 / 11.2, 15.0 /
+// 14.7, 32.0 / 30.0 and, 1000 vectors, 41.4 / 43.4 at 26.8 M; binary32 sums 9.0 /
+// 9.9, but 13.4 / 11.3 at 4.7 M.
+constexpr int kDefaultBlock = 256, kDefaultUnroll = 32, kShortUnroll = 8;
+constexpr int64_t kShortChunk = int64_t(kDefaultBlock) * kShortUnroll;
+constexpr int64_t kShortTotal = int64_t(1) << 21, kShortTotalMost = int64_t(1) << 25;
+constexpr int32_t kShortVectors = 1 << 16;
+
+bool is_default(const ff_dot_cfg *cfg)
+{
+    return !cfg || (cfg->block == 0 && cfg->chunk == 0 && cfg->grid == 0 && cfg->unroll == 0);
+}
+
+bool short_chunks(int64_t total, int32_t nvec, int planes)
+{
+    return nvec <= kShortVectors &&
+           (total <= kShortTotal || (planes >= 2 && total <= kShortTotalMost &&
+                                     total <= static_cast<int64_t>(nvec) * 64 * kShortChunk));
+}
+
+// Workspace of the default shape: enough for either chunk length at this
+// total or any smaller one, so that a workspace sized for a caller's largest
+// batch serves its smaller ones.
+size_t default_workspace_bytes(int64_t total, int32_t nvec)
+{
+    int64_t chunks = total / (int64_t(kDefaultBlock) * kDefaultUnroll);
+    if (nvec <= kShortVectors) {
+        const int64_t most =
+            (total < kShortTotalMost ? total : kShortTotalMost) / kShortChunk;
+        chunks = chunks > most ? chunks : most;
+    }
+    return workspace_bytes_for(chunks + nvec, nvec);
+}
 
 bool valid_unroll(int u)
 {
@@ -407,10 +630,10 @@ bool valid_unroll(int u)
 // two), chunk = block * unroll; zero fields take the kind's default (an
 // unroll of zero with a chunk given takes chunk / block); grid is reserved
 // and must be zero.
-ff_status resolve_cfg(const ff_dot_cfg *cfg, int def_block, int def_unroll, Cfg &out)
+ff_status resolve_cfg(const ff_dot_cfg *cfg, Cfg &out)
 {
-    out.block = def_block;
-    out.unroll = def_unroll;
+    out.block = kDefaultBlock;
+    out.unroll = kDefaultUnroll;
     int64_t chunk = 0;
     if (cfg) {
         if (cfg->grid != 0 || cfg->block < 0 || cfg->chunk < 0 || cfg->unroll < 0)
@@ -433,18 +656,29 @@ ff_status resolve_cfg(const ff_dot_cfg *cfg, int def_block, int def_unroll, Cfg 
     return FF_OK;
 }
 
-template <class In, class Acc, int BLOCK>
-void launch_chunks(int unroll, unsigned grid, hipStream_t st, const In &in, const Workspace &w,
-                   int32_t nvec)
+template <class In, class Acc, int BLOCK, int PER>
+void launch_partials(bool inlined, unsigned grid, hipStream_t st, const In &in,
+                     const int64_t *offsets, int32_t nvec, int64_t total, const Workspace &w)
 {
-    switch (unroll) {
-    case 1: hipLaunchKernelGGL((dot_chunks<In, Acc, BLOCK, 1>), dim3(grid), dim3(BLOCK), 0, st, in, w, nvec); break;
-    case 2: hipLaunchKernelGGL((dot_chunks<In, Acc, BLOCK, 2>), dim3(grid), dim3(BLOCK), 0, st, in, w, nvec); break;
-    case 4: hipLaunchKernelGGL((dot_chunks<In, Acc, BLOCK, 4>), dim3(grid), dim3(BLOCK), 0, st, in, w, nvec); break;
-    case 8: hipLaunchKernelGGL((dot_chunks<In, Acc, BLOCK, 8>), dim3(grid), dim3(BLOCK), 0, st, in, w, nvec); break;
-    case 16: hipLaunchKernelGGL((dot_chunks<In, Acc, BLOCK, 16>), dim3(grid), dim3(BLOCK), 0, st, in, w, nvec); break;
-    default: hipLaunchKernelGGL((dot_chunks<In, Acc, BLOCK, 32>), dim3(grid), dim3(BLOCK), 0, st, in, w, nvec); break;
-    }
+    if (inlined)
+        hipLaunchKernelGGL((dot_chunks<In, Acc, BLOCK, PER, true>), dim3(grid), dim3(BLOCK), 0, st,
+                           in, offsets, nvec, total, w);
+    else
+        hipLaunchKernelGGL((dot_chunks<In, Acc, BLOCK, PER, false>), dim3(grid), dim3(BLOCK), 0,
+                           st, in, offsets, nvec, total, w);
+}
+
+template <class In, class Acc, int BLOCK>
+void launch_chunks(int unroll, bool inlined, unsigned grid, hipStream_t st, const In &in,
+                   const int64_t *offsets, int32_t nvec, int64_t total, const Workspace &w)
+{
+    auto launch = unroll == 1    ? launch_partials<In, Acc, BLOCK, 1>
+                  : unroll == 2  ? launch_partials<In, Acc, BLOCK, 2>
+                  : unroll == 4  ? launch_partials<In, Acc, BLOCK, 4>
+                  : unroll == 8  ? launch_partials<In, Acc, BLOCK, 8>
+                  : unroll == 16 ? launch_partials<In, Acc, BLOCK, 16>
+                                 : launch_partials<In, Acc, BLOCK, 32>;
+    launch(inlined, grid, st, in, offsets, nvec, total, w);
 }
 
 template <class In, class Acc = AccFF>
@@ -453,12 +687,17 @@ ff_status dot_batched_entry(const In &in, const int64_t *offsets, int32_t nvec, 
                             float *out_lo, void *stream_ptr)
 {
     Cfg cfg;
-    const ff_status cs =
-        resolve_cfg(cfg_in, DefaultShape<In>::kBlock, DefaultShape<In>::kUnroll, cfg);
+    const ff_status cs = resolve_cfg(cfg_in, cfg);
     if (cs != FF_OK)
         return cs;
     if (nvec == 0)
         return FF_OK;
+    // (a workspace that only holds the long chunks of the default keeps them)
+    if (is_default(cfg_in) && short_chunks(total, nvec, In::kPlanes) &&
+        ws_bytes >= workspace_bytes(total, nvec, kShortChunk)) {
+        cfg.unroll = kShortUnroll;
+        cfg.chunk = kShortChunk;
+    }
     if (!offsets || !out_hi || !out_lo || !ws)
         return FF_ERR_NULL;
     if (!ffh::aligned(offsets, 8) || !ffh::aligned(out_hi, 4) || !ffh::aligned(out_lo, 4) ||
@@ -472,25 +711,27 @@ ff_status dot_batched_entry(const In &in, const int64_t *offsets, int32_t nvec, 
     hipStream_t st = ffh::as_stream(stream_ptr);
     const unsigned wave_blocks = static_cast<unsigned>(ffh::cdiv(nvec, 4));
     const unsigned grid = static_cast<unsigned>(w.cap);
-    hipLaunchKernelGGL(dot_plan, dim3(1), dim3(kPlanBlock), 0, st, offsets, nvec, total,
-                       cfg.chunk, w);
-    hipLaunchKernelGGL(dot_ranges, dim3(wave_blocks), dim3(256), 0, st, offsets, nvec, total,
-                       cfg.chunk, w);
-    switch (cfg.block) {
-    case 64: launch_chunks<In, Acc, 64>(cfg.unroll, grid, st, in, w, nvec); break;
-    case 128: launch_chunks<In, Acc, 128>(cfg.unroll, grid, st, in, w, nvec); break;
-    case 256: launch_chunks<In, Acc, 256>(cfg.unroll, grid, st, in, w, nvec); break;
-    default: launch_chunks<In, Acc, 512>(cfg.unroll, grid, st, in, w, nvec); break;
+    const bool inlined = nvec <= kInlinePlanVectors && w.cap <= kInlinePlanChunks &&
+                         nvec * w.cap <= kInlinePlanWork;
+    if (!inlined && nvec <= kMergedPlanMax) {
+        hipLaunchKernelGGL(dot_plan_ranges,
+                           dim3(static_cast<unsigned>(ffh::cdiv(nvec, kPlanGroup))), dim3(kPlanBlock),
+                           0, st, offsets, nvec, total, __builtin_ctzll(cfg.chunk), w);
+    } else if (!inlined) {
+        hipLaunchKernelGGL(dot_plan, dim3(1), dim3(kPlanBlock), 0, st, offsets, nvec, total,
+                           cfg.chunk, w);
+        hipLaunchKernelGGL(dot_ranges, dim3(wave_blocks), dim3(256), 0, st, offsets, nvec, total,
+                           cfg.chunk, w);
     }
+    auto chunks = cfg.block == 64    ? launch_chunks<In, Acc, 64>
+                  : cfg.block == 128 ? launch_chunks<In, Acc, 128>
+                  : cfg.block == 256 ? launch_chunks<In, Acc, 256>
+                                     : launch_chunks<In, Acc, 512>;
+    chunks(cfg.unroll, inlined, grid, st, in, offsets, nvec, total, w);
     hipLaunchKernelGGL(dot_combine<Acc>, dim3(wave_blocks), dim3(256), 0, st, nvec, w, out_hi,
                        out_lo);
     return ffh::launch_status();
 }
-
-// The smallest default chunk over the input kinds: a workspace sized for it
-// serves every kind's default shape.
-constexpr int64_t kSmallestDefaultChunk =
-    static_cast<int64_t>(DefaultShape<InFF>::kBlock) * DefaultShape<InFF>::kUnroll;
 
 } // namespace ffk
 
@@ -500,12 +741,11 @@ extern "C" {
 
 size_t ff_dot_batched_workspace_size(int64_t total_len, int32_t nvec, const ff_dot_cfg *cfg)
 {
-    // resolved with the smallest default chunk of the input kinds: enough for
-    // every entry point called with this cfg
     Cfg c;
-    if (total_len < 0 || nvec < 0 ||
-        resolve_cfg(cfg, DefaultShape<InFF>::kBlock, DefaultShape<InFF>::kUnroll, c) != FF_OK)
+    if (total_len < 0 || nvec < 0 || resolve_cfg(cfg, c) != FF_OK)
         return 0;
+    if (is_default(cfg))
+        return default_workspace_bytes(total_len, nvec);
     return workspace_bytes(total_len, nvec, c.chunk);
 }
 
@@ -650,8 +890,7 @@ ff_status ff_dot_batched_noalloc(const float *x, const float *y, const int64_t *
     if (!ffh::aligned(x, 4) || !ffh::aligned(y, 4))
         return FF_ERR_ALIGN;
     Cfg c;
-    const ff_status cs =
-        resolve_cfg(cfg, DefaultShape<InF32>::kBlock, DefaultShape<InF32>::kUnroll, c);
+    const ff_status cs = resolve_cfg(cfg, c);
     if (cs != FF_OK)
         return cs;
     if (nvec == 0)

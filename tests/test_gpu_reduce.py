@@ -286,3 +286,66 @@ def test_out_of_range_offsets_are_clamped():
     ex2 = oracle.exact_dot(xn[:10], yn[:10])
     assert abs(frac(got[0, 2]) + frac(got[1, 2]) - ex2) <= TWO_M44 * oracle.exact_dot(
         np.abs(xn[:10]), np.abs(yn[:10]))
+
+
+@pytest.mark.parametrize("kind", ["dot", "dot_ff", "sum"])
+def test_plan_forms_give_the_same_bits(kind):
+    # the same vectors planned within the partials launch (up to 1024 vectors),
+    # by one launch (up to 16384) and by two: empty vectors appended after them
+    # move the batch from one form to the next and change nothing else.
+    # Lengths at the edges of the loads a chunk issues and of chunks.
+    ff = _ff()
+    edges = [1, 2, 255, 256, 257]
+    for per in (4, 8, 16, 32):
+        edges += [256 * per - 1, 256 * per, 256 * per + 1]
+    lengths = np.array(edges + [0, 0, 3 * 8192 + 5, 20000, 0] + [7] * 900)
+    rng = np.random.default_rng(4711)
+    lengths = lengths[rng.permutation(len(lengths))]
+    n = len(lengths)
+    total = int(lengths.sum()) + 11                   # elements of no vector at the end
+    _announce(f"[gpu] dot plan forms, {kind}, {n} vectors, {total} elements")
+    x, y = (fi.gaussian_ff((total,), 4712 + k).cuda() for k in range(2))
+
+    def run(nvec, cfg):
+        offs = np.full(nvec + 1, int(lengths.sum()), dtype=np.int64)
+        offs[:n + 1] = np.concatenate([[0], np.cumsum(lengths)])
+        offs = torch.from_numpy(offs).cuda()
+        if kind == "dot":
+            r = ff.ff_dot_batched(x[0], y[0], offs, cfg=cfg)
+        elif kind == "dot_ff":
+            r = ff.ff_dot_ff_batched(x, y, offs, cfg=cfg)
+        else:
+            r = ff.ff_sum_batched(x[0], offs, cfg=cfg)
+        return r.cpu().numpy().view(np.uint32), offs.cpu()
+
+    for cfg in (None, (256, 8192, 0, 32), (64, 0, 0, 1)):
+        want, offs = run(n, cfg)
+        for nvec in (1024, 1025, 16384, 16385):
+            got, _ = run(nvec, cfg)
+            assert np.array_equal(got[:, :n], want), (cfg, nvec)
+            assert not got[:, n:].any(), (cfg, nvec)
+    if kind == "dot":
+        got = ff.ff_dot_batched(x[0], y[0], offs.cuda())
+        check_against_exact(x[0], y[0], offs, got, (256, 0, 0, 8), "plan forms")
+
+
+def test_default_shape_by_size_and_workspace():
+    # a workspace that only holds chunks of 8192 is still accepted for a batch
+    # that would take chunks of 2048, and gives that shape's results; the
+    # queried size grows with the batch
+    ff = _ff()
+    x, y, offs = fi.batched_dot(4721, device="cuda", nvec=40, log2_min=6, log2_max=16)
+    long_shape = (256, 8192, 0, 32)
+    small = ff.ff_dot_batched_workspace_size(x.numel(), 40, long_shape)
+    assert small < ff.ff_dot_batched_workspace_size(x.numel(), 40)
+    ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+    got = ff.ff_dot_batched(x, y, offs, workspace=None)
+    want = ff.ff_dot_batched(x, y, offs, cfg=long_shape)
+    status = ff.lib.ff_dot_batched(x.data_ptr(), y.data_ptr(), offs.data_ptr(), 40, x.numel(),
+                                   None, ws.data_ptr(), small, got[0].data_ptr(),
+                                   got[1].data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert status == 0
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+    sizes = [ff.ff_dot_batched_workspace_size(1 << b, 40) for b in range(10, 33)]
+    assert sizes == sorted(sizes)
