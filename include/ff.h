@@ -421,6 +421,15 @@ ff_status ff_dot_batched_backward(const float *g_hi, const float *g_lo,
                                   float *dx_lo, float *dy_hi, float *dy_lo,
                                   void *ws, size_t ws_bytes, void *stream);
 
+/* A gradient delivered plane by plane as a float-float value: where both
+ * planes of g hold the same number (ordinary operations on the two planes of
+ * a value send each its own partial derivative, and the two are equal; a
+ * normalised float-float number never has equal words except zero), v = (g_hi,
+ * 0); elsewhere v = (g_hi, g_lo).  n values; v may not overlap g.
+ * Errors: FF_ERR_SIZE (n < 0), FF_ERR_NULL, FF_ERR_ALIGN, FF_ERR_HIP. */
+ff_status ff_gradient_value(const float *g_hi, const float *g_lo, float *v_hi,
+                            float *v_lo, int64_t n, void *stream);
+
 /* ------------------------------------------------------------------------ */
 /* Matrix product C = A B                                                   */
 /* ------------------------------------------------------------------------ */

@@ -31,7 +31,7 @@ __all__ = [
     "ff_dot_batched_workspace_size",
     "ff_sum_batched", "ff_sum_ff_batched", "ff_dot2_batched", "ff_sum2_batched",
     "ff_matvec", "ff_matvec_backward", "ff_matvec_backward_workspace_size", "ff_dot_backward",
-    "ff_dot_batched_backward", "ff_dot_batched_backward_workspace_size",
+    "ff_dot_batched_backward", "ff_dot_batched_backward_workspace_size", "ff_gradient_value",
     "MATVEC_FAST", "MATVEC_PLAIN",
     "ff_gemm", "ff_gemm_workspace_size", "GEMM_FMA_LOOP", "GEMM_SLICED_BF16", "GEMM_SLICED_I8",
     "ff_empty", "ff_zeros", "ff_from_f64", "ff_to_f64",
@@ -44,6 +44,11 @@ def build_info() -> str:
     return lib.ff_build_info().decode()
 
 
+# The binding is on the path of every small call, where it costs more than the
+# kernel: a tensor is described by its strides and address (no views are made
+# of its planes), the raw handle of the current stream is read directly, and
+# the device is switched only when it has to be.
+
 def _torch_stream(stream):
     if isinstance(stream, torch.cuda.Stream):
         return stream
@@ -55,11 +60,11 @@ def _on_stream(fn):
     so that the outputs and workspaces it allocates belong to the stream its
     kernels are enqueued on: the caching allocator then cannot hand that
     memory to other work before those kernels are done with it."""
-    sig = inspect.signature(fn)
+    position = list(inspect.signature(fn).parameters).index("stream")
 
     @functools.wraps(fn)
     def run(*args, **kwargs):
-        stream = sig.bind_partial(*args, **kwargs).arguments.get("stream")
+        stream = args[position] if len(args) > position else kwargs.get("stream")
         if stream is None:
             return fn(*args, **kwargs)
         with torch.cuda.stream(_torch_stream(stream)):
@@ -68,63 +73,93 @@ def _on_stream(fn):
     return run
 
 
-def _stream_handle(stream) -> ctypes.c_void_p:
+def _enqueue(name: str, device: torch.device, stream, *args) -> None:
+    """Call entry point ``name`` with ``args`` and, last, the stream: the
+    current one of ``device`` unless given."""
+    index = device.index
+    if index != torch._C._cuda_getDevice():
+        with torch.cuda.device(device):
+            _enqueue(name, device, stream, *args)
+        return
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        handle = torch._C._cuda_getCurrentRawStream(index)
+    else:
+        handle = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    status = getattr(lib, name)(*args, handle)
+    if status:
+        check(name, status)
+
+
+def _dense(shape, strides, first: int) -> bool:
+    """Whether the dimensions from ``first`` on are contiguous (as
+    torch.Tensor.is_contiguous counts them: dimensions of one element have any
+    stride, and nothing is asked of an empty tensor)."""
+    expect = 1
+    for d in range(len(shape) - 1, first - 1, -1):
+        size = shape[d]
+        if size != 1:
+            if size == 0:
+                return True
+            if strides[d] != expect:
+                return 0 in shape[first:]
+            expect *= size
+    return True
 
 
 def _check_ff(t: torch.Tensor, name: str) -> None:
     if not isinstance(t, torch.Tensor) or t.dtype != torch.float32:
         raise TypeError(f"{name}: expected a float32 tensor")
-    if t.dim() < 1 or t.shape[0] != 2:
+    shape = t.shape
+    if len(shape) < 1 or shape[0] != 2:
         raise ValueError(f"{name}: a float-float tensor has shape (2, ...), got {tuple(t.shape)}")
     if not t.is_cuda:
         raise ValueError(f"{name}: must be on a HIP device (libff runs on the GPU only)")
-    if not (t[0].is_contiguous() and t[1].is_contiguous()):
+    if not _dense(shape, t.stride(), 1):
         raise ValueError(f"{name}: each plane must be contiguous")
 
 
 def _planes(t: torch.Tensor):
-    return ctypes.c_void_p(t[0].data_ptr()), ctypes.c_void_p(t[1].data_ptr())
+    """Addresses of the two planes (0 for an empty tensor)."""
+    hi = t.data_ptr()
+    return (hi, hi + 4 * t.stride(0)) if hi else (0, 0)
 
 
 # Plane stride granule of ff_empty / ff_zeros, in binary32 words (4 KiB).
 PLANE_ALIGN = 1024
 
 
-def _planar(alloc, shape, device) -> torch.Tensor:
-    """A (2, *shape) float32 tensor whose two planes are each contiguous and
-    start a multiple of 4 KiB apart.  The allocator aligns the first plane,
-    so both are: a wavefront's access of 64 consecutive words of either plane
-    is then one aligned 256-byte segment.  (In a plain (2, n) tensor the low
-    plane starts 4n bytes after the high one; unless n is a multiple of 64
-    every such access straddles two segments, which cost the streaming
-    kernels up to 8 % of their rate on MI355X.)"""
-    shape = tuple(int(d) for d in shape)
-    numel = 1
-    for d in shape:
-        numel *= d
-    stride = -(-max(numel, 1) // PLANE_ALIGN) * PLANE_ALIGN
-    base = alloc(2 * stride, dtype=torch.float32, device=device)
-    inner = []
-    acc = 1
+def _plane_layout(shape):
+    """(size, strides) of a float-float tensor of value shape ``shape`` whose
+    two planes are each contiguous and start a multiple of 4 KiB apart.  The
+    allocator aligns the first plane, so both are: a wavefront's access of 64
+    consecutive words of either plane is then one aligned 256-byte segment.
+    (In a plain (2, n) tensor the low plane starts 4n bytes after the high one;
+    unless n is a multiple of 64 every such access straddles two segments,
+    which cost the streaming kernels up to 8 % of their rate on MI355X.)"""
+    size, strides, acc = [], [], 1
     for d in reversed(shape):
-        inner.append(acc)
-        acc *= max(d, 1)
-    return base.as_strided((2, *shape), (stride, *reversed(inner)))
+        d = int(d)
+        size.append(d)
+        strides.append(acc)
+        acc *= d if d > 1 else 1
+    words = 0 if 0 in size else acc
+    strides.append(-(-max(words, 1) // PLANE_ALIGN) * PLANE_ALIGN)
+    size.append(2)
+    return size[::-1], strides[::-1]
 
 
 def ff_empty(shape, device="cuda") -> torch.Tensor:
     """Uninitialised float-float tensor of the given value shape (planes
-    aligned as described in _planar)."""
-    return _planar(torch.empty, shape, device)
+    aligned as described in _plane_layout)."""
+    size, strides = _plane_layout(shape)
+    return torch.empty_strided(size, strides, dtype=torch.float32, device=device)
 
 
 def ff_zeros(shape, device="cuda") -> torch.Tensor:
     """Float-float zeros of the given value shape (planes aligned as
-    described in _planar)."""
-    return _planar(torch.zeros, shape, device)
+    described in _plane_layout)."""
+    size, strides = _plane_layout(shape)
+    return torch.zeros(2 * strides[0], dtype=torch.float32, device=device).as_strided(size, strides)
 
 
 def _elementwise(name: str, a: torch.Tensor, b: torch.Tensor, out, stream) -> torch.Tensor:
@@ -140,12 +175,11 @@ def _elementwise(name: str, a: torch.Tensor, b: torch.Tensor, out, stream) -> to
         _check_ff(out, "out")
         if out.shape != a.shape:
             raise ValueError(f"{name}: out has shape {tuple(out.shape)}")
-    n = a[0].numel()
+    n = a.numel() // 2
     ah, al = _planes(a)
     bh, bl = _planes(b)
     rh, rl = _planes(out)
-    with torch.cuda.device(a.device):
-        check(name, getattr(lib, name)(ah, al, bh, bl, rh, rl, n, _stream_handle(stream)))
+    _enqueue(name, a.device, stream, ah, al, bh, bl, rh, rl, n)
     return out
 
 
@@ -217,9 +251,7 @@ def ff_copy(src: torch.Tensor, dst: torch.Tensor, stream=None) -> torch.Tensor:
         raise ValueError("ff_copy: contiguous tensors of equal size expected")
     if not src.is_cuda:
         raise ValueError("ff_copy: tensors must be on a HIP device")
-    with torch.cuda.device(src.device):
-        check("ff_copy", lib.ff_copy(ctypes.c_void_p(src.data_ptr()), ctypes.c_void_p(dst.data_ptr()),
-                                     src.numel(), _stream_handle(stream)))
+    _enqueue("ff_copy", src.device, stream, src.data_ptr(), dst.data_ptr(), src.numel())
     return dst
 
 
@@ -243,8 +275,8 @@ def _check_pair_out(name: str, out: torch.Tensor, a: torch.Tensor) -> None:
         raise ValueError(f"{name}: out must have shape {(2, *a.shape)} on {a.device}")
 
 
-def _ptr(t: torch.Tensor) -> ctypes.c_void_p:
-    return ctypes.c_void_p(t.data_ptr())
+def _ptr(t: torch.Tensor) -> int:
+    return t.data_ptr()
 
 
 @_on_stream
@@ -254,9 +286,7 @@ def ff_add12(a: torch.Tensor, b: torch.Tensor, out=None, stream=None) -> torch.T
     _f32_operands("ff_add12", a, b)
     out = ff_empty(a.shape, device=a.device) if out is None else out
     _check_pair_out("ff_add12", out, a)
-    with torch.cuda.device(a.device):
-        check("ff_add12", lib.ff_add12(_ptr(a), _ptr(b), *_planes(out), a.numel(),
-                                       _stream_handle(stream)))
+    _enqueue("ff_add12", a.device, stream, _ptr(a), _ptr(b), *_planes(out), a.numel())
     return out
 
 
@@ -269,9 +299,7 @@ def ff_mul12(a: torch.Tensor, b: torch.Tensor, dekker: bool = False, out=None,
     _f32_operands(name, a, b)
     out = ff_empty(a.shape, device=a.device) if out is None else out
     _check_pair_out(name, out, a)
-    with torch.cuda.device(a.device):
-        check(name, getattr(lib, name)(_ptr(a), _ptr(b), *_planes(out), a.numel(),
-                                       _stream_handle(stream)))
+    _enqueue(name, a.device, stream, _ptr(a), _ptr(b), *_planes(out), a.numel())
     return out
 
 
@@ -279,9 +307,7 @@ def _f32_binary(name: str, a, b, out, stream) -> torch.Tensor:
     _f32_operands(name, a, b)
     out = torch.empty_like(a) if out is None else out
     _f32_operands(name, a, out)
-    with torch.cuda.device(a.device):
-        check(name, getattr(lib, name)(_ptr(a), _ptr(b), _ptr(out), a.numel(),
-                                       _stream_handle(stream)))
+    _enqueue(name, a.device, stream, _ptr(a), _ptr(b), _ptr(out), a.numel())
     return out
 
 
@@ -303,9 +329,7 @@ def f32_mad(a, b, c, out=None, stream=None) -> torch.Tensor:
     _f32_operands("ff_f32_mad", a, b, c)
     out = torch.empty_like(a) if out is None else out
     _f32_operands("ff_f32_mad", a, out)
-    with torch.cuda.device(a.device):
-        check("ff_f32_mad", lib.ff_f32_mad(_ptr(a), _ptr(b), _ptr(c), _ptr(out), a.numel(),
-                                           _stream_handle(stream)))
+    _enqueue("ff_f32_mad", a.device, stream, _ptr(a), _ptr(b), _ptr(c), _ptr(out), a.numel())
     return out
 
 
@@ -323,9 +347,7 @@ def ff_from_f64(x: torch.Tensor, out=None, stream=None) -> torch.Tensor:
     _check_ff(out, "out")
     if tuple(out.shape) != (2, *x.shape) or out.device != x.device:
         raise ValueError(f"ff_from_f64: out must have shape {(2, *x.shape)} on {x.device}")
-    with torch.cuda.device(x.device):
-        check("ff_from_f64", lib.ff_from_f64(_ptr(x), *_planes(out), x.numel(),
-                                             _stream_handle(stream)))
+    _enqueue("ff_from_f64", x.device, stream, _ptr(x), *_planes(out), x.numel())
     return out
 
 
@@ -339,9 +361,7 @@ def ff_to_f64(a: torch.Tensor, out=None, stream=None) -> torch.Tensor:
     if not isinstance(out, torch.Tensor) or out.dtype != torch.float64 or \
             tuple(out.shape) != shape or out.device != a.device or not out.is_contiguous():
         raise ValueError(f"ff_to_f64: out must be a contiguous float64 tensor of shape {shape}")
-    with torch.cuda.device(a.device):
-        check("ff_to_f64", lib.ff_to_f64(*_planes(a), _ptr(out), out.numel(),
-                                         _stream_handle(stream)))
+    _enqueue("ff_to_f64", a.device, stream, *_planes(a), _ptr(out), out.numel())
     return out
 
 
@@ -355,15 +375,15 @@ def _coefficients(name: str, coef: torch.Tensor, ff: bool):
     if coef.dim() == 1:
         if not coef.is_contiguous():
             raise ValueError(f"{name}: coefficients must be contiguous")
-        hi, lo, count = coef, None, coef.numel()
+        hi, lo, count = _ptr(coef), None, coef.numel()
     elif ff and coef.dim() == 2 and coef.shape[0] == 2:
         _check_ff(coef, "coef")
-        hi, lo, count = coef[0], coef[1], coef.shape[1]
+        (hi, lo), count = _planes(coef), coef.shape[1]
     else:
         raise ValueError(f"{name}: coefficients of shape {tuple(coef.shape)}")
     if count < 1:
         raise ValueError(f"{name}: a polynomial needs at least one coefficient")
-    return _ptr(hi), (None if lo is None else _ptr(lo)), count - 1
+    return hi, lo, count - 1
 
 
 def _horner_f32(name, coef, x, out, stream):
@@ -373,9 +393,7 @@ def _horner_f32(name, coef, x, out, stream):
         raise ValueError(f"{name}: coefficients and points on different devices")
     out = torch.empty_like(x) if out is None else out
     _f32_operands(name, x, out)
-    with torch.cuda.device(x.device):
-        check(name, getattr(lib, name)(ch, degree, _ptr(x), _ptr(out), x.numel(),
-                                       _stream_handle(stream)))
+    _enqueue(name, x.device, stream, ch, degree, _ptr(x), _ptr(out), x.numel())
     return out
 
 
@@ -418,9 +436,7 @@ def ff_horner_ff(coef, x, out=None, stream=None, ff_points: bool = True) -> torc
     n = 1
     for d in shape:
         n *= d
-    with torch.cuda.device(dev):
-        check(name, lib.ff_horner_ff(ch, cl, degree, xh, xl, *_planes(out), n,
-                                     _stream_handle(stream)))
+    _enqueue("ff_horner_ff", dev, stream, ch, cl, degree, xh, xl, *_planes(out), n)
     return out
 
 
@@ -473,11 +489,8 @@ def ff_dot_batched(x: torch.Tensor, y: torch.Tensor, offsets: torch.Tensor, cfg=
     nbytes = ff_dot_batched_workspace_size(x.numel(), nvec, cfg)
     ws = _workspace(nbytes, x.device, workspace)
     oh, ol = _planes(out)
-    with torch.cuda.device(x.device):
-        check("ff_dot_batched", lib.ff_dot_batched(
-            ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
-            ctypes.c_void_p(offsets.data_ptr()), nvec, x.numel(), _cfg_ptr(cfg),
-            ctypes.c_void_p(ws.data_ptr()), ws.numel(), oh, ol, _stream_handle(stream)))
+    _enqueue("ff_dot_batched", x.device, stream, x.data_ptr(), y.data_ptr(), offsets.data_ptr(),
+             nvec, x.numel(), _cfg_ptr(cfg), ws.data_ptr(), ws.numel(), oh, ol)
     return out
 
 
@@ -497,11 +510,8 @@ def ff_dot_batched_noalloc(x: torch.Tensor, y: torch.Tensor, offsets: torch.Tens
     out = ff_empty((nvec,), device=x.device) if out is None else out
     _check_ff(out, "out")
     oh, ol = _planes(out)
-    with torch.cuda.device(x.device):
-        check("ff_dot_batched_noalloc", lib.ff_dot_batched_noalloc(
-            ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
-            ctypes.c_void_p(offsets.data_ptr()), nvec, x.numel(), _cfg_ptr(cfg), oh, ol,
-            _stream_handle(stream)))
+    _enqueue("ff_dot_batched_noalloc", x.device, stream, x.data_ptr(), y.data_ptr(),
+             offsets.data_ptr(), nvec, x.numel(), _cfg_ptr(cfg), oh, ol)
     return out
 
 
@@ -521,11 +531,8 @@ def ff_dot2_batched(x: torch.Tensor, y: torch.Tensor, offsets: torch.Tensor, cfg
     _check_ff(out, "out")
     ws = _workspace(ff_dot_batched_workspace_size(x.numel(), nvec, cfg), x.device, workspace)
     oh, ol = _planes(out)
-    with torch.cuda.device(x.device):
-        check("ff_dot2_batched", lib.ff_dot2_batched(
-            ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
-            ctypes.c_void_p(offsets.data_ptr()), nvec, x.numel(), _cfg_ptr(cfg),
-            ctypes.c_void_p(ws.data_ptr()), ws.numel(), oh, ol, _stream_handle(stream)))
+    _enqueue("ff_dot2_batched", x.device, stream, x.data_ptr(), y.data_ptr(), offsets.data_ptr(),
+             nvec, x.numel(), _cfg_ptr(cfg), ws.data_ptr(), ws.numel(), oh, ol)
     return out
 
 
@@ -541,11 +548,8 @@ def ff_sum2_batched(x: torch.Tensor, offsets: torch.Tensor, cfg=None, out=None, 
     _check_ff(out, "out")
     ws = _workspace(ff_dot_batched_workspace_size(x.numel(), nvec, cfg), x.device, workspace)
     oh, ol = _planes(out)
-    with torch.cuda.device(x.device):
-        check("ff_sum2_batched", lib.ff_sum2_batched(
-            ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(offsets.data_ptr()), nvec, x.numel(),
-            _cfg_ptr(cfg), ctypes.c_void_p(ws.data_ptr()), ws.numel(), oh, ol,
-            _stream_handle(stream)))
+    _enqueue("ff_sum2_batched", x.device, stream, x.data_ptr(), offsets.data_ptr(), nvec,
+             x.numel(), _cfg_ptr(cfg), ws.data_ptr(), ws.numel(), oh, ol)
     return out
 
 
@@ -567,10 +571,8 @@ def ff_dot_ff_batched(x: torch.Tensor, y: torch.Tensor, offsets: torch.Tensor, c
     xh, xl = _planes(x)
     yh, yl = _planes(y)
     oh, ol = _planes(out)
-    with torch.cuda.device(x.device):
-        check("ff_dot_ff_batched", lib.ff_dot_ff_batched(
-            xh, xl, yh, yl, ctypes.c_void_p(offsets.data_ptr()), nvec, total, _cfg_ptr(cfg),
-            ctypes.c_void_p(ws.data_ptr()), ws.numel(), oh, ol, _stream_handle(stream)))
+    _enqueue("ff_dot_ff_batched", x.device, stream, xh, xl, yh, yl, offsets.data_ptr(), nvec,
+             total, _cfg_ptr(cfg), ws.data_ptr(), ws.numel(), oh, ol)
     return out
 
 
@@ -586,11 +588,8 @@ def ff_sum_batched(x: torch.Tensor, offsets: torch.Tensor, cfg=None, out=None, w
     _check_ff(out, "out")
     ws = _workspace(ff_dot_batched_workspace_size(x.numel(), nvec, cfg), x.device, workspace)
     oh, ol = _planes(out)
-    with torch.cuda.device(x.device):
-        check("ff_sum_batched", lib.ff_sum_batched(
-            ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(offsets.data_ptr()), nvec, x.numel(),
-            _cfg_ptr(cfg), ctypes.c_void_p(ws.data_ptr()), ws.numel(), oh, ol,
-            _stream_handle(stream)))
+    _enqueue("ff_sum_batched", x.device, stream, x.data_ptr(), offsets.data_ptr(), nvec, x.numel(),
+             _cfg_ptr(cfg), ws.data_ptr(), ws.numel(), oh, ol)
     return out
 
 
@@ -608,17 +607,15 @@ def ff_sum_ff_batched(x: torch.Tensor, offsets: torch.Tensor, cfg=None, out=None
     ws = _workspace(ff_dot_batched_workspace_size(total, nvec, cfg), x.device, workspace)
     xh, xl = _planes(x)
     oh, ol = _planes(out)
-    with torch.cuda.device(x.device):
-        check("ff_sum_ff_batched", lib.ff_sum_ff_batched(
-            xh, xl, ctypes.c_void_p(offsets.data_ptr()), nvec, total, _cfg_ptr(cfg),
-            ctypes.c_void_p(ws.data_ptr()), ws.numel(), oh, ol, _stream_handle(stream)))
+    _enqueue("ff_sum_ff_batched", x.device, stream, xh, xl, offsets.data_ptr(), nvec, total,
+             _cfg_ptr(cfg), ws.data_ptr(), ws.numel(), oh, ol)
     return out
 
 
 # ------------------------------------------------------------ differentiation
 
 def _null():
-    return ctypes.c_void_p(0)
+    return 0
 
 
 def _check_matrix(A: torch.Tensor):
@@ -650,9 +647,7 @@ def ff_matvec(A: torch.Tensor, x: torch.Tensor, algo: int = MATVEC_FAST, out=Non
     Ah, Al = _planes(A)
     xh, xl = _planes(x)
     yh, yl = _planes(out)
-    with torch.cuda.device(A.device):
-        check("ff_matvec", lib.ff_matvec(M, N, Ah, Al, lda, xh, xl, yh, yl, int(algo),
-                                         _stream_handle(stream)))
+    _enqueue("ff_matvec", A.device, stream, M, N, Ah, Al, lda, xh, xl, yh, yl, int(algo))
     return out
 
 
@@ -692,10 +687,8 @@ def ff_matvec_backward(A: torch.Tensor, x: torch.Tensor, g: torch.Tensor, want_d
     gh, gl = _planes(g)
     dAh, dAl = _planes(dA) if want_dA else (_null(), _null())
     dxh, dxl = _planes(dx) if want_dx else (_null(), _null())
-    with torch.cuda.device(A.device):
-        check("ff_matvec_backward", lib.ff_matvec_backward(
-            M, N, Ah, Al, lda, xh, xl, gh, gl, dAh, dAl, N, dxh, dxl, int(algo),
-            ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream_handle(stream)))
+    _enqueue("ff_matvec_backward", A.device, stream, M, N, Ah, Al, lda, xh, xl, gh, gl, dAh, dAl,
+             N, dxh, dxl, int(algo), ws.data_ptr(), ws.numel())
     return dA, dx
 
 
@@ -708,9 +701,9 @@ def ff_dot_backward(g: torch.Tensor, x: torch.Tensor, y: torch.Tensor, want_dx: 
     _check_ff(g, "g")
     _check_ff(x, "x")
     _check_ff(y, "y")
-    if g[0].numel() != 1 or x.shape != y.shape:
+    if g.numel() != 2 or x.shape != y.shape:
         raise ValueError("g must hold one float-float value and x, y agree in shape")
-    n = x[0].numel()
+    n = x.numel() // 2
     dx = (ff_empty(x.shape[1:], device=x.device) if dx_out is None else dx_out) if want_dx else None
     dy = (ff_empty(y.shape[1:], device=y.device) if dy_out is None else dy_out) if want_dy else None
     for t, name in ((dx, "dx_out"), (dy, "dy_out")):
@@ -718,15 +711,12 @@ def ff_dot_backward(g: torch.Tensor, x: torch.Tensor, y: torch.Tensor, want_dx: 
             _check_ff(t, name)
             if t.shape != x.shape or t.device != x.device:
                 raise ValueError(f"{name} must have shape {tuple(x.shape)} on {x.device}")
-    g = g.reshape(2, 1).contiguous()
     gh, gl = _planes(g)
     xh, xl = _planes(x)
     yh, yl = _planes(y)
     dxh, dxl = _planes(dx) if want_dx else (_null(), _null())
     dyh, dyl = _planes(dy) if want_dy else (_null(), _null())
-    with torch.cuda.device(x.device):
-        check("ff_dot_backward", lib.ff_dot_backward(gh, gl, xh, xl, yh, yl, dxh, dxl, dyh, dyl, n,
-                                                     _stream_handle(stream)))
+    _enqueue("ff_dot_backward", x.device, stream, gh, gl, xh, xl, yh, yl, dxh, dxl, dyh, dyl, n)
     return dx, dy
 
 
@@ -741,6 +731,21 @@ def _ff_or_f32_planes(t: torch.Tensor, name: str):
         raise ValueError(f"{name}: float-float vector (2, n) or binary32 vector (n,) expected")
     hi, lo = _planes(t)
     return hi, lo, t.shape[1]
+
+
+@_on_stream
+def ff_gradient_value(g: torch.Tensor, out=None, stream=None) -> torch.Tensor:
+    """The incoming gradient of a float-float tensor as a float-float value:
+    elements whose two planes are equal (the per-plane derivative delivered by
+    ordinary torch operations) keep plane 0 and get a zero low word, others
+    are copied."""
+    _check_ff(g, "g")
+    out = ff_empty(g.shape[1:], device=g.device) if out is None else out
+    _check_ff(out, "out")
+    if out.shape != g.shape or out.device != g.device:
+        raise ValueError(f"ff_gradient_value: out must have shape {tuple(g.shape)} on {g.device}")
+    _enqueue("ff_gradient_value", g.device, stream, *_planes(g), *_planes(out), g.numel() // 2)
+    return out
 
 
 def ff_dot_batched_backward_workspace_size(total: int) -> int:
@@ -779,10 +784,8 @@ def ff_dot_batched_backward(g: torch.Tensor, x: torch.Tensor, y: torch.Tensor,
     gh, gl = _planes(g)
     dxh, dxl = _planes(dx) if want_dx else (_null(), _null())
     dyh, dyl = _planes(dy) if want_dy else (_null(), _null())
-    with torch.cuda.device(g.device):
-        check("ff_dot_batched_backward", lib.ff_dot_batched_backward(
-            gh, gl, ctypes.c_void_p(offsets.data_ptr()), nvec, n, xh, xl, yh, yl, dxh, dxl, dyh,
-            dyl, ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream_handle(stream)))
+    _enqueue("ff_dot_batched_backward", g.device, stream, gh, gl, offsets.data_ptr(), nvec, n, xh,
+             xl, yh, yl, dxh, dxl, dyh, dyl, ws.data_ptr(), ws.numel())
     return dx, dy
 
 
@@ -822,10 +825,8 @@ def ff_gemm(A: torch.Tensor, B: torch.Tensor, algo: int = GEMM_SLICED_I8, out=No
     Ah, Al = _planes(A)
     Bh, Bl = _planes(B)
     Ch, Cl = _planes(out)
-    with torch.cuda.device(A.device):
-        check("ff_gemm", lib.ff_gemm(M, N, K, Ah, Al, lda, Bh, Bl, ldb, Ch, Cl, ldc, int(algo),
-                                     ctypes.c_void_p(ws.data_ptr()), ws.numel(),
-                                     _stream_handle(stream)))
+    _enqueue("ff_gemm", A.device, stream, M, N, K, Ah, Al, lda, Bh, Bl, ldb, Ch, Cl, ldc,
+             int(algo), ws.data_ptr(), ws.numel())
     return out
 
 

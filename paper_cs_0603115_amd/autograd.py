@@ -22,19 +22,19 @@ from __future__ import annotations
 
 import torch
 
-from . import (MATVEC_FAST, ff_dot_backward, ff_dot_batched_backward, ff_dot_ff_batched,
-               ff_matvec, ff_matvec_backward)
+from . import (MATVEC_FAST, _dense, ff_dot_backward, ff_dot_batched_backward, ff_dot_ff_batched,
+               ff_gradient_value, ff_matvec, ff_matvec_backward)
 
 __all__ = ["FFMatVec", "FFDot", "FFDotBatched", "ff_one"]
 
 
 def _value_gradient(g: torch.Tensor) -> torch.Tensor:
-    """The incoming gradient as a float-float value: elements whose two
-    planes are equal (the per-plane derivative delivered by ordinary torch
-    operations) keep plane 0 and get a zero low word."""
-    g = g.contiguous()
-    lo = torch.where(g[0] == g[1], torch.zeros_like(g[1]), g[1])
-    return torch.stack((g[0], lo))
+    """The incoming gradient as a float-float value (ff_gradient_value);
+    gradients of other layouts (expanded ones, for example) are copied first."""
+    g = g.detach()
+    if not _dense(g.shape, g.stride(), 1):
+        g = g.contiguous()
+    return ff_gradient_value(g)
 
 
 def ff_one(device="cuda") -> torch.Tensor:
@@ -69,7 +69,9 @@ class FFDot(torch.autograd.Function):
     def forward(ctx, u, v):
         ctx.save_for_backward(u, v)
         n = u.shape[1]
-        offsets = torch.tensor([0, n], dtype=torch.int64, device=u.device)
+        # [0, n], made on the device: a copy from the host would wait for it
+        offsets = (torch.arange(0, n + 1, n, device=u.device) if n else
+                   torch.zeros(2, dtype=torch.int64, device=u.device))
         return ff_dot_ff_batched(u, v, offsets).reshape(2)
 
     @staticmethod

@@ -1,0 +1,68 @@
+"""The Python binding's descriptions of tensors against torch's own: which
+layouts count as float-float planes, and where the planes are (host tensors
+are enough: nothing is launched)."""
+import itertools
+
+import pytest
+import torch
+
+import paper_cs_0603115_amd as ff
+
+
+def _layouts():
+    """(2, ...) tensors of many shapes and strides, among them dimensions of
+    one element and of none, expanded, transposed and shifted ones."""
+    base = torch.arange(4096, dtype=torch.float32)
+    for dims in range(0, 4):
+        for shape in itertools.product((0, 1, 2, 3), repeat=dims):
+            for strides in itertools.product((0, 1, 2, 3, 6, 9), repeat=dims):
+                for plane in (0, 1, 7, 100):
+                    yield base.as_strided((2, *shape), (plane, *strides), 5)
+
+
+def test_plane_contiguity_is_torchs():
+    n = 0
+    for t in _layouts():
+        want = t[0].is_contiguous() and t[1].is_contiguous()
+        assert ff._dense(t.shape, t.stride(), 1) == want, (t.shape, t.stride())
+        n += 1
+    assert n > 10000
+
+
+def test_plane_addresses_are_torchs():
+    for t in itertools.islice(_layouts(), 0, None, 37):
+        if t.numel():
+            assert ff._planes(t) == (t[0].data_ptr(), t[1].data_ptr()), (t.shape, t.stride())
+
+
+@pytest.mark.parametrize("shape", [(), (0,), (1,), (5,), (1024,), (1025,), (3, 4), (0, 3), (2, 1, 5)])
+def test_ff_empty_and_zeros_share_a_layout(shape):
+    a, b = ff.ff_empty(shape, device="cpu"), ff.ff_zeros(shape, device="cpu")
+    assert a.shape == b.shape == (2, *shape) and a.stride() == b.stride()
+    assert a.stride(0) % ff.PLANE_ALIGN == 0 and not b.any()
+    a.fill_(1.0)                       # both planes lie within the storage
+    assert float(a.sum()) == a.numel()
+
+
+def test_stream_argument_by_position_and_keyword(monkeypatch):
+    # the wrapper finds the stream wherever the caller put it
+    seen = []
+
+    class Entered:
+        def __enter__(self):
+            seen.append("entered")
+
+        def __exit__(self, *exc):
+            return False
+
+    monkeypatch.setattr(ff, "_torch_stream", lambda s: s)
+    monkeypatch.setattr(torch.cuda, "stream", lambda s: Entered())
+
+    @ff._on_stream
+    def wrapper(a, out=None, stream=None, more=1):
+        return a, out, stream, more
+
+    assert wrapper(1) == (1, None, None, 1) and not seen
+    assert wrapper(1, None, "s") == (1, None, "s", 1) and len(seen) == 1
+    assert wrapper(1, stream="s", more=2) == (1, None, "s", 2) and len(seen) == 2
+    assert wrapper(1, 2, None, 3) == (1, 2, None, 3) and len(seen) == 2

@@ -289,3 +289,29 @@ def test_offsets_out_of_order_write_only_real_gradients(case):
     xh, xl = _planes(x)
     assert _candidates_hold(dx, gn, yh, yl).all()
     assert _candidates_hold(dy, gn, xh, xl).all()
+
+
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 5000])
+def test_gradient_value_selects_the_plane(n):
+    # equal planes -> (g, 0), other values copied; signed zeros, infinities and
+    # NaN (never equal to itself) among them, and gradients that autograd
+    # hands over expanded or with other strides
+    import paper_cs_0603115_amd as ff
+    from paper_cs_0603115_amd.autograd import _value_gradient
+
+    g = fi.random_ff(n, 9100 + n)
+    same = torch.arange(n) % 3 == 0
+    g[1] = torch.where(same, g[0], g[1])
+    special = torch.tensor([[0.0, -0.0, float("inf"), float("nan"), 0.0, float("-inf")],
+                            [-0.0, -0.0, float("inf"), float("nan"), 1.0, float("inf")]])
+    k = min(n, special.shape[1])
+    g[:, :k] = special[:, :k]
+    want = torch.stack([g[0], torch.where(g[0] == g[1], torch.zeros(n), g[1])])
+    got = ff.ff_gradient_value(g.cuda()).cpu()
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+    wide = torch.zeros(2, 2 * n, device="cuda")
+    wide[:, ::2] = g.cuda()
+    got = _value_gradient(wide[:, ::2]).cpu()          # planes not contiguous
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+    one = _value_gradient(torch.ones((), device="cuda").expand(2, n)).cpu()
+    assert torch.all(one[0] == 1) and torch.all(one[1] == 0)
