@@ -343,8 +343,8 @@ ff_status ff_dot_batched_autotune(const float *x, const float *y,
  * dimension lda >= N (elements); vectors are float-float planes.  Every term
  * is a Mul22 product (FMA TwoProd) and sums use Add22 (section 4.1).
  *
- * algo FF_MATVEC_FAST  -- tiled kernels: one workgroup per pair of rows
- *                         sharing each load of x (forward);
+ * algo FF_MATVEC_FAST  -- tiled kernels: 16 to 512 threads per row or pair of
+ *                         rows sharing each load of x (forward);
  *                         one fused pass over A writing dA and per-band
  *                         partial column sums of A^T g (backward), combined
  *                         in band order by a second small launch.
@@ -363,7 +363,9 @@ ff_status ff_matvec(int64_t M, int64_t N, const float *A_hi, const float *A_lo,
                     float *y_hi, float *y_lo, int32_t algo, void *stream);
 
 /* Workspace bytes of ff_matvec_backward (partial column sums of the fast
- * algorithm; 0 for the plain one). */
+ * algorithm, one row of N per band of 4 to 128 rows; 0 for the plain one).  A
+ * workspace that only holds the sums of longer bands, up to 128 rows, is
+ * accepted and used for those. */
 size_t ff_matvec_backward_workspace_size(int64_t M, int64_t N, int32_t algo);
 
 /* Backward pass of y = A x for an upstream gradient g = dL/dy (M values):

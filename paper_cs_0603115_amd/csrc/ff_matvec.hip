@@ -7,11 +7,11 @@
 // (16 bytes per element) with Mul22 (dA) + Mul22 + Add22 (dx) (~38 VALU).
 // Both are HBM-bound on gfx950 (ridge ~9.8 binary32 operations per byte).
 //
-// Fast forward: one workgroup per pair of rows; lane t takes float4 groups
-// t, t + BLOCK, ... of both rows (coalesced 1 KiB per wavefront load), each
-// load of x serving both, keeps four Add22 accumulators per row (one per
-// float4 component), then a wavefront butterfly and an in-order LDS combine
-// give y_i.  x is re-read from L2 by every pair of rows.
+// Fast forward: a group of 16 to 512 threads per row or pair of rows; lane t
+// takes the float4 groups t, t + threads, ... of its rows, each load of x
+// serving both, keeps four Add22 accumulators per row (one per float4
+// component), then a butterfly over the group's lanes and, for several
+// wavefronts, an in-order LDS combine give y_i.  x is re-read from L2.
 // Fast backward: the workgroup grid is (column tiles) x (row bands); a
 // thread owns four adjacent columns, walks the rows of its band, writes
 // dA_ij = Mul22(g_i, x_j) and accumulates Mul22(g_i, A_ij) per column; the
@@ -24,22 +24,37 @@
 
 namespace ffk {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Four consecutive words at any 4-byte alignment: gfx950's 16-byte global
+// accesses need no more, so rows of any length and any plane take them.
+typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 
-constexpr int kRowBlock = 256;
-// Backward band kernel: 128 threads (four columns each) by 128-row bands
-// measured fastest at 8192 x 8192 (175-176 us against 183-185 us for 256
-// threads by 64 rows; taller bands also halve the partial-sum traffic).
+// Backward band kernel: workgroups of 128 threads of four columns each, as many
+// across the columns as these need (16 to 128) and the rest over further
+// bands.  A band is so many rows that the matrix makes about 2^17 threads
+// (two wavefronts per SIMD), at most 128 rows: at 8192 x 8192 those measured
+// 175-176 us against 183-185 for 64, but they left 1024 x 1024 with sixteen
+// workgroups (70 us, 8.2 now).  At most 1024 bands, so that combining
+// their partial sums stays short.
 constexpr int kColBlock = 128;
 constexpr int64_t kBandRows = 128;
 
-// Fast forward for kRowsPerGroup rows at a time: the rows share each load
-// of x, and each lane issues the loads of kRowUnroll float4 groups (both
-// rows' planes and x) before any arithmetic.
-constexpr int kRowsPerGroup = 2;
+inline int64_t band_rows_of(int64_t M, int64_t N)
+{
+    if (N < 64)
+        return kBandRows;
+    int64_t rows = ffh::cdiv(M * N, int64_t(1) << 19);
+    rows = rows < 4 ? 4 : rows;
+    rows = rows < ffh::cdiv(M, 1024) ? ffh::cdiv(M, 1024) : rows;
+    rows = (rows + 1) & ~int64_t(1);
+    return rows < kBandRows ? rows : kBandRows;
+}
+
+// Fast forward: RT consecutive threads per group of R rows.  The rows share
+// each load of x, and each lane issues the loads of kRowUnroll float4 groups
+// (all rows' planes and x) before any arithmetic.
 constexpr int kRowUnroll = 2;
 
-template <int BLOCK, bool VEC>
+template <int BLOCK, int RT, int R>
 __global__ __launch_bounds__(BLOCK) void matvec_rows(int64_t M, int64_t N,
                                                      const float *__restrict__ Ah,
                                                      const float *__restrict__ Al, int64_t lda,
@@ -47,100 +62,110 @@ __global__ __launch_bounds__(BLOCK) void matvec_rows(int64_t M, int64_t N,
                                                      const float *__restrict__ xl,
                                                      float *__restrict__ yh, float *__restrict__ yl)
 {
-    constexpr int kWaves = BLOCK / 64;
-    constexpr int R = kRowsPerGroup, U = kRowUnroll;
-    __shared__ float2 part[R][kWaves];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int64_t r0 = static_cast<int64_t>(blockIdx.x) * R; r0 < M;
-         r0 += static_cast<int64_t>(gridDim.x) * R) {
-        // rows r0 .. r0 + R - 1; a row beyond M repeats row r0 (not stored)
-        const float *rh[R], *rl[R];
+    constexpr int kGroups = BLOCK / RT, kWaves = RT > 64 ? RT / 64 : 1, U = kRowUnroll;
+    const int t = threadIdx.x % RT;
+    const int64_t r0 = (static_cast<int64_t>(blockIdx.x) * kGroups + threadIdx.x / RT) * R;
+    // rows r0 .. r0 + R - 1; a row beyond M repeats the last one (not stored)
+    const float *rh[R], *rl[R];
 #pragma unroll
-        for (int q = 0; q < R; ++q) {
-            const int64_t r = (r0 + q < M) ? r0 + q : r0;
-            rh[q] = Ah + r * lda;
-            rl[q] = Al + r * lda;
-        }
-        float2 acc[R][4];
+    for (int q = 0; q < R; ++q) {
+        const int64_t r = r0 + q < M ? r0 + q : M - 1;
+        rh[q] = Ah + r * lda;
+        rl[q] = Al + r * lda;
+    }
+    float2 acc[R][4];
 #pragma unroll
-        for (int q = 0; q < R; ++q)
+    for (int q = 0; q < R; ++q)
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                acc[q][k] = make_float2(0.0f, 0.0f);
-        auto add_term = [&](int q, int k, float ah, float al, float bh, float bl) {
-            float ph, pl;
-            ffd::mul22<false>(ah, al, bh, bl, ph, pl);
-            ffd::add22(acc[q][k].x, acc[q][k].y, ph, pl, acc[q][k].x, acc[q][k].y);
-        };
-        int64_t j_scalar = tid;
-        if (VEC) {
-            const int64_t ng = N >> 2;
-            const f32x4 *xh4 = reinterpret_cast<const f32x4 *>(xh);
-            const f32x4 *xl4 = reinterpret_cast<const f32x4 *>(xl);
-            int64_t g = tid;
-            for (; g + (U - 1) * BLOCK < ng; g += U * BLOCK) {
-                f32x4 bh[U], bl[U], ah[R][U], al[R][U];
+        for (int k = 0; k < 4; ++k)
+            acc[q][k] = make_float2(0.0f, 0.0f);
+    auto add_term = [&](int q, int k, float ah, float al, float bh, float bl) {
+        float ph, pl;
+        ffd::mul22<false>(ah, al, bh, bl, ph, pl);
+        ffd::add22(acc[q][k].x, acc[q][k].y, ph, pl, acc[q][k].x, acc[q][k].y);
+    };
+    const int64_t ng = N >> 2;
+    const f32x4 *xh4 = reinterpret_cast<const f32x4 *>(xh);
+    const f32x4 *xl4 = reinterpret_cast<const f32x4 *>(xl);
+    int64_t g = t;
+    for (; g + (U - 1) * RT < ng; g += U * RT) {
+        f32x4 bh[U], bl[U], ah[R][U], al[R][U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    bh[u] = xh4[g + u * BLOCK];
-                    bl[u] = xl4[g + u * BLOCK];
+        for (int u = 0; u < U; ++u) {
+            bh[u] = xh4[g + u * RT];
+            bl[u] = xl4[g + u * RT];
 #pragma unroll
-                    for (int q = 0; q < R; ++q) {
-                        ah[q][u] = __builtin_nontemporal_load(
-                            reinterpret_cast<const f32x4 *>(rh[q]) + g + u * BLOCK);
-                        al[q][u] = __builtin_nontemporal_load(
-                            reinterpret_cast<const f32x4 *>(rl[q]) + g + u * BLOCK);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int q = 0; q < R; ++q)
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            add_term(q, k, ah[q][u][k], al[q][u][k], bh[u][k], bl[u][k]);
+            for (int q = 0; q < R; ++q) {
+                ah[q][u] = __builtin_nontemporal_load(
+                    reinterpret_cast<const f32x4 *>(rh[q]) + g + u * RT);
+                al[q][u] = __builtin_nontemporal_load(
+                    reinterpret_cast<const f32x4 *>(rl[q]) + g + u * RT);
             }
-            for (; g < ng; g += BLOCK) {
-                const f32x4 bh = xh4[g], bl = xl4[g];
-#pragma unroll
-                for (int q = 0; q < R; ++q) {
-                    const f32x4 ah = __builtin_nontemporal_load(
-                        reinterpret_cast<const f32x4 *>(rh[q]) + g);
-                    const f32x4 al = __builtin_nontemporal_load(
-                        reinterpret_cast<const f32x4 *>(rl[q]) + g);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        add_term(q, k, ah[k], al[k], bh[k], bl[k]);
-                }
-            }
-            j_scalar = 4 * ng + tid;
         }
-        for (int64_t j = j_scalar; j < N; j += BLOCK) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int q = 0; q < R; ++q)
-                add_term(q, 0, rh[q][j], rl[q][j], xh[j], xl[j]);
-        }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    add_term(q, k, ah[q][u][k], al[q][u][k], bh[u][k], bl[u][k]);
+    }
+    for (; g < ng; g += RT) {
+        const f32x4 bh = xh4[g], bl = xl4[g];
 #pragma unroll
         for (int q = 0; q < R; ++q) {
-            float h = acc[q][0].x, l = acc[q][0].y, h2 = acc[q][2].x, l2 = acc[q][2].y;
-            ffd::add22(h, l, acc[q][1].x, acc[q][1].y, h, l);
-            ffd::add22(h2, l2, acc[q][3].x, acc[q][3].y, h2, l2);
-            ffd::add22(h, l, h2, l2, h, l);
-            ffd::wave_allreduce_add22(h, l);
-            if (lane == 0)
-                part[q][wave] = make_float2(h, l);
-        }
-        __syncthreads();
-        if (tid < R && r0 + tid < M) {
-            float th = part[tid][0].x, tl = part[tid][0].y;
+            const f32x4 ah =
+                __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(rh[q]) + g);
+            const f32x4 al =
+                __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(rl[q]) + g);
 #pragma unroll
-            for (int k = 1; k < kWaves; ++k)
-                ffd::add22(th, tl, part[tid][k].x, part[tid][k].y, th, tl);
-            yh[r0 + tid] = th;
-            yl[r0 + tid] = tl;
+            for (int k = 0; k < 4; ++k)
+                add_term(q, k, ah[k], al[k], bh[k], bl[k]);
         }
-        __syncthreads();
     }
+    if (4 * ng + t < N) {
+        const int64_t j = 4 * ng + t;
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+            add_term(q, 0, rh[q][j], rl[q][j], xh[j], xl[j]);
+    }
+    float h[R], l[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        float h2 = acc[q][2].x, l2 = acc[q][2].y;
+        h[q] = acc[q][0].x;
+        l[q] = acc[q][0].y;
+        ffd::add22(h[q], l[q], acc[q][1].x, acc[q][1].y, h[q], l[q]);
+        ffd::add22(h2, l2, acc[q][3].x, acc[q][3].y, h2, l2);
+        ffd::add22(h[q], l[q], h2, l2, h[q], l[q]);
+#pragma unroll
+        for (int m = (RT < 64 ? RT : 64) / 2; m >= 1; m >>= 1) {
+            const float oh = __shfl_xor(h[q], m, 64), ol = __shfl_xor(l[q], m, 64);
+            ffd::add22(h[q], l[q], oh, ol, h[q], l[q]);
+        }
+    }
+    if constexpr (kWaves > 1) {
+        static_assert(RT == BLOCK, "one group of several wavefronts");
+        __shared__ float2 part[R][kWaves];
+        if ((t & 63) == 0)
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+                part[q][t >> 6] = make_float2(h[q], l[q]);
+        __syncthreads();
+        if (t == 0)
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+#pragma unroll
+                for (int k = 1; k < kWaves; ++k)
+                    ffd::add22(h[q], l[q], part[q][k].x, part[q][k].y, h[q], l[q]);
+    }
+    if (t == 0)
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+            if (r0 + q < M) {
+                yh[r0 + q] = h[q];
+                yl[r0 + q] = l[q];
+            }
 }
 
 // Plain forward: one thread per row, terms added in column order.
@@ -164,19 +189,28 @@ __global__ __launch_bounds__(256) void matvec_plain(int64_t M, int64_t N,
     yl[r] = l;
 }
 
-// Fused backward over one row band: thread owns COLS adjacent columns.
-template <int BLOCK, int COLS, bool WANT_DA, bool WANT_DX>
+// Fused backward over row bands: thread owns COLS adjacent columns of one
+// band, ROWS rows' loads issued before any arithmetic; 2^col_shift threads of
+// the workgroup span the columns.
+template <int BLOCK, int COLS, bool WANT_DA, bool WANT_DX, int ROWS>
 __global__ __launch_bounds__(BLOCK) void matvec_bwd_band(
     int64_t M, int64_t N, const float *__restrict__ Ah, const float *__restrict__ Al, int64_t lda,
     const float *__restrict__ xh, const float *__restrict__ xl, const float *__restrict__ gh,
     const float *__restrict__ gl, float *__restrict__ dAh, float *__restrict__ dAl, int64_t ldda,
-    float2 *__restrict__ part)
+    float2 *__restrict__ part, int band_rows, int col_shift)
 {
-    const int64_t c0 = (static_cast<int64_t>(blockIdx.x) * BLOCK + threadIdx.x) * COLS;
-    if (c0 >= N)
+    const int across = 1 << col_shift;
+    int64_t c0 = ((static_cast<int64_t>(blockIdx.x) << col_shift) + (threadIdx.x & (across - 1))) *
+                 COLS;
+    const int64_t band = (static_cast<int64_t>(blockIdx.y) * BLOCK + threadIdx.x) >> col_shift;
+    const int64_t i0 = band * band_rows;
+    if (c0 >= N || i0 >= M)
         return;
-    const int64_t i0 = static_cast<int64_t>(blockIdx.y) * kBandRows;
-    const int64_t i1 = (i0 + kBandRows < M) ? i0 + kBandRows : M;
+    // the last thread's columns end with the row: those it shares with the
+    // thread before are computed twice, to the same bits
+    if (c0 + COLS > N)
+        c0 = N - COLS;
+    const int64_t i1 = (i0 + band_rows < M) ? i0 + band_rows : M;
     float x_h[COLS], x_l[COLS];
     float2 acc[COLS];
 #pragma unroll
@@ -187,8 +221,6 @@ __global__ __launch_bounds__(BLOCK) void matvec_bwd_band(
             x_l[k] = xl[c0 + k];
         }
     }
-    // rows in pairs: both rows' loads are issued before any arithmetic
-    constexpr int kRowPair = 2;
     auto row = [&](int64_t i, const float (&a_h)[COLS], const float (&a_l)[COLS]) {
         const float g_h = gh[i], g_l = gl[i];
         if (WANT_DA) {
@@ -232,13 +264,13 @@ __global__ __launch_bounds__(BLOCK) void matvec_bwd_band(
         }
     };
     int64_t i = i0;
-    for (; i + kRowPair <= i1; i += kRowPair) {
-        float a_h[kRowPair][COLS], a_l[kRowPair][COLS];
+    for (; i + ROWS <= i1; i += ROWS) {
+        float a_h[ROWS][COLS], a_l[ROWS][COLS];
 #pragma unroll
-        for (int p = 0; p < kRowPair; ++p)
+        for (int p = 0; p < ROWS; ++p)
             load_row(i + p, a_h[p], a_l[p]);
 #pragma unroll
-        for (int p = 0; p < kRowPair; ++p)
+        for (int p = 0; p < ROWS; ++p)
             row(i + p, a_h[p], a_l[p]);
     }
     for (; i < i1; ++i) {
@@ -249,37 +281,36 @@ __global__ __launch_bounds__(BLOCK) void matvec_bwd_band(
     if (WANT_DX) {
 #pragma unroll
         for (int k = 0; k < COLS; ++k)
-            part[static_cast<int64_t>(blockIdx.y) * N + c0 + k] = acc[k];
+            part[band * N + c0 + k] = acc[k];
     }
 }
 
-// dx_j = partial sums of column j added in band order.
-// dx_j = sum over bands of the per-band partials, for 64 columns per
-// workgroup: eight groups of threads take bands g, g + 8, ... (coalesced
-// 512-byte rows of partials, several loads in flight per thread), then the
-// eight group sums are added in a fixed tree through LDS.
-constexpr int kCombineGroups = 8;
-
-__global__ __launch_bounds__(64 * kCombineGroups) void matvec_bwd_combine(
+// dx_j = sum over bands of the per-band partials, for COLS columns per
+// workgroup: GROUPS groups of threads take bands g, g + GROUPS, ... (rows of
+// partials of COLS columns, several loads in flight per thread), then the
+// group sums are added in a fixed tree through LDS.  64 columns by 8 groups
+// for wide matrices; 16 by 64 where there are few columns and more bands.
+template <int COLS, int GROUPS>
+__global__ __launch_bounds__(COLS * GROUPS) void matvec_bwd_combine(
     int64_t N, int64_t nbands, const float2 *__restrict__ part, float *__restrict__ dxh,
     float *__restrict__ dxl)
 {
-    __shared__ float2 sums[kCombineGroups][64];
-    const int col = threadIdx.x & 63, grp = threadIdx.x >> 6;
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * 64 + col;
+    __shared__ float2 sums[GROUPS][COLS];
+    const int col = threadIdx.x % COLS, grp = threadIdx.x / COLS;
+    const int64_t j = static_cast<int64_t>(blockIdx.x) * COLS + col;
     float h = 0.0f, l = 0.0f;
     if (j < N) {
         int64_t b = grp;
-        for (; b + 3 * kCombineGroups < nbands; b += 4 * kCombineGroups) {
+        for (; b + 3 * GROUPS < nbands; b += 4 * GROUPS) {
             float2 p[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                p[u] = part[(b + u * kCombineGroups) * N + j];
+                p[u] = part[(b + u * GROUPS) * N + j];
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 ffd::add22(h, l, p[u].x, p[u].y, h, l);
         }
-        for (; b < nbands; b += kCombineGroups) {
+        for (; b < nbands; b += GROUPS) {
             const float2 p = part[b * N + j];
             ffd::add22(h, l, p.x, p.y, h, l);
         }
@@ -287,7 +318,7 @@ __global__ __launch_bounds__(64 * kCombineGroups) void matvec_bwd_combine(
     sums[grp][col] = make_float2(h, l);
     __syncthreads();
 #pragma unroll
-    for (int w = kCombineGroups / 2; w >= 1; w >>= 1) {
+    for (int w = GROUPS / 2; w >= 1; w >>= 1) {
         if (grp < w) {
             const float2 a = sums[grp][col], c = sums[grp + w][col];
             float rh, rl;
@@ -591,7 +622,11 @@ bool all_aligned(std::initializer_list<const void *> ptrs, uintptr_t bytes)
     return true;
 }
 
-int64_t nbands_of(int64_t M) { return (M + kBandRows - 1) / kBandRows; }
+// Partial sums of dx: one row of N per band.
+size_t band_bytes(int64_t M, int64_t N, int64_t band_rows)
+{
+    return static_cast<size_t>(ffh::cdiv(M, band_rows)) * static_cast<size_t>(N) * sizeof(float2);
+}
 
 } // namespace ffk
 
@@ -620,17 +655,27 @@ ff_status ff_matvec(int64_t M, int64_t N, const float *A_hi, const float *A_lo, 
         hipLaunchKernelGGL(matvec_plain, dim3(static_cast<unsigned>(ffh::cdiv(M, 256))), dim3(256),
                            0, st, M, N, A_hi, A_lo, lda, x_hi, x_lo, y_hi, y_lo);
     } else {
-        const bool vec = all_aligned({A_hi, A_lo, x_hi, x_lo}, 16) && lda % 4 == 0;
-        if (vec)
-            hipLaunchKernelGGL((matvec_rows<kRowBlock, true>),
-                               dim3(static_cast<unsigned>(ffh::cdiv(M, kRowsPerGroup))),
-                               dim3(kRowBlock), 0, st, M, N, A_hi, A_lo, lda, x_hi, x_lo, y_hi,
-                               y_lo);
+        auto launch = [&](auto kernel, int block, int rows) {
+            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(ffh::cdiv(M, rows))), dim3(block),
+                               0, st, M, N, A_hi, A_lo, lda, x_hi, x_lo, y_hi, y_lo);
+        };
+        // As many threads per row as it feeds with a few float4 groups each, one
+        // row per group of threads, two where there are rows enough for 512
+        // workgroups.  us, chosen against 256 threads by two rows: 16384 x 64
+        // 3.4 / 18.0, 16384 x 512 11.9 / 21.8 (16 threads); 1024 x 1024 3.8 /
+        // 4.2, 16384 x 1000 24.1 / 27.8 (64); 300 x 5000 5.9 / 7.1, 64 x 16384
+        // 7.4 / 13.5 (512); 1000 x 1531 5.2-5.7 / 5.3-5.7 (256, one row); and
+        // for two rows against one 1000 x 16384 23.9 / 27.3, 8192 x 8192 81 / 90.
+        if (N <= 128 || (N <= 512 && M >= 4096))
+            launch(matvec_rows<256, 16, 1>, 256, 16);
+        else if (N <= 1024 || (N <= 2048 && M >= 2048))
+            launch(matvec_rows<256, 64, 1>, 256, 4);
+        else if (M < 768)
+            launch(matvec_rows<512, 512, 1>, 512, 1);
+        else if (M < 1536 && N <= 8192)
+            launch(matvec_rows<256, 256, 1>, 256, 1);
         else
-            hipLaunchKernelGGL((matvec_rows<kRowBlock, false>),
-                               dim3(static_cast<unsigned>(ffh::cdiv(M, kRowsPerGroup))),
-                               dim3(kRowBlock), 0, st, M, N, A_hi, A_lo, lda, x_hi, x_lo, y_hi,
-                               y_lo);
+            launch(matvec_rows<256, 256, 2>, 256, 2);
     }
     return ffh::launch_status();
 }
@@ -639,7 +684,7 @@ size_t ff_matvec_backward_workspace_size(int64_t M, int64_t N, int32_t algo)
 {
     if (M < 0 || N < 0 || algo != FF_MATVEC_FAST)
         return 0;
-    return static_cast<size_t>(nbands_of(M)) * static_cast<size_t>(N) * sizeof(float2);
+    return band_bytes(M, N, band_rows_of(M, N));
 }
 
 ff_status ff_matvec_backward(int64_t M, int64_t N, const float *A_hi, const float *A_lo,
@@ -680,45 +725,67 @@ ff_status ff_matvec_backward(int64_t M, int64_t N, const float *A_hi, const floa
                                dim3(256), 0, st, M, N, A_hi, A_lo, lda, g_hi, g_lo, dx_hi, dx_lo);
         return ffh::launch_status();
     }
-    const int64_t nbands = nbands_of(M);
+    int64_t band_rows = band_rows_of(M, N);
     if (want_dx && M > 0) {
         if (!ws)
             return FF_ERR_NULL;
-        if (ws_bytes < ff_matvec_backward_workspace_size(M, N, algo))
+        // a workspace that only holds longer bands' sums gets longer bands
+        while (band_rows < kBandRows && ws_bytes < band_bytes(M, N, band_rows))
+            band_rows = 2 * band_rows < kBandRows ? 2 * band_rows : kBandRows;
+        if (ws_bytes < band_bytes(M, N, band_rows))
             return FF_ERR_WORKSPACE;
         if (!ffh::aligned(ws, 16))
             return FF_ERR_ALIGN;
     }
+    const int64_t nbands = ffh::cdiv(M, band_rows);
     float2 *part = static_cast<float2 *>(ws);
     if (M > 0) {
-        const bool vec = N % 4 == 0 && lda % 4 == 0 && (!want_da || ldda % 4 == 0) &&
-                         all_aligned({A_hi, A_lo, dA_hi, dA_lo}, 16);
-        const int cols = vec ? 4 : 1;
-        const dim3 grid(static_cast<unsigned>(ffh::cdiv(N, int64_t(kColBlock) * cols)),
-                        static_cast<unsigned>(nbands));
-#define FF_BWD_LAUNCH(C, DA, DX)                                                               \
-    hipLaunchKernelGGL((matvec_bwd_band<kColBlock, C, DA, DX>), grid, dim3(kColBlock), 0, st, M, \
-                       N, A_hi, A_lo, lda, x_hi, x_lo, g_hi, g_lo, dA_hi, dA_lo, ldda, part)
-        if (vec) {
+        const int cols = N >= 4 ? 4 : 1;
+        int col_shift = 4;
+        while ((1 << col_shift) < kColBlock && (int64_t(cols) << col_shift) < N)
+            ++col_shift;
+        const int64_t across = int64_t(cols) << col_shift, stacked = kColBlock >> col_shift;
+        const dim3 grid(static_cast<unsigned>(ffh::cdiv(N, across)),
+                        static_cast<unsigned>(ffh::cdiv(nbands, stacked)));
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(kColBlock), 0, st, M, N, A_hi, A_lo, lda, x_hi,
+                               x_lo, g_hi, g_lo, dA_hi, dA_lo, ldda, part,
+                               static_cast<int>(band_rows), col_shift);
+        };
+        // four rows in flight where bands are short and wavefronts few, two
+        // in long bands (196 us with four against 184 at 8192 x 8192)
+        const bool four = band_rows < 64;
+        if (cols == 4 && four) {
             if (want_da && want_dx)
-                FF_BWD_LAUNCH(4, true, true);
+                launch(matvec_bwd_band<kColBlock, 4, true, true, 4>);
             else if (want_da)
-                FF_BWD_LAUNCH(4, true, false);
+                launch(matvec_bwd_band<kColBlock, 4, true, false, 4>);
             else
-                FF_BWD_LAUNCH(4, false, true);
+                launch(matvec_bwd_band<kColBlock, 4, false, true, 4>);
+        } else if (cols == 4) {
+            if (want_da && want_dx)
+                launch(matvec_bwd_band<kColBlock, 4, true, true, 2>);
+            else if (want_da)
+                launch(matvec_bwd_band<kColBlock, 4, true, false, 2>);
+            else
+                launch(matvec_bwd_band<kColBlock, 4, false, true, 2>);
         } else {
             if (want_da && want_dx)
-                FF_BWD_LAUNCH(1, true, true);
+                launch(matvec_bwd_band<kColBlock, 1, true, true, 2>);
             else if (want_da)
-                FF_BWD_LAUNCH(1, true, false);
+                launch(matvec_bwd_band<kColBlock, 1, true, false, 2>);
             else
-                FF_BWD_LAUNCH(1, false, true);
+                launch(matvec_bwd_band<kColBlock, 1, false, true, 2>);
         }
-#undef FF_BWD_LAUNCH
     }
-    if (want_dx)
-        hipLaunchKernelGGL(matvec_bwd_combine, dim3(static_cast<unsigned>(ffh::cdiv(N, 64))),
-                           dim3(64 * kCombineGroups), 0, st, N, nbands, part, dx_hi, dx_lo);
+    if (want_dx && N >= 4096)
+        hipLaunchKernelGGL((matvec_bwd_combine<64, 8>),
+                           dim3(static_cast<unsigned>(ffh::cdiv(N, 64))), dim3(64 * 8), 0, st, N,
+                           nbands, part, dx_hi, dx_lo);
+    else if (want_dx)
+        hipLaunchKernelGGL((matvec_bwd_combine<16, 64>),
+                           dim3(static_cast<unsigned>(ffh::cdiv(N, 16))), dim3(16 * 64), 0, st, N,
+                           nbands, part, dx_hi, dx_lo);
     return ffh::launch_status();
 }
 

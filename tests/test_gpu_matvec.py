@@ -346,3 +346,68 @@ def test_full_size_8192_matvec_and_backward():
         assert abs(fd - an) <= 1e-9 * max(1.0, abs(an)), (i, j, fd, an)
     del A, x, y, loss
     torch.cuda.empty_cache()
+
+
+# one shape on each side of every line between the forward's forms and the
+# backward's widths, with row lengths of every remainder mod 4
+EDGE_SHAPES = [(5, 3), (33, 63), (33, 65), (40, 128), (40, 130), (4100, 511), (4096, 513), (90, 1023),
+               (70, 1025), (2048, 1027), (700, 2050), (767, 2049), (768, 2051), (1536, 2049),
+               (20, 8193)]
+
+
+@pytest.mark.parametrize("M,N", EDGE_SHAPES)
+@pytest.mark.parametrize("shift", [0, 1])
+def test_forward_and_backward_at_the_edges_of_their_forms(M, N, shift):
+    # shift 1: planes and rows start 4 bytes past 16-byte alignment, rows are
+    # padded, and the words around the outputs stay untouched
+    ff = _ff()
+    _announce(f"[gpu] matvec edges {M}x{N} shift {shift}")
+    A = fi.gaussian_ff((M, N), 6200 + M)
+    x, g = fi.gaussian_ff((N,), 6201 + N), fi.gaussian_ff((M,), 6202 + M)
+    wide = torch.zeros(2, M, N + 5 * shift, device="cuda")
+    Ad = wide[:, :, shift:N + shift]
+    Ad.copy_(A)
+    xd = torch.zeros(2, N + shift, device="cuda")[:, shift:]
+    xd.copy_(x)
+    gd = g.cuda()
+    y = ff.ff_matvec(Ad, xd)
+    rows = np.unique(np.linspace(0, M - 1, 24).astype(int))
+    check_rows_exact(A[:, rows], x, y[:, torch.from_numpy(rows).cuda()], f"y {M}x{N}")
+    buf = torch.full((2, M * N + 2 * shift), 7.0, device="cuda")
+    dA = buf[:, shift:M * N + shift].unflatten(1, (M, N))
+    _, dx = ff.ff_matvec_backward(Ad, xd, gd, dA_out=dA)
+    torch.cuda.synchronize()
+    if shift:
+        assert torch.all(buf[:, 0] == 7.0) and torch.all(buf[:, -1] == 7.0)
+    gn, xn = g.numpy(), x.numpy()
+    n = M * N
+    wh, wl = oracle.elementwise("mul", np.repeat(gn[0], N), np.repeat(gn[1], N),
+                                np.tile(xn[0], M), np.tile(xn[1], M))
+    got = dA.cpu().numpy().reshape(2, n)
+    assert same_bits(got[0], wh) and same_bits(got[1], wl)
+    cols = np.unique(np.concatenate([np.arange(min(N, 6)), np.linspace(0, N - 1, 12).astype(int),
+                                     np.arange(max(0, N - 6), N)]))
+    check_cols_exact(A, g, dx, f"dx {M}x{N}", cols=cols)
+    _, dx_only = ff.ff_matvec_backward(Ad, xd, gd, want_dA=False)
+    assert torch.equal(dx_only.view(torch.int32), dx.view(torch.int32))
+
+
+def test_backward_takes_a_workspace_of_longer_bands():
+    # a workspace that only holds the sums of 128-row bands is accepted; one
+    # byte less is not
+    ff = _ff()
+    M, N = 1000, 640
+    A, x = fi.gaussian_ff((M, N), 6301).cuda(), fi.gaussian_ff((N,), 6302).cuda()
+    g = fi.gaussian_ff((M,), 6303).cuda()
+    longest = 8 * N * 8                       # eight bands of 128 rows
+    assert ff.ff_matvec_backward_workspace_size(M, N) > longest
+    ws = torch.empty(longest, dtype=torch.uint8, device="cuda")
+    dx = ff.ff_empty((N,))
+    call = lambda nbytes: ff.lib.ff_matvec_backward(  # noqa: E731
+        M, N, A[0].data_ptr(), A[1].data_ptr(), N, x[0].data_ptr(), x[1].data_ptr(),
+        g[0].data_ptr(), g[1].data_ptr(), None, None, N, dx[0].data_ptr(), dx[1].data_ptr(), 0,
+        ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream)
+    assert call(longest - 1) == 4             # FF_ERR_WORKSPACE
+    assert call(longest) == 0
+    torch.cuda.synchronize()
+    check_cols_exact(A, g, dx, "long bands", cols=np.arange(0, N, 37))
