@@ -38,6 +38,7 @@
 //
 // Four launches per chunk of K: partial maxima, residue planes, products,
 // reconstruction (the first two once per call).
+
 #include <type_traits>
 
 #include "ff_device.h"
@@ -128,10 +129,17 @@ constexpr int kP = 54;                // fixed-point bits: |X| <= 2^kP
 constexpr int64_t kMaxKChunk = 16384; // sums of this many products stay below P / 2
 constexpr int kBlk = 32;              // rows (or columns) of one matrix-core operand
 constexpr int kFragBytes = 1024;      // one operand: 32 rows by 32 bytes of K
+constexpr int kXcds = 8;              // accelerator dies, one L2 each; workgroup b runs on die b % 8
 constexpr int kStageFrags = 2;        // operands per block of rows and stage
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes of memory at any 4-byte alignment: the hardware loads and stores
+// them in one instruction.  Every row of the operands is read this way; word
+// by word, rows of odd lengths took 6.2 us (maxima) and 28.6 us (residues) at
+// 1000 x 1531 x 2047, now 6.3 and 23.2.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
@@ -166,7 +174,6 @@ __device__ __forceinline__ int exponent_bound(uint32_t ub)
 constexpr int kRowSegment = 4096;
 constexpr int kColBand = 128;
 
-template <bool VEC>
 __global__ __launch_bounds__(256) void absmax_partials(
     int64_t M, int64_t N, int64_t K, const float *__restrict__ Ah, int64_t lda,
     const float *__restrict__ Bh, int64_t ldb, int64_t row_groups, int64_t col_groups,
@@ -184,22 +191,24 @@ __global__ __launch_bounds__(256) void absmax_partials(
         const int64_t k1 = (k0 + kRowSegment < K) ? k0 + kRowSegment : K;
         const float *a = Ah + row * lda;
         uint32_t m = 0;
-        int64_t k = k0;
-        if (VEC) {
-            const int64_t kv = k0 + ((k1 - k0) & ~int64_t(255));   // whole 256-entry steps
-#pragma unroll 8
-            for (k = k0 + 4 * lane; k < kv; k += 256) {
-                const float4 v = *reinterpret_cast<const float4 *>(a + k);
-                m = max(m, max(max(__float_as_uint(v.x) & 0x7fffffffu,
-                                   __float_as_uint(v.y) & 0x7fffffffu),
-                               max(__float_as_uint(v.z) & 0x7fffffffu,
-                                   __float_as_uint(v.w) & 0x7fffffffu)));
+        if (k1 - k0 >= 4) {
+            // entries past the end repeat the last four, so that eight loads
+            // are in flight whatever the length
+            for (int64_t k = k0 + 4 * lane; k - 4 * lane < k1; k += 8 * 256) {
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    const int64_t at = k + 256 * s < k1 - 4 ? k + 256 * s : k1 - 4;
+                    const f32x4 v = *reinterpret_cast<const f32x4u *>(a + at);
+                    m = max(m, max(max(__float_as_uint(v[0]) & 0x7fffffffu,
+                                       __float_as_uint(v[1]) & 0x7fffffffu),
+                                   max(__float_as_uint(v[2]) & 0x7fffffffu,
+                                       __float_as_uint(v[3]) & 0x7fffffffu)));
+                }
             }
-            k = kv;
+        } else {
+            for (int64_t k = k0; k < k1; ++k)
+                m = max(m, __float_as_uint(a[k]) & 0x7fffffffu);
         }
-#pragma unroll 8
-        for (k += lane; k < k1; k += 64)
-            m = max(m, __float_as_uint(a[k]) & 0x7fffffffu);
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1)
             m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), off, 64)));
@@ -211,41 +220,30 @@ __global__ __launch_bounds__(256) void absmax_partials(
     b -= rgrid;
     const int64_t band = b / col_groups, j0 = b % col_groups * 64;
     uint32_t m[4] = {0, 0, 0, 0};
-    constexpr int kGroups = VEC ? 16 : 4, kRows = kColBand / kGroups;
+    constexpr int kGroups = 16, kRows = kColBand / kGroups;
     __shared__ uint32_t part[kGroups][64];
     const int group = threadIdx.x / (256 / kGroups);
     const int64_t k0 = band * kColBand + group * kRows;
-    if constexpr (VEC) {
-        const int64_t j = j0 + 4 * (threadIdx.x & 15);
-        if (j + 4 <= N) {
-#pragma unroll
-            for (int k = 0; k < kRows; ++k) {
-                const int64_t row = k0 + k < K ? k0 + k : K - 1;
-                const float4 v = *reinterpret_cast<const float4 *>(Bh + row * ldb + j);
-                m[0] = max(m[0], __float_as_uint(v.x) & 0x7fffffffu);
-                m[1] = max(m[1], __float_as_uint(v.y) & 0x7fffffffu);
-                m[2] = max(m[2], __float_as_uint(v.z) & 0x7fffffffu);
-                m[3] = max(m[3], __float_as_uint(v.w) & 0x7fffffffu);
-            }
-        } else {
-            for (int u = 0; u < 4 && j + u < N; ++u)
-                for (int k = 0; k < kRows; ++k) {
-                    const int64_t row = k0 + k < K ? k0 + k : K - 1;
-                    m[u] = max(m[u], __float_as_uint(Bh[row * ldb + j + u]) & 0x7fffffffu);
-                }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            part[group][4 * (threadIdx.x & 15) + u] = m[u];
-    } else {
-        const int64_t j = j0 + lane < N ? j0 + lane : N - 1;
+    const int64_t j = j0 + 4 * (threadIdx.x & 15);
+    if (j + 4 <= N) {
 #pragma unroll
         for (int k = 0; k < kRows; ++k) {
             const int64_t row = k0 + k < K ? k0 + k : K - 1;
-            m[k & 3] = max(m[k & 3], __float_as_uint(Bh[row * ldb + j]) & 0x7fffffffu);
+            const f32x4 v = *reinterpret_cast<const f32x4u *>(Bh + row * ldb + j);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                m[u] = max(m[u], __float_as_uint(v[u]) & 0x7fffffffu);
         }
-        part[group][lane] = max(max(m[0], m[1]), max(m[2], m[3]));
+    } else {
+        for (int u = 0; u < 4 && j + u < N; ++u)
+            for (int k = 0; k < kRows; ++k) {
+                const int64_t row = k0 + k < K ? k0 + k : K - 1;
+                m[u] = max(m[u], __float_as_uint(Bh[row * ldb + j + u]) & 0x7fffffffu);
+            }
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        part[group][4 * (threadIdx.x & 15) + u] = m[u];
     __syncthreads();
     if (wave == 0 && j0 + lane < N) {
         uint32_t r = 0;
@@ -289,7 +287,7 @@ constexpr int kPitchA = kResidueSpan + 4, kPitchB = kBlk + 16;
 constexpr int kStaged = kResidueSpan * kPitchB > kBlk * kPitchA ? kResidueSpan * kPitchB
                                                                : kBlk * kPitchA;
 
-template <class Dg, bool VEC>
+template <class Dg>
 __global__ __launch_bounds__(256, 4) void residue_planes(
     int64_t M, int64_t N, int64_t K, const float *__restrict__ Ah, const float *__restrict__ Al,
     int64_t lda, const float *__restrict__ Bh, const float *__restrict__ Bl, int64_t ldb, int nRB,
@@ -299,7 +297,7 @@ __global__ __launch_bounds__(256, 4) void residue_planes(
     int64_t plane_b)
 {
     constexpr int kPer = kResidueSpan * kBlk / 256;   // staged entries per thread and plane
-    __shared__ float staged[2][kStaged];
+    __shared__ alignas(16) float staged[2][kStaged];
     __shared__ uint32_t part[8][kBlk];
     __shared__ int exps[kBlk];
     const int t = threadIdx.x;
@@ -315,32 +313,27 @@ __global__ __launch_bounds__(256, 4) void residue_planes(
     const int64_t limit = is_a ? M : N;
 
     // 32 rows by kResidueSpan K-entries of A, or kResidueSpan K rows by 32
-    // columns of B: 16-byte loads where rows and planes are aligned
+    // columns of B, 16 bytes per load
     const float *const ph = is_a ? Ah : Bh, *const pl = is_a ? Al : Bl;
     const int64_t ld = is_a ? lda : ldb, xn = is_a ? K : N, yn = is_a ? M : K;
-    constexpr int kWide = VEC ? 4 : 1;
-    const int across = (is_a ? kResidueSpan : kBlk) / kWide, pitch = is_a ? kPitchA : kPitchB;
-    float fh[kPer], fl[kPer];
+    const int across = (is_a ? kResidueSpan : kBlk) / 4, pitch = is_a ? kPitchA : kPitchB;
+    f32x4 fh[kPer / 4], fl[kPer / 4];
     auto fetch = [&](int span0) {
         const int64_t x0 = is_a ? span0 : blk * kBlk, y0 = is_a ? blk * kBlk : span0;
 #pragma unroll
-        for (int n = 0; n < kPer / kWide; ++n) {
+        for (int n = 0; n < kPer / 4; ++n) {
             const int q = n * 256 + t;
-            const int64_t x = x0 + q % across * kWide, y = y0 + q / across;
+            const int64_t x = x0 + q % across * 4, y = y0 + q / across;
             const float *const h = ph + y * ld + x, *const l = pl + y * ld + x;
-            if (VEC && y < yn && x + 4 <= xn) {
-                const float4 h4 = *reinterpret_cast<const float4 *>(h);
-                const float4 l4 = *reinterpret_cast<const float4 *>(l);
-                fh[n * kWide] = h4.x; fh[n * kWide + (1 & -VEC)] = h4.y;
-                fh[n * kWide + (2 & -VEC)] = h4.z; fh[n * kWide + (3 & -VEC)] = h4.w;
-                fl[n * kWide] = l4.x; fl[n * kWide + (1 & -VEC)] = l4.y;
-                fl[n * kWide + (2 & -VEC)] = l4.z; fl[n * kWide + (3 & -VEC)] = l4.w;
+            if (y < yn && x + 4 <= xn) {
+                fh[n] = *reinterpret_cast<const f32x4u *>(h);
+                fl[n] = *reinterpret_cast<const f32x4u *>(l);
             } else {
 #pragma unroll
-                for (int u = 0; u < kWide; ++u) {
+                for (int u = 0; u < 4; ++u) {
                     const bool in = y < yn && x + u < xn;
-                    fh[n * kWide + u] = in ? h[u] : 0.0f;
-                    fl[n * kWide + u] = in ? l[u] : 0.0f;
+                    fh[n][u] = in ? h[u] : 0.0f;
+                    fl[n][u] = in ? l[u] : 0.0f;
                 }
             }
         }
@@ -392,15 +385,10 @@ __global__ __launch_bounds__(256, 4) void residue_planes(
 #pragma unroll 1
     for (int span0 = first; span0 < last; span0 += kResidueSpan) {
 #pragma unroll
-        for (int n = 0; n < kPer / kWide; ++n) {
-            const int q = n * 256 + t;
-            float *const sh = &staged[0][q / across * pitch + q % across * kWide];
-            float *const sl = &staged[1][q / across * pitch + q % across * kWide];
-#pragma unroll
-            for (int u = 0; u < kWide; ++u) {
-                sh[u] = fh[n * kWide + u];
-                sl[u] = fl[n * kWide + u];
-            }
+        for (int n = 0; n < kPer / 4; ++n) {
+            const int at = (n * 256 + t) / across * pitch + (n * 256 + t) % across * 4;
+            *reinterpret_cast<f32x4 *>(&staged[0][at]) = fh[n];
+            *reinterpret_cast<f32x4 *>(&staged[1][at]) = fl[n];
         }
         __syncthreads();
         if (span0 + kResidueSpan < last)
@@ -510,10 +498,10 @@ __device__ __forceinline__ int modulus_of(int i)
     return static_cast<int>((w >> (8 * (i & 3))) & 255u) + 1;
 }
 
-// The products of the residue planes: workgroup = (modulus, 64 T x 64 T tile
-// of C), four wavefronts of T x T matrix-core blocks (32 x 32) each.
+// The products of the residue planes: workgroup = (modulus, 64 TM x 64 TN tile
+// of C), four wavefronts of TM x TN matrix-core blocks (32 x 32) each.
 //
-// T = 4 (256 x 256 tiles, one wavefront per SIMD with all 256 accumulation
+// 4 x 4 (256 x 256 tiles, one wavefront per SIMD with all 256 accumulation
 // registers): an operand read from LDS feeds four MFMAs, 64 LDS bytes per
 // cycle and compute unit of the 128 it can deliver.  A wavefront keeps its
 // matrix core busy by itself: operands are read one K-step ahead into a
@@ -526,37 +514,50 @@ __device__ __forceinline__ int modulus_of(int i)
 // K-steps and one sum per MFMA of the other blocks, is hidden by the matrix
 // core: 1.61 ms at 4096^3 (1.37 PFLOP/s), against 2.07 ms reduced between
 // stages; 224 against 285 us at 2048^3.
-// T = 2, T = 1 (128 x 128 and 64 x 64 tiles) when there are too few larger
-// tiles to fill 256 compute units: 60 us against 102 us for the digit pairs at
-// 1000 x 1531 x 2047, 4.7 against 31 us at 200 x 300 x 257.
+// 4 x 2 (256 x 128 tiles, three stages in the ring, two workgroups per compute
+// unit): one works while the other starts or stores, at 96 LDS bytes per cycle
+// for operands; the product kernel of 1000 x 1531 x 2047 takes 46 us, 51 with
+// 2 x 2 (128 LDS bytes per cycle, all it can deliver).  2 x 2 and 1 x 1 are for
+// outputs with too few larger tiles.
 //
-// Workgroups run modulus by modulus, so that the planes in use are one
-// modulus's; within it each XCD takes a contiguous run of tiles ordered in
-// strips of four tile rows, so that 32 neighbouring tiles share L2.
-template <class Dg, int T>
-__global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
+// Where the tiles of a modulus are few (own_xcd), each die computes two moduli
+// alone, so that a plane is fetched into one L2 instead of all eight.
+// Otherwise workgroups run modulus by modulus, so that the planes in use are
+// one modulus's, and each XCD takes a contiguous run of its tiles.  Either way
+// tiles are ordered in strips of four tile rows, so that neighbours share L2.
+template <class Dg, int TM, int TN>
+__global__ __launch_bounds__(256, TM * TN == 16 ? 1 : 2) void gemm_residues(
     const uint8_t *__restrict__ Ap, const uint8_t *__restrict__ Bp, int64_t plane_a,
     int64_t plane_b, int nKB, int kb0, int kb1, int nTI, int nTJ, uint8_t *__restrict__ Cr,
-    int64_t plane_c, int exact)
+    int64_t plane_c, int exact, int own_xcd)
 {
     using Acc = typename Dg::Acc;
     constexpr int kChunk = kStageFrags * kFragBytes;      // a block's bytes per stage
-    constexpr int kSlotBytes = 4 * T * kChunk;
-    constexpr int kDma = T * kStageFrags;                 // DMA instructions per wave and stage
-    constexpr int kRead = 2 * T;                          // operands per K-step and wave
-    constexpr int kSlots = 4;
+    constexpr int kSlotBytes = 2 * (TM + TN) * kChunk;
+    constexpr int kShare = (TM + TN) / 2;                 // chunks each wave sends per stage
+    constexpr int kDma = kShare * kStageFrags;            // DMA instructions per wave and stage
+    constexpr int kRead = TM + TN;                        // operands per K-step and wave
+    constexpr int kBlocks = TM * TN;
+    constexpr int kSlots = TM == TN ? 4 : 3;
     __shared__ uint4 ring[kSlots * kSlotBytes / 16];
     uint8_t *const lds = reinterpret_cast<uint8_t *>(ring);
     const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) uint8_t *)lds));
 
     const int tiles = nTI * nTJ;
-    const int mod = blockIdx.x / tiles;
-    int ti, tj;
+    int mod, ti, tj;
     {
-        int j = blockIdx.x % tiles;
-        if (tiles % 8 == 0)                       // XCD j % 8 takes a contiguous run
-            j = (j % 8) * (tiles / 8) + j / 8;
+        int j;
+        if (own_xcd) {
+            const int nth = blockIdx.x / kXcds;
+            mod = blockIdx.x % kXcds * (kModuli / kXcds) + nth / tiles;
+            j = nth % tiles;
+        } else {
+            mod = blockIdx.x / tiles;
+            j = blockIdx.x % tiles;
+            if (tiles % kXcds == 0)               // XCD j % 8 takes a contiguous run
+                j = (j % kXcds) * (tiles / kXcds) + j / kXcds;
+        }
         const int group = j / (4 * nTJ), rows = nTI - 4 * group < 4 ? nTI - 4 * group : 4;
         const int in = j - group * 4 * nTJ;
         ti = 4 * group + in % rows;
@@ -566,31 +567,33 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
 
-    // this wavefront's DMA share: T of the 4 T chunks (2 T of A, 2 T of B)
-    const uint8_t *src;
-    {
-        const bool of_a = wave < 2;
-        const int64_t blk = static_cast<int64_t>(of_a ? ti : tj) * (2 * T) + (wave & 1) * T;
-        src = (of_a ? Ap + mod * plane_a : Bp + mod * plane_b) + (blk * nKB + kb0) * kFragBytes;
+    // this wavefront's DMA share of the 2 TM chunks of A and 2 TN of B
+    const uint8_t *src[kShare];
+#pragma unroll
+    for (int c = 0; c < kShare; ++c) {
+        const int n = wave * kShare + c;
+        const bool of_a = n < 2 * TM;
+        const int64_t blk = of_a ? static_cast<int64_t>(ti) * (2 * TM) + n
+                                 : static_cast<int64_t>(tj) * (2 * TN) + n - 2 * TM;
+        src[c] = (of_a ? Ap + mod * plane_a : Bp + mod * plane_b) + (blk * nKB + kb0) * kFragBytes;
     }
-    const int64_t blk_stride = static_cast<int64_t>(nKB) * kFragBytes;
     const int nst = (kb1 - kb0) / kStageFrags;
     // DMA q of stage st; past the end the last stage again, so that every
     // stage sends the same number and the waits below need no cases
     const uint32_t lane16 = lane * 16;
     auto dma = [&](int st, int q) {
         const int c = q / kStageFrags, h = q % kStageFrags;
-        lds_dma16(src + c * blk_stride + static_cast<int64_t>(st < nst ? st : nst - 1) * kChunk +
+        lds_dma16(src[c] + static_cast<int64_t>(st < nst ? st : nst - 1) * kChunk +
                       h * kFragBytes,
                   lane16,
-                  lds_base + (st % kSlots) * kSlotBytes + (wave * T + c) * kChunk + h * kFragBytes);
+                  lds_base + (st % kSlots) * kSlotBytes + (wave * kShare + c) * kChunk + h * kFragBytes);
     };
 
-    Acc acc[T][T];
+    Acc acc[TM][TN];
 #pragma unroll
-    for (int i = 0; i < T; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < T; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 acc[i][j][r] = 0;
@@ -600,57 +603,57 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
     // BF16 residues: one FP32 sum reduced mod m
     auto fold = [&](int block, int r) {
         if constexpr (Dg::kFoldStages > 0) {
-            const float c = acc[block / T][block % T][r];
+            const float c = acc[block / TN][block % TN][r];
             const float n = __builtin_fmaf(c, inv, kRoundMagic) - kRoundMagic;
-            acc[block / T][block % T][r] = __builtin_fmaf(n, -static_cast<float>(m), c);
+            acc[block / TN][block % TN][r] = __builtin_fmaf(n, -static_cast<float>(m), c);
         }
     };
 
     uint4 f0[kRead], f1[kRead];
-    const int oa = wm * T * kChunk + lane * 16, ob = (2 + wn) * T * kChunk + lane * 16;
-    // operand q (T of A, then T of B) of K-step kk in the slot at byte `at`
+    const int oa = wm * TM * kChunk + lane * 16, ob = (2 * TM + wn * TN) * kChunk + lane * 16;
+    // operand q (TM of A, then TN of B) of K-step kk in the slot at byte `at`
     auto read = [&](uint4 (&f)[kRead], int at, int kk, int q) {
         f[q] = *reinterpret_cast<const uint4 *>(
-            lds + at + (q < T ? oa + q * kChunk : ob + (q - T) * kChunk) + kk * kFragBytes);
+            lds + at + (q < TM ? oa + q * kChunk : ob + (q - TM) * kChunk) + kk * kFragBytes);
     };
     // MFMA q of a K-step
     auto mfma = [&](const uint4 (&f)[kRead], int q) {
-        const int i = q / T, j = q % T;
-        acc[i][j] = mma(f[i], f[T + j], acc[i][j]);
+        const int i = q / TN, j = q % TN;
+        acc[i][j] = mma(f[i], f[TM + j], acc[i][j]);
     };
-    constexpr int kSteps = T * T > kRead ? T * T : kRead;
+    constexpr int kSteps = kBlocks > kRead ? kBlocks : kRead;
 
 #pragma unroll
     for (int s = 0; s < kSlots; ++s)
 #pragma unroll
         for (int q = 0; q < kDma; ++q)
             dma(s, q);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * kDma));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((kSlots - 1) * kDma));
     barrier_no_fence();
     __builtin_amdgcn_sched_barrier(0);
     // Stage st, whose first K-step has been read into f0: multiplies it while
     // the second K-step is read; then, once stage st + 1 has landed everywhere
     // and everyone has read this slot, reads that stage's first K-step and
-    // sends stage st + 4 into this slot under the second K-step's MFMAs.
+    // sends stage st + kSlots into this slot under the second K-step's MFMAs.
     // BF16: the sums of block `FOLD` are reduced between its MFMA of the first
     // K-step and that of the second, one sum per MFMA of the other blocks.
     auto stage = [&](int st, auto which, auto ahead) {
         constexpr int FOLD = decltype(which)::value;
         constexpr bool AHEAD = decltype(ahead)::value;
-        constexpr bool kFold = FOLD >= 0 && FOLD < T * T;
+        constexpr bool kFold = FOLD >= 0 && FOLD < kBlocks;
         const int at = (st % kSlots) * kSlotBytes, next = ((st + 1) % kSlots) * kSlotBytes;
 #pragma unroll
         for (int q = 0; q < kSteps; ++q) {
             if (q < kRead)
                 read(f1, at, 1, q);
-            if (q < T * T)
+            if (q < kBlocks)
                 mfma(f0, q);
-            if (kFold && T == 4 && q > FOLD)
+            if (kFold && kBlocks == 16 && q > FOLD)
                 fold(FOLD, q - FOLD - 1);
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (kFold) {
-            if constexpr (T == 4) {
+            if constexpr (kBlocks == 16) {
                 fold(FOLD, 15);
             } else {
 #pragma unroll
@@ -658,19 +661,19 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
                     fold(FOLD, r);
             }
         }
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kDma) & lgkmcnt_imm(0));
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((kSlots - 2) * kDma) & lgkmcnt_imm(0));
         barrier_no_fence();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < kSteps; ++q) {
             if (q < kRead && AHEAD)
                 read(f0, next, 0, q);
-            if (kFold && T == 4 && q < FOLD)
+            if (kFold && kBlocks == 16 && q < FOLD)
                 fold(FOLD, 15 - FOLD + q);
-            if (q < T * T)
+            if (q < kBlocks)
                 mfma(f1, q);
             if (q < kDma)
-                dma(st + 4, q);
+                dma(st + kSlots, q);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -709,15 +712,15 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_residues(
 
     // Residue planes of C: per modulus and 32 x 32 block 1 KiB, word w of
     // lane l (rows 8 w + 4 (l / 32) + 0..3 of column l % 32) at 256 w + 4 l.
-    const int64_t nCB = static_cast<int64_t>(nTJ) * (2 * T);
+    const int64_t nCB = static_cast<int64_t>(nTJ) * (2 * TN);
     uint8_t *const out = Cr + mod * plane_c;
     auto store = [&](auto low_byte) {
 #pragma unroll
-        for (int i = 0; i < T; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < T; ++j) {
-                const int64_t rb = static_cast<int64_t>(ti) * (2 * T) + wm * T + i;
-                const int64_t cb = static_cast<int64_t>(tj) * (2 * T) + wn * T + j;
+            for (int j = 0; j < TN; ++j) {
+                const int64_t rb = static_cast<int64_t>(ti) * (2 * TM) + wm * TM + i;
+                const int64_t cb = static_cast<int64_t>(tj) * (2 * TN) + wn * TN + j;
                 uint8_t *const dst = out + (rb * nCB + cb) * kFragBytes + lane * 4;
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
@@ -887,8 +890,8 @@ __global__ __launch_bounds__(256) void zero_matrix(int64_t M, int64_t N, float *
 constexpr int64_t kPlaneSkew = 4096 + 256;
 
 struct ResidueGeom {
-    int tile;                  // 32 x 32 blocks per wavefront and dimension: 1, 2 or 4
-    int64_t nTI, nTJ;          // tiles of 64 * tile
+    int tm, tn;                // 32 x 32 blocks per wavefront: 1 x 1, 2 x 2, 4 x 2 or 4 x 4
+    int64_t nTI, nTJ;          // tiles of 64 tm x 64 tn
     int64_t nRB, nCB, nKB;     // 32-row blocks, 32-column blocks, K-steps (padded)
     int64_t nseg, nband;       // partial maxima per row / column
     int64_t plane_a, plane_b, plane_c;
@@ -900,22 +903,41 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 inline ResidueGeom residue_geom(int64_t M, int64_t N, int64_t K, int frag_k)
 {
     ResidueGeom g;
-    // The largest tile that still fills the chip.  T = 4 from four workgroups
-    // per compute unit on (fewer leave much of it idle in the last round) and
-    // K >= 512, below which the 64 KiB its four stages hold are mostly start-up:
-    // 200 against 209 us (T = 2) per call at 2048^3 and 553 against 614 at
-    // 3072^3, but 115 against 106 at 1536^3 and 118 against 106 at
-    // 2500 x 2500 x 300.  T = 2 from one workgroup per compute unit on: 27.0
-    // against 27.5 us (T = 1) at 512^3, 49 against 58 at 1024^3, and 17.2
-    // against 16.5 at 256^3.
-    const int64_t tiles256 = ffh::cdiv(M, 256) * ffh::cdiv(N, 256) * kModuli;
-    const int64_t tiles128 = ffh::cdiv(M, 128) * ffh::cdiv(N, 128) * kModuli;
-    g.tile = tiles256 >= 1024 && K >= 512 ? 4 : tiles128 >= 256 ? 2 : 1;
-    g.nTI = ffh::cdiv(M, 64 * g.tile);
-    g.nTJ = ffh::cdiv(N, 64 * g.tile);
-    g.nRB = g.nTI * 2 * g.tile;
-    g.nCB = g.nTJ * 2 * g.tile;
-    g.nKB = ffh::cdiv(K, static_cast<int64_t>(frag_k) * kStageFrags) * kStageFrags;
+    // The tile of the least estimated time: the rounds of one workgroup per
+    // compute unit that the tiles of a die make, times the cost of a round in
+    // units of half a 256 x 128 one.  The costs were fitted to per-call times of
+    // all four tiles at 40 shapes (int8 unless said): 4 x 2 against 4 x 4 and
+    // 2 x 2 takes 45.4, 47.0 and 46.6 us at 1024^3, 347, 357 and 376 at 2560^3,
+    // 447, 485 and 490 at 5000 x 5000 x 512; whole rounds matter between 2 x 2
+    // and 4 x 2 (84.8 against 87.5 us at 1300^3, 101.4 against 97.1 at 1536^3);
+    // 1 x 1 against 2 x 2 takes 16.8 and 17.3 us at 200 x 300 x 257, 48.9 and
+    // 53.5 at 64 x 5000 x 1000, 23.2 and 22.2 at 512^3.  4 x 4 leaves the
+    // start and end of a tile to one workgroup per compute unit and so pays
+    // only from 96 K-steps on: 1166 against 1182 us at 4096^3 and 311 against
+    // 315 at 2048^3 in BF16, but 690 against 675 at 4096 x 4096 x 2048.
+    const int64_t nkb = ffh::cdiv(K, static_cast<int64_t>(frag_k) * kStageFrags) * kStageFrags;
+    constexpr struct {
+        int tm, tn;
+        double round;
+    } kTiles[] = {{1, 1, 0.45}, {2, 2, 1.15}, {4, 2, 2.0}, {4, 4, 3.88}};
+    double best = 0;
+    for (const auto &t : kTiles) {
+        if (t.tn == 4 && nkb < 96)
+            break;
+        const int64_t per_die =
+            ffh::cdiv(M, 64 * t.tm) * ffh::cdiv(N, 64 * t.tn) * (kModuli / kXcds);
+        const double cost = t.round * static_cast<double>(ffh::cdiv(per_die, 32));
+        if (best == 0 || cost <= best) {
+            best = cost;
+            g.tm = t.tm;
+            g.tn = t.tn;
+        }
+    }
+    g.nTI = ffh::cdiv(M, 64 * g.tm);
+    g.nTJ = ffh::cdiv(N, 64 * g.tn);
+    g.nRB = g.nTI * 2 * g.tm;
+    g.nCB = g.nTJ * 2 * g.tn;
+    g.nKB = nkb;
     g.nseg = ffh::cdiv(K, kRowSegment);
     g.nband = ffh::cdiv(K, kColBand);
     g.plane_a = g.nRB * g.nKB * kFragBytes + kPlaneSkew;
@@ -953,10 +975,10 @@ ff_status sliced_gemm(int64_t M, int64_t N, int64_t K, const float *Ah, const fl
         return FF_ERR_SIZE;
     const int64_t row_groups = ffh::cdiv(M, 4), col_groups = ffh::cdiv(N, 64);
     const int64_t max_grid = row_groups * g.nseg + col_groups * g.nband;
-    // up to 8 spans per workgroup, as long as that leaves eight per compute unit
+    // up to 8 spans per workgroup, as long as that leaves four per compute unit
     const int64_t all_spans = ffh::cdiv(g.nKB * Dg::kFragK, kResidueSpan);
     int spans = 8;
-    while (spans > 1 && (g.nRB + g.nCB) * ffh::cdiv(all_spans, spans) < 2048)
+    while (spans > 1 && (g.nRB + g.nCB) * ffh::cdiv(all_spans, spans) < 1024)
         spans /= 2;
     const int64_t res_grid = (g.nRB + g.nCB) * ffh::cdiv(all_spans, spans);
     const int64_t gemm_grid = kModuli * g.nTI * g.nTJ;
@@ -979,20 +1001,23 @@ ff_status sliced_gemm(int64_t M, int64_t N, int64_t K, const float *Ah, const fl
     uint8_t *Ap = reinterpret_cast<uint8_t *>(base + g.off_a);
     uint8_t *Bp = reinterpret_cast<uint8_t *>(base + g.off_b);
     uint8_t *Cr = reinterpret_cast<uint8_t *>(base + g.off_c);
-    const bool all_vec = lda % 4 == 0 && ldb % 4 == 0 && ffh::aligned(Ah, 16) &&
-                         ffh::aligned(Al, 16) && ffh::aligned(Bh, 16) && ffh::aligned(Bl, 16);
-    auto absmax = all_vec ? absmax_partials<true> : absmax_partials<false>;
-    hipLaunchKernelGGL(absmax, dim3(static_cast<unsigned>(max_grid)), dim3(256), 0, st, M, N, K,
+    hipLaunchKernelGGL(absmax_partials, dim3(static_cast<unsigned>(max_grid)), dim3(256), 0, st, M, N, K,
                        Ah, lda, Bh, ldb, row_groups, col_groups, rowpart, colpart);
-    auto residues = all_vec ? residue_planes<Dg, true> : residue_planes<Dg, false>;
-    hipLaunchKernelGGL(residues, dim3(static_cast<unsigned>(res_grid)), dim3(256), 0, st, M, N, K,
+    hipLaunchKernelGGL(residue_planes<Dg>, dim3(static_cast<unsigned>(res_grid)), dim3(256), 0, st, M, N, K,
                        Ah, Al, lda, Bh, Bl, ldb, static_cast<int>(g.nRB),
                        static_cast<int>(g.nCB), static_cast<int>(g.nKB), spans, rowpart, colpart,
                        static_cast<int>(g.nseg), static_cast<int>(g.nband), rowexp, colexp, Ap,
                        Bp, g.plane_a, g.plane_b);
-    auto product = g.tile == 4   ? gemm_residues<Dg, 4>
-                   : g.tile == 2 ? gemm_residues<Dg, 2>
-                                 : gemm_residues<Dg, 1>;
+    auto product = g.tn == 4   ? gemm_residues<Dg, 4, 4>
+                   : g.tm == 4 ? gemm_residues<Dg, 4, 2>
+                   : g.tm == 2 ? gemm_residues<Dg, 2, 2>
+                               : gemm_residues<Dg, 1, 1>;
+    // One modulus's planes pass through one die's L2 while its tiles are few;
+    // with more, each die's share of them is enough (447 against 470 us at
+    // 5000 x 5000 x 512, 97 against 100 at 2500 x 2500 x 300), with fewer it
+    // would fetch nearly all of both operands (57.6 against 45.4 us at 1024^3,
+    // 18.5 against 16.8 at 200 x 300 x 257, 143 against 139 at 1700^3).
+    const int own_xcd = g.nTI * g.nTJ <= 128 ? 1 : 0;
     const int64_t chunk = kMaxKChunk / Dg::kFragK;
     for (int64_t kb0 = 0; kb0 < g.nKB; kb0 += chunk) {
         const int64_t kb1 = kb0 + chunk < g.nKB ? kb0 + chunk : g.nKB;
@@ -1000,7 +1025,8 @@ ff_status sliced_gemm(int64_t M, int64_t N, int64_t K, const float *Ah, const fl
                            Bp, g.plane_a, g.plane_b, static_cast<int>(g.nKB),
                            static_cast<int>(kb0), static_cast<int>(kb1),
                            static_cast<int>(g.nTI), static_cast<int>(g.nTJ), Cr, g.plane_c,
-                           (kb1 - kb0) * Dg::kFragK > 4096 ? 1 : 0);
+                           (kb1 - kb0) * Dg::kFragK > 4096 ? 1 : 0,
+                           own_xcd);
         hipLaunchKernelGGL(combine_residues, dim3(static_cast<unsigned>(out_grid)), dim3(256), 0,
                            st, M, N, nBJ, Cr, g.nCB, g.plane_c, rowexp, colexp, Ch, Cl, ldc,
                            kb0 > 0 ? 1 : 0);

@@ -331,3 +331,17 @@ def test_largest_residue_sums_and_tile_edges(algo, M, N, K):
             exact = ai * (frac(b[0, j]) + frac(b[1, j]))
             err = abs(frac(C[0, i, j]) + frac(C[1, i, j]) - exact)
             assert err <= abs(exact) / (1 << 48), (i, j)
+
+
+@pytest.mark.parametrize("algo,M,N,K", [
+    # 256 x 128 tiles, one to four stages in a ring of three, and more
+    ("i8", 1000, 1000, 33), ("i8", 900, 1020, 65), ("i8", 1024, 1024, 130), ("i8", 1001, 993, 200),
+    ("bf16", 1000, 1000, 17), ("bf16", 900, 1020, 33), ("bf16", 1024, 1024, 65),
+    ("bf16", 1001, 993, 1100),
+    # 256 x 256 tiles, few and many
+    ("i8", 2040, 2041, 3100), ("bf16", 2040, 2041, 1600), ("i8", 2950, 3001, 3073),
+    # many 64 x 64 tiles, their number no multiple of 8
+    ("i8", 60, 8300, 65), ("bf16", 8300, 60, 40)])
+def test_tile_choice_and_order(algo, M, N, K):
+    # every tile by the rule on M, N and K, in both orders of the workgroups
+    test_largest_residue_sums_and_tile_edges(algo, M, N, K)
