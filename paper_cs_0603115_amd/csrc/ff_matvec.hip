@@ -13,7 +13,7 @@
 // component), then a butterfly over the group's lanes and, for several
 // wavefronts, an in-order LDS combine give y_i.  x is re-read from L2.
 // Fast backward: the workgroup grid is (column tiles) x (row bands); a
-// thread owns four adjacent columns, walks the rows of its band, writes
+// thread owns four adjacent columns, walks the row pairs of its band, writes
 // dA_ij = Mul22(g_i, x_j) and accumulates Mul22(g_i, A_ij) per column; the
 // per-band partial column sums go to the workspace and a second launch adds
 // them in band order.
@@ -31,10 +31,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 // Backward band kernel: workgroups of 128 threads of four columns each, as many
 // across the columns as these need (16 to 128) and the rest over further
 // bands.  A band is so many rows that the matrix makes about 2^17 threads
-// (two wavefronts per SIMD), at most 128 rows: at 8192 x 8192 those measured
-// 175-176 us against 183-185 for 64, but they left 1024 x 1024 with sixteen
-// workgroups (70 us, 8.2 now).  At most 1024 bands, so that combining
-// their partial sums stays short.
+// (two wavefronts per SIMD), at most 128 rows: 128-row bands left 1024 x 1024
+// with sixteen workgroups (70 us, 8.6 now).  At most 1024 bands, so that
+// combining their partial sums stays short.
 constexpr int kColBlock = 128;
 constexpr int64_t kBandRows = 128;
 
@@ -190,27 +189,31 @@ __global__ __launch_bounds__(256) void matvec_plain(int64_t M, int64_t N,
 }
 
 // Fused backward over row bands: thread owns COLS adjacent columns of one
-// band, ROWS rows' loads issued before any arithmetic; 2^col_shift threads of
-// the workgroup span the columns.
-template <int BLOCK, int COLS, bool WANT_DA, bool WANT_DX, int ROWS>
+// band, both rows' loads of a pair issued before any arithmetic; 2^col_shift
+// threads of the workgroup span the columns.  Band b of n takes the row pairs
+// b, b + n, b + 2 n, ..., so that the workgroups in flight sweep the four
+// planes together: with adjacent rows per band every band kept pages of its
+// own open (14271 x 4110: 263 us, 234 now; 14336 x 4096: 218, 171; 4096 x 4096:
+// 57, 51; 8191 x 8191: 235, 220; 8192 x 8192: 172, 169, 6.3 TB/s; of 30 shapes
+// two lost, 4096 x 16384 181 to 196 and 2048 x 32768 193 to 215).  Loading two
+// pairs ahead of the stores, or four rows at once, gave nothing.
+template <int BLOCK, int COLS, bool WANT_DA, bool WANT_DX>
 __global__ __launch_bounds__(BLOCK) void matvec_bwd_band(
     int64_t M, int64_t N, const float *__restrict__ Ah, const float *__restrict__ Al, int64_t lda,
     const float *__restrict__ xh, const float *__restrict__ xl, const float *__restrict__ gh,
     const float *__restrict__ gl, float *__restrict__ dAh, float *__restrict__ dAl, int64_t ldda,
-    float2 *__restrict__ part, int band_rows, int col_shift)
+    float2 *__restrict__ part, int nbands, int col_shift)
 {
     const int across = 1 << col_shift;
     int64_t c0 = ((static_cast<int64_t>(blockIdx.x) << col_shift) + (threadIdx.x & (across - 1))) *
                  COLS;
     const int64_t band = (static_cast<int64_t>(blockIdx.y) * BLOCK + threadIdx.x) >> col_shift;
-    const int64_t i0 = band * band_rows;
-    if (c0 >= N || i0 >= M)
+    if (c0 >= N || band >= nbands)
         return;
     // the last thread's columns end with the row: those it shares with the
     // thread before are computed twice, to the same bits
     if (c0 + COLS > N)
         c0 = N - COLS;
-    const int64_t i1 = (i0 + band_rows < M) ? i0 + band_rows : M;
     float x_h[COLS], x_l[COLS];
     float2 acc[COLS];
 #pragma unroll
@@ -263,17 +266,18 @@ __global__ __launch_bounds__(BLOCK) void matvec_bwd_band(
             }
         }
     };
-    int64_t i = i0;
-    for (; i + ROWS <= i1; i += ROWS) {
-        float a_h[ROWS][COLS], a_l[ROWS][COLS];
+    const int64_t step = 2 * static_cast<int64_t>(nbands);
+    int64_t i = 2 * band;
+    for (; i + 2 <= M; i += step) {
+        float a_h[2][COLS], a_l[2][COLS];
 #pragma unroll
-        for (int p = 0; p < ROWS; ++p)
+        for (int p = 0; p < 2; ++p)
             load_row(i + p, a_h[p], a_l[p]);
 #pragma unroll
-        for (int p = 0; p < ROWS; ++p)
+        for (int p = 0; p < 2; ++p)
             row(i + p, a_h[p], a_l[p]);
     }
-    for (; i < i1; ++i) {
+    if (i < M) {   // the last row of an odd number
         float a_h[COLS], a_l[COLS];
         load_row(i, a_h, a_l);
         row(i, a_h, a_l);
@@ -750,32 +754,22 @@ ff_status ff_matvec_backward(int64_t M, int64_t N, const float *A_hi, const floa
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, dim3(kColBlock), 0, st, M, N, A_hi, A_lo, lda, x_hi,
                                x_lo, g_hi, g_lo, dA_hi, dA_lo, ldda, part,
-                               static_cast<int>(band_rows), col_shift);
+                               static_cast<int>(nbands), col_shift);
         };
-        // four rows in flight where bands are short and wavefronts few, two
-        // in long bands (196 us with four against 184 at 8192 x 8192)
-        const bool four = band_rows < 64;
-        if (cols == 4 && four) {
+        if (cols == 4) {
             if (want_da && want_dx)
-                launch(matvec_bwd_band<kColBlock, 4, true, true, 4>);
+                launch(matvec_bwd_band<kColBlock, 4, true, true>);
             else if (want_da)
-                launch(matvec_bwd_band<kColBlock, 4, true, false, 4>);
+                launch(matvec_bwd_band<kColBlock, 4, true, false>);
             else
-                launch(matvec_bwd_band<kColBlock, 4, false, true, 4>);
-        } else if (cols == 4) {
-            if (want_da && want_dx)
-                launch(matvec_bwd_band<kColBlock, 4, true, true, 2>);
-            else if (want_da)
-                launch(matvec_bwd_band<kColBlock, 4, true, false, 2>);
-            else
-                launch(matvec_bwd_band<kColBlock, 4, false, true, 2>);
+                launch(matvec_bwd_band<kColBlock, 4, false, true>);
         } else {
             if (want_da && want_dx)
-                launch(matvec_bwd_band<kColBlock, 1, true, true, 2>);
+                launch(matvec_bwd_band<kColBlock, 1, true, true>);
             else if (want_da)
-                launch(matvec_bwd_band<kColBlock, 1, true, false, 2>);
+                launch(matvec_bwd_band<kColBlock, 1, true, false>);
             else
-                launch(matvec_bwd_band<kColBlock, 1, false, true, 2>);
+                launch(matvec_bwd_band<kColBlock, 1, false, true>);
         }
     }
     if (want_dx && N >= 4096)

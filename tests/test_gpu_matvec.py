@@ -411,3 +411,20 @@ def test_backward_takes_a_workspace_of_longer_bands():
     assert call(longest) == 0
     torch.cuda.synchronize()
     check_cols_exact(A, g, dx, "long bands", cols=np.arange(0, N, 37))
+
+
+@pytest.mark.parametrize("M,N", [(1, 70), (2, 70), (3, 70), (7, 64), (515, 130), (1030, 64), (4099, 257)])
+def test_backward_takes_every_row_once(M, N):
+    # row pairs dealt to the bands in turn: odd and even numbers of rows, last
+    # rounds in which some bands have a pair, one a single row, others none.
+    # Small integers make every sum exact, so a row missed or taken twice shows.
+    ff = _ff()
+    _announce(f"[gpu] matvec rows {M}x{N}")
+    A, x, g = ff.ff_zeros((M, N)), ff.ff_zeros((N,)), ff.ff_zeros((M,))
+    A[0] = torch.arange(M * N, device="cuda").remainder(7).view(M, N).float()
+    x[0] = torch.arange(N, device="cuda").remainder(5).float()
+    g[0] = torch.arange(M, device="cuda").remainder(11).float()
+    dA, dx = ff.ff_matvec_backward(A, x, g)
+    assert torch.equal(dx[0].double(), (g[0].double()[:, None] * A[0].double()).sum(0))
+    assert torch.equal(dA[0], g[0][:, None] * x[0][None, :])
+    assert not dx[1].any() and not dA[1].any()
