@@ -4,9 +4,9 @@
 //
 // FMA loop (the plain float-float GEMM): C_ij = Add22 accumulation, k
 // ascending, of Mul22(A_ik, B_kj) -- section 4.1's operators applied term by
-// term.  LDS-tiled (64 x 64 outputs per workgroup, 4 x 4 per thread), VALU
-// bound: ~26 binary32 operations per multiply-add, no contraction.  Bit for
-// bit the sequential definition.
+// term.  LDS-tiled (1, 4 or 16 outputs per thread), VALU bound: ~26 binary32
+// operations per multiply-add, no contraction.  Bit for bit the sequential
+// definition.
 //
 // Sliced (the fast path; the paper has no GEMM): every entry of A and B is
 // turned into a signed fixed-point integer relative to a power of two of its
@@ -49,9 +49,14 @@ namespace ffk {
 
 // ----------------------------------------------------------------- plain
 
-constexpr int kPT = 64;   // plain tile: 64 x 64 outputs
-constexpr int kPK = 16;   // k per LDS stage
-
+// Workgroup = 16 R x 16 R outputs, R x R per thread, K in stages of KS entries
+// through LDS; the next stage is loaded while one is multiplied.  An output is a
+// serial chain of ~26 operations per k, so a small product is bound by the
+// chains that a wavefront carries: four by four per thread took 240 us at
+// 200 x 300 x 257 on twenty workgroups, one per thread takes 23; with
+// workgroups enough the vector unit is the bound (1024^3: 1010 us with four by
+// four, 516 now, 2 x 2).
+template <int R, int KS>
 __global__ __launch_bounds__(256) void gemm_fma_loop(int64_t M, int64_t N, int64_t K,
                                                      const float *__restrict__ Ah,
                                                      const float *__restrict__ Al, int64_t lda,
@@ -60,61 +65,77 @@ __global__ __launch_bounds__(256) void gemm_fma_loop(int64_t M, int64_t N, int64
                                                      float *__restrict__ Ch,
                                                      float *__restrict__ Cl, int64_t ldc)
 {
-    __shared__ float sAh[kPK][kPT + 1], sAl[kPK][kPT + 1];
-    __shared__ float sBh[kPK][kPT], sBl[kPK][kPT];
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    const int64_t i0 = static_cast<int64_t>(blockIdx.y) * kPT;
-    const int64_t j0 = static_cast<int64_t>(blockIdx.x) * kPT;
-    float ch[4][4], cl[4][4];
+    constexpr int kTile = 16 * R, kPer = kTile * KS / 256;
+    __shared__ float sAh[KS][kTile + 1], sAl[KS][kTile + 1];
+    __shared__ float sBh[KS][kTile], sBl[KS][kTile];
+    const int t = threadIdx.x, tx = t % 16, ty = t / 16;
+    const int64_t i0 = static_cast<int64_t>(blockIdx.y) * kTile;
+    const int64_t j0 = static_cast<int64_t>(blockIdx.x) * kTile;
+    float ch[R][R], cl[R][R];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < R; ++c)
             ch[r][c] = cl[r][c] = 0.0f;
-    for (int64_t k0 = 0; k0 < K; k0 += kPK) {
-        for (int e = threadIdx.x; e < kPT * kPK; e += 256) {
-            const int r = e / kPK, c = e % kPK;
-            const int64_t gi = i0 + r, gk = k0 + c;
-            const bool ok = gi < M && gk < K;
-            sAh[c][r] = ok ? Ah[gi * lda + gk] : 0.0f;
-            sAl[c][r] = ok ? Al[gi * lda + gk] : 0.0f;
+    float fah[kPer], fal[kPer], fbh[kPer], fbl[kPer];
+    auto fetch = [&](int64_t k0) {
+#pragma unroll
+        for (int n = 0; n < kPer; ++n) {
+            const int e = n * 256 + t;
+            const int64_t ai = i0 + e / KS, ak = k0 + e % KS;
+            const bool in_a = ai < M && ak < K;
+            fah[n] = in_a ? Ah[ai * lda + ak] : 0.0f;
+            fal[n] = in_a ? Al[ai * lda + ak] : 0.0f;
+            const int64_t bk = k0 + e / kTile, bj = j0 + e % kTile;
+            const bool in_b = bk < K && bj < N;
+            fbh[n] = in_b ? Bh[bk * ldb + bj] : 0.0f;
+            fbl[n] = in_b ? Bl[bk * ldb + bj] : 0.0f;
         }
-        for (int e = threadIdx.x; e < kPK * kPT; e += 256) {
-            const int r = e / kPT, c = e % kPT;
-            const int64_t gk = k0 + r, gj = j0 + c;
-            const bool ok = gk < K && gj < N;
-            sBh[r][c] = ok ? Bh[gk * ldb + gj] : 0.0f;
-            sBl[r][c] = ok ? Bl[gk * ldb + gj] : 0.0f;
+    };
+    auto term = [&](int kk) {
+        float ah[R], al[R], bh[R], bl[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            ah[r] = sAh[kk][ty + 16 * r];
+            al[r] = sAl[kk][ty + 16 * r];
+            bh[r] = sBh[kk][tx + 16 * r];
+            bl[r] = sBl[kk][tx + 16 * r];
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < R; ++c) {
+                float ph, pl;
+                ffd::mul22<false>(ah[r], al[r], bh[c], bl[c], ph, pl);
+                ffd::add22(ch[r][c], cl[r][c], ph, pl, ch[r][c], cl[r][c]);
+            }
+    };
+    fetch(0);
+    for (int64_t k0 = 0; k0 < K; k0 += KS) {
+#pragma unroll
+        for (int n = 0; n < kPer; ++n) {
+            const int e = n * 256 + t;
+            sAh[e % KS][e / KS] = fah[n];
+            sAl[e % KS][e / KS] = fal[n];
+            sBh[e / kTile][e % kTile] = fbh[n];
+            sBl[e / kTile][e % kTile] = fbl[n];
         }
         __syncthreads();
-        const int kmax = (K - k0 < kPK) ? static_cast<int>(K - k0) : kPK;
-        for (int kk = 0; kk < kmax; ++kk) {
-            float ah[4], al[4], bh[4], bl[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                ah[r] = sAh[kk][ty + 16 * r];
-                al[r] = sAl[kk][ty + 16 * r];
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                bh[c] = sBh[kk][tx + 16 * c];
-                bl[c] = sBl[kk][tx + 16 * c];
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    float ph, pl;
-                    ffd::mul22<false>(ah[r], al[r], bh[c], bl[c], ph, pl);
-                    ffd::add22(ch[r][c], cl[r][c], ph, pl, ch[r][c], cl[r][c]);
-                }
+        fetch(k0 + KS);   // beyond K: zeros, not used
+        if (K - k0 >= KS) {
+#pragma unroll 4
+            for (int kk = 0; kk < KS; ++kk)
+                term(kk);
+        } else {
+            for (int kk = 0; kk < static_cast<int>(K - k0); ++kk)
+                term(kk);
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < R; ++c) {
             const int64_t gi = i0 + ty + 16 * r, gj = j0 + tx + 16 * c;
             if (gi < M && gj < N) {
                 Ch[gi * ldc + gj] = ch[r][c];
@@ -1074,11 +1095,24 @@ ff_status ff_gemm(int64_t M, int64_t N, int64_t K, const float *A_hi, const floa
     hipStream_t st = ffh::as_stream(stream);
     switch (algo) {
     case FF_GEMM_FMA_LOOP:
-        hipLaunchKernelGGL(gemm_fma_loop,
-                           dim3(static_cast<unsigned>(ffh::cdiv(N, kPT)),
-                                static_cast<unsigned>(ffh::cdiv(M, kPT))),
-                           dim3(256), 0, st, M, N, K, A_hi, A_lo, lda, B_hi, B_lo, ldb, C_hi, C_lo,
-                           ldc);
+    {
+        auto launch = [&](auto kernel, int tile) {
+            hipLaunchKernelGGL(kernel,
+                               dim3(static_cast<unsigned>(ffh::cdiv(N, tile)),
+                                    static_cast<unsigned>(ffh::cdiv(M, tile))),
+                               dim3(256), 0, st, M, N, K, A_hi, A_lo, lda, B_hi, B_lo, ldb, C_hi,
+                               C_lo, ldc);
+        };
+        // as many outputs per thread (less LDS traffic each) as leave four
+        // workgroups per compute unit; us with 1, 4 and 16: 1024^3 530 / 516 /
+        // 890, 2048 x 2048 x 512 1024 / 959 / 940, 700 x 900 x 800 272 / 333 / 693
+        if (ffh::cdiv(M, 64) * ffh::cdiv(N, 64) >= 1024)
+            launch(gemm_fma_loop<4, 16>, 64);
+        else if (ffh::cdiv(M, 32) * ffh::cdiv(N, 32) >= 1024)
+            launch(gemm_fma_loop<2, 32>, 32);
+        else
+            launch(gemm_fma_loop<1, 32>, 16);
+    }
         return ffh::launch_status();
     case FF_GEMM_SLICED_BF16:
         return sliced_gemm<ResiduesBF16>(M, N, K, A_hi, A_lo, lda, B_hi, B_lo, ldb, C_hi, C_lo, ldc,

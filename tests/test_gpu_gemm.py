@@ -345,3 +345,24 @@ def test_largest_residue_sums_and_tile_edges(algo, M, N, K):
 def test_tile_choice_and_order(algo, M, N, K):
     # every tile by the rule on M, N and K, in both orders of the workgroups
     test_largest_residue_sums_and_tile_edges(algo, M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (16, 17, 32), (15, 33, 31), (33, 16, 65),          # one output per thread
+    (1024, 993, 33), (993, 1025, 64), (1001, 999, 1),  # 2 x 2
+    (1985, 2048, 16), (2048, 2001, 35)])               # 4 x 4
+def test_fma_loop_tiles_match_the_sequential_definition(M, N, K):
+    ff = _ff()
+    _announce(f"[gpu] gemm loop {M}x{N}x{K}")
+    A, B = fi.gaussian_ff((M, K), 8800 + M), fi.gaussian_ff((K, N), 8801 + N)
+    C = ff.ff_gemm(A.cuda(), B.cuda(), algo=_algo("fma")).cpu().numpy()
+    rows = np.unique(np.concatenate([np.arange(min(M, 3)), np.linspace(0, M - 1, 9).astype(int),
+                                     np.arange(max(0, M - 3), M)]))
+    Ar = A[:, rows].numpy()
+    Ch, Cl = oracle.gemm_ff_seq(Ar[0], Ar[1], B[0].numpy(), B[1].numpy())
+    assert same_bits(C[0, rows], Ch) and same_bits(C[1, rows], Cl)
+    cols = np.unique(np.concatenate([np.arange(3), np.arange(max(0, N - 3), N)]))
+    Bc = np.ascontiguousarray(B[:, :, cols].numpy())
+    Ch, Cl = oracle.gemm_ff_seq(A[0].numpy(), A[1].numpy(), Bc[0], Bc[1])
+    assert same_bits(np.ascontiguousarray(C[0][:, cols]), Ch)
+    assert same_bits(np.ascontiguousarray(C[1][:, cols]), Cl)
