@@ -26,8 +26,8 @@
  *           propagate as IEEE arithmetic makes them, and division by zero
  *           gives IEEE infinities/NaN (not a meaningful float-float value).
  * Alignment Float pointers must be 4-byte aligned (FF_ERR_ALIGN otherwise).
- *           Where an entry point has a float4 path for 16-byte aligned
- *           planes, its comment says when that path runs.
+ *           Where an entry point has a float4 path, its comment says when
+ *           that path runs.
  * Aliasing  Elementwise entry points (the float-float operators, ff_copy,
  *           the paper's stream operators, the polynomial evaluators) allow
  *           an output plane to be the same array as an input plane (in
@@ -89,8 +89,8 @@ const char *ff_last_error(void);
 /*     (r_hi[i], r_lo[i]) = OP((a_hi[i], a_lo[i]), (b_hi[i], b_lo[i]))      */
 /* All six planes (four in, two out) hold n binary32 values.  Results are  */
 /* bit-identical to the documented binary32 operation sequence, whatever   */
-/* the alignment and launch form (float4 groups below 2^24 elements when   */
-/* every plane is 16-byte aligned, 4-byte accesses otherwise).  Errors:    */
+/* the alignment and launch form (float4 groups below 2^24 elements, 4-byte */
+/* accesses from there on).  Errors:                                       */
 /* FF_ERR_SIZE (n < 0), FF_ERR_NULL (a NULL plane, n > 0), FF_ERR_ALIGN,   */
 /* FF_ERR_HIP.                                                              */
 /* ------------------------------------------------------------------------ */
@@ -506,9 +506,8 @@ ff_status ff_gemm(int64_t M, int64_t N, int64_t K, const float *A_hi,
  *                    "Mad"; gfx950 has no unfused binary32 multiply-add)
  * All pointers: device, caller-owned, n binary32 words each; an output may
  * alias an input exactly (in place), partial overlap is undefined.  Below
- * 2^24 elements, when every pointer is 16-byte aligned, a float4 path runs;
- * otherwise 4-byte accesses, one lane-contiguous element per lane and
- * plane at a time.  Results do not depend on the path.
+ * 2^24 elements a float4 path runs; otherwise 4-byte accesses, one
+ * lane-contiguous element per lane and plane at a time.  Results do not depend on the path.
  * Errors: FF_ERR_SIZE (n < 0), FF_ERR_NULL, FF_ERR_ALIGN (a pointer not
  * 4-byte aligned), FF_ERR_HIP.  n = 0 is a no-op. */
 ff_status ff_add12(const float *a, const float *b, float *s, float *r,

@@ -232,3 +232,37 @@ def test_last_lane_of_the_float4_form(op, n):
     gpu_op(op, da, db, out=out)
     assert_parity(op, da, db, out, f"n={n}")
     assert torch.all(base[:, n:] == 7.0)
+
+
+@pytest.mark.parametrize("op", ["add", "div_accurate"])
+@pytest.mark.parametrize("n", [1, 3, 4, 1022, 1025, 70001])
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_float4_form_at_any_alignment(op, n, shift):
+    # the six planes start at different words past 16-byte alignment; the
+    # words around the outputs stay untouched, in place as well
+    ff = _ff()
+    _announce(f"[gpu] elementwise any alignment n={n} shift={shift} op={op}")
+    a, b, _ = fi.mixed_ff_pair(n, 1300 + n)
+
+    def place(t, k):
+        pitch = -(-n // 4) * 4 + 8 + k          # hi at k words, lo at pitch + k words
+        base = torch.full((2, pitch), 7.0, device="cuda")
+        view = base[:, k:k + n]
+        if t is not None:
+            view.copy_(t)
+        return base, view
+
+    _, da = place(a, shift)
+    _, db = place(b, (shift + 1) % 4)
+    base, out = place(None, (2 * shift) % 4)
+    want = ff.ff_empty((n,))
+    ga, gb = ff.ff_empty((n,)), ff.ff_empty((n,))
+    ga.copy_(a)
+    gb.copy_(b)
+    gpu_op(op, da, db, out=out)
+    assert_parity(op, ga, gb, out, f"n={n} shift={shift}")
+    k = (2 * shift) % 4
+    assert torch.all(base[:, :k] == 7.0) and torch.all(base[:, k + n:] == 7.0)
+    gpu_op(op, ga, gb, out=want)
+    gpu_op(op, da, db, out=da)
+    assert torch.equal(da.view(torch.int32), want.view(torch.int32))
