@@ -809,7 +809,7 @@ def ff_gemm(A: torch.Tensor, B: torch.Tensor, algo: int = GEMM_SLICED_I8, out=No
     dynamic range (normal(0,1) data at 4096^3: 2^-51.6), with the general bound
     in include/ff.h otherwise.  For rows or columns whose
     small entries matter 2^40 below their largest, use GEMM_FMA_LOOP (the
-    plain Add22/Mul22 loop, about 17 times slower at 4096^3)."""
+    plain Add22/Mul22 loop, about 25 times slower at 4096^3)."""
     M, K, lda = _check_matrix(A)
     K2, N, ldb = _check_matrix(B)
     if K2 != K:
