@@ -552,8 +552,8 @@ ff_status ff_f32_mad(const float *a, const float *b, const float *c, float *r,
  * x / x_hi (non-null) and x_lo (null: binary32 points); y / y_hi, y_lo
  * (non-null).  All device pointers, caller-owned, 4-byte aligned; the float4
  * path runs above 2^17 points (binary32, compensated) or 2^18 (float-float),
- * for binary32 also below degree 16, when every point and result plane is
- * 16-byte aligned, one point per lane otherwise; results do not depend on it.
+ * from degree 16 on above 786432 (compensated, float-float), for binary32 also
+ * below degree 16; one point per lane otherwise; results do not depend on it.
  * A result plane may alias a point plane exactly (in place); coefficients
  * must not alias a result.
  * Errors: FF_ERR_NULL, FF_ERR_SIZE (degree < 0 or n < 0), FF_ERR_ALIGN,

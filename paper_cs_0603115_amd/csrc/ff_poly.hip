@@ -28,7 +28,8 @@
 
 namespace ffk {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// 16-byte accesses at any 4-byte alignment
+typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kPolyBlock = 256;
 
@@ -48,12 +49,21 @@ struct PolyArgs {
 // against four): float-float 3.2 / 6.5 at 1000 points and degree 25, 5.1 / 7.2
 // at 2^18; compensated 2.5 / 3.9 and 2.8 / 4.2 at 2^17, but 2.6 / 2.5 at 2^18
 // and degree 5; binary32 2.2 / 2.5 at 1000 and degree 25, but 2.2 / 2.2 at
-// degree 5 and 3.2 / 2.8 at 2^18.
+// degree 5 and 3.2 / 2.8 at 2^18.  Long recurrences (degree 16 on) keep this
+// form up to kMorePoints: float-float 7.0 / 7.5 at 400000 points and degree 25,
+// 11.2 / 13.1 at 800000, but 4.4 / 4.2 at 600000 and degree 5; compensated 4.8 /
+// 6.0 at 2^19 and degree 25, but 4.1 / 3.6 at 800000 and degree 5.
+// Planes off 16-byte alignment take the same forms: at 2^26 + 1 points and degree
+// 25 one point per lane took 364 / 396 / 776 us (binary32, compensated,
+// float-float), four take 96 / 290 / 712.
 //
+constexpr int kMoreDegree = 16;
+
 // Horner's rule in binary32: s = (s (x) x) (+) c_i, two roundings per step.
 struct HornerF32 {
     static constexpr bool kFF = false;
     static constexpr int64_t kFewPoints = int64_t(1) << 17;
+    static constexpr int64_t kMorePoints = 0;
     static constexpr int kFewDegree = 16;
     struct State { float s; };
     __device__ __forceinline__ static void init(State &st, float ch, float) { st.s = ch; }
@@ -72,6 +82,7 @@ struct HornerF32 {
 struct HornerComp {
     static constexpr bool kFF = false;
     static constexpr int64_t kFewPoints = int64_t(1) << 17;
+    static constexpr int64_t kMorePoints = 3 << 18;
     static constexpr int kFewDegree = 0;
     struct State { float s, r; };
     __device__ __forceinline__ static void init(State &st, float ch, float)
@@ -96,6 +107,7 @@ struct HornerComp {
 struct HornerFF {
     static constexpr bool kFF = true;
     static constexpr int64_t kFewPoints = int64_t(1) << 18;
+    static constexpr int64_t kMorePoints = 3 << 18;
     static constexpr int kFewDegree = 0;
     struct State { float h, l; };
     __device__ __forceinline__ static void init(State &st, float ch, float cl)
@@ -178,7 +190,7 @@ __global__ __launch_bounds__(kPolyBlock) void horner_vec(PolyArgs a, int64_t n)
     }
 }
 
-// One point per lane: few points, and planes that are not 16-byte aligned.
+// One point per lane: few points.
 template <class Alg, bool CLO, bool XLO>
 __global__ __launch_bounds__(kPolyBlock) void horner_scalar(PolyArgs a, int64_t n)
 {
@@ -228,15 +240,11 @@ ff_status horner(PolyArgs a, int64_t n, void *stream_ptr)
     if (!a.ch || !a.xh || !a.yh || (Alg::kFF && !a.yl))
         return FF_ERR_NULL;
     const void *planes[] = {a.ch, a.cl, a.xh, a.xl, a.yh, Alg::kFF ? a.yl : nullptr};
-    bool vec = n > Alg::kFewPoints || a.degree < Alg::kFewDegree;
-    for (const void *p : planes) {
-        if (!p)
-            continue;
-        if (!ffh::aligned(p, 4))
+    const bool vec = !(n <= Alg::kFewPoints && a.degree >= Alg::kFewDegree) &&
+                     !(n <= Alg::kMorePoints && a.degree >= kMoreDegree);
+    for (const void *p : planes)
+        if (p && !ffh::aligned(p, 4))
             return FF_ERR_ALIGN;
-        if (p != a.ch && p != a.cl)
-            vec = vec && ffh::aligned(p, 16);
-    }
     hipStream_t st = ffh::as_stream(stream_ptr);
     if constexpr (!Alg::kFF)
         return launch_horner<Alg, false, false>(a, n, vec, st);

@@ -190,3 +190,24 @@ def test_four_points_per_lane_and_its_last_lane(algo, n):
         dev.copy_(pts)
     got = _gpu(algo, coef.cuda(), dev)
     _check(got, _want(algo, coef.numpy(), pts.numpy()), f"{algo} n={n}")
+
+
+@pytest.mark.parametrize("algo", ["f32", "comp", "ff"])
+@pytest.mark.parametrize("degree,n", [(3, 50001), (3, 300002), (16, 300003), (15, 300005),
+                                      (16, 786432), (17, 786433)])
+def test_points_and_degrees_choose_the_form_at_any_alignment(algo, degree, n):
+    # both sides of the lines in points and degree, every plane 4 or 8 bytes
+    # past 16-byte alignment; the words around the results stay untouched
+    _announce(f"[gpu] horner {algo} degree={degree} n={n} off alignment")
+    coef = fi.random_poly(degree, 1911, ff=(algo == "ff"))
+    x = fi.horner_points(n, 1912, -1.2, 1.2)
+    pts = torch.stack([x, 1e-9 * x]) if algo == "ff" else x
+    shape = (2, n + 8) if algo == "ff" else (n + 8,)
+    dev = torch.zeros(shape, device="cuda")[..., 1:n + 1]
+    dev.copy_(pts)
+    base = torch.full(shape, 7.0, device="cuda")
+    fn = {"f32": _ff().ff_horner_f32, "comp": _ff().ff_horner_comp, "ff": _ff().ff_horner_ff}[algo]
+    got = fn(coef.cuda(), dev, out=base[..., 2:n + 2])
+    torch.cuda.synchronize()
+    assert torch.all(base[..., :2] == 7.0) and torch.all(base[..., n + 2:] == 7.0)
+    _check(got.cpu().numpy(), _want(algo, coef.numpy(), pts.numpy()), f"{algo} off alignment")
