@@ -18,7 +18,7 @@
 // Each modulus is one plain integer GEMM on matrix cores,
 //   * int8 residues, v_mfma_i32_32x32x32_i8, int32 accumulation;
 //   * BF16 residues (integers |r| <= 128 are exact in BF16),
-//     v_mfma_f32_32x32x16_bf16, FP32 accumulation reduced mod m every 512 k,
+//     v_mfma_f32_32x32x16_bf16, FP32 accumulation reduced mod m every 640 k,
 //     before any partial sum can exceed 2^24,
 // its sums are reduced mod m to one byte per output and modulus, and a last
 // pass puts the sixteen bytes of an output together to the 128-bit integer
@@ -625,8 +625,7 @@ __global__ __launch_bounds__(256, TM * TN == 16 ? 1 : 2) void gemm_residues(
     auto fold = [&](int block, int r) {
         if constexpr (Dg::kFoldStages > 0) {
             const float c = acc[block / TN][block % TN][r];
-            const float n = __builtin_fmaf(c, inv, kRoundMagic) - kRoundMagic;
-            acc[block / TN][block % TN][r] = __builtin_fmaf(n, -static_cast<float>(m), c);
+            acc[block / TN][block % TN][r] = reduce_float(c, m, inv);
         }
     };
 
@@ -759,11 +758,7 @@ __global__ __launch_bounds__(256, TM * TN == 16 ? 1 : 2) void gemm_residues(
     // the two reductions for all 256 sums ahead of the branch, which would
     // hold them in as many registers again)
     if constexpr (Dg::kFoldStages > 0)
-        store([&](float c) {
-            const float t = __builtin_fmaf(c, inv, kRoundMagic);
-            return static_cast<uint32_t>(static_cast<int>(c)) +
-                   static_cast<uint32_t>(times24(t, -m));
-        });
+        store([&](float c) { return residue_of_float(c, m, inv); });
     else if (exact || m > 244)
         store([&](int c) {
             asm volatile("; two steps" : "+v"(c));

@@ -111,27 +111,46 @@ __device__ __forceinline__ int dot4(uint32_t a, uint32_t b, int c)
 // 1.5 2^23: the float and its 23 low bits 2^22 + q.
 constexpr float kRoundMagic = 12582912.0f;
 
-__device__ __forceinline__ int times24(float t, int neg_m)
+__host__ __device__ __forceinline__ int times24(float t, int neg_m)
 {
     // (2^22 + q) (-m) as a 24-bit product (one multiply-add with the sum):
     // the low 24 bits of the float hold 2^22 + q with bit 23 clear
-    const int n = static_cast<int>(__float_as_uint(t) << 8) >> 8;
+    const int n = static_cast<int>(__builtin_bit_cast(uint32_t, t) << 8) >> 8;
     return static_cast<int>(static_cast<uint32_t>(n) *
                             static_cast<uint32_t>((neg_m << 8) >> 8));
 }
 
 // s - q m for q = the integer nearest fl(fl(s) / m), in the low byte of the
 // result (the magic number adds 2^22 m, a multiple of 256).  |s| < 2^22 m.
-__device__ __forceinline__ uint32_t reduce_low_byte(int s, int m, float inv)
+__host__ __device__ __forceinline__ uint32_t reduce_low_byte(int s, int m, float inv)
 {
     const float t = __builtin_fmaf(static_cast<float>(s), inv, kRoundMagic);
     return static_cast<uint32_t>(s) + static_cast<uint32_t>(times24(t, -m));
 }
 
 // The same difference itself, as a signed integer.
-__device__ __forceinline__ int reduce_once(int s, int m, float inv)
+__host__ __device__ __forceinline__ int reduce_once(int s, int m, float inv)
 {
     return static_cast<int>(reduce_low_byte(s, m, inv) + (static_cast<uint32_t>(m) << 22));
+}
+
+// The same for an integer c that a binary32 sum holds, |c| < 2^24: the
+// difference is exact in binary32 too.
+__host__ __device__ __forceinline__ float reduce_float(float c, int m, float inv)
+{
+    const float n = __builtin_fmaf(c, inv, kRoundMagic) - kRoundMagic;
+    return __builtin_fmaf(n, -static_cast<float>(m), c);
+}
+
+// The residue of such a sum in the low byte.  Reduced twice: 1 / m in binary32
+// is off by up to 2^-24 of itself, so that one reduction of a c above 2^23 can
+// take the quotient next to the nearest and leave 128 (255 = m, c = -8454907),
+// which no signed byte holds; of a difference that small the second is exact.
+__host__ __device__ __forceinline__ uint32_t residue_of_float(float c, int m, float inv)
+{
+    c = reduce_float(c, m, inv);
+    const float t = __builtin_fmaf(c, inv, kRoundMagic);
+    return static_cast<uint32_t>(static_cast<int>(c)) + static_cast<uint32_t>(times24(t, -m));
 }
 
 // A sum s of digit products, |s| < 2^17, read from the integer that an
@@ -172,17 +191,17 @@ constexpr BiasedTable kBiased = make_biased_table();
 // moves a quotient over one half.  It stays within [-128, 127]: only 255 has no
 // room above its largest balanced residue, and 1 / 255 rounds up, which moves
 // quotients up and residues down.
-__device__ __forceinline__ uint32_t residue_from_biased(int v, const BiasedModulus &b)
+__host__ __device__ __forceinline__ uint32_t residue_from_biased(int v, const BiasedModulus &b)
 {
-    const float t = __builtin_fmaf(__int_as_float(v), b.inv, b.offset);
+    const float t = __builtin_fmaf(__builtin_bit_cast(float, v), b.inv, b.offset);
     return static_cast<uint32_t>(v) + static_cast<uint32_t>(times24(t, b.neg_m));
 }
 
 // The same residue as a float.
-__device__ __forceinline__ float residue_float_from_biased(int v, const BiasedModulus &b)
+__host__ __device__ __forceinline__ float residue_float_from_biased(int v, const BiasedModulus &b)
 {
-    const float s = __int_as_float(v) - b.base;
-    const float n = __builtin_fmaf(__int_as_float(v), b.inv, b.offset) - kRoundMagic;
+    const float x = __builtin_bit_cast(float, v), s = x - b.base;
+    const float n = __builtin_fmaf(x, b.inv, b.offset) - kRoundMagic;
     return __builtin_fmaf(n, static_cast<float>(b.neg_m), s);
 }
 

@@ -366,3 +366,55 @@ def test_fma_loop_tiles_match_the_sequential_definition(M, N, K):
     Ch, Cl = oracle.gemm_ff_seq(A[0].numpy(), A[1].numpy(), Bc[0], Bc[1])
     assert same_bits(np.ascontiguousarray(C[0][:, cols]), Ch)
     assert same_bits(np.ascontiguousarray(C[1][:, cols]), Cl)
+
+
+def _residue_operand(n, seed):
+    """n float-float numbers 0.75 + t 2^-54 (fixed-point integer 3 2^52 + t):
+    number i has, modulo modulus i % 16, one of the residues farthest from
+    zero, of either sign."""
+    moduli = [256, 255, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217, 211, 199, 197, 193]
+    rng = np.random.default_rng(seed)
+    t = np.empty(n, dtype=np.int64)
+    for i in range(n):
+        m = moduli[i % 16]
+        r = m // 2 - (i // 32) % 4
+        t[i] = ((r if i // 16 % 2 else -r) - 3 * 2 ** 52) % m + m * int(rng.integers(0, 1 << 15))
+    x = np.empty((2, n), dtype=np.float32)
+    x[0], x[1] = 0.75, np.ldexp(t.astype(np.float64), -54)
+    assert np.all(x[1].astype(np.float64) == np.ldexp(t.astype(np.float64), -54))
+    return x
+
+
+@pytest.mark.parametrize("algo,M,N,K", [
+    # BF16: as many k as pass between two reductions of a sum, every tile
+    ("bf16", 128, 128, 640), ("bf16", 128, 128, 656), ("bf16", 128, 128, 703),
+    ("bf16", 128, 128, 763), ("bf16", 512, 512, 656), ("bf16", 512, 512, 763),
+    ("bf16", 1000, 1000, 763), ("bf16", 1024, 1024, 719), ("bf16", 2048, 2048, 2033),
+    ("bf16", 128, 128, 16385),
+    # int8: both ends of one and two reductions of a sum
+    ("i8", 128, 128, 4095), ("i8", 128, 128, 4096), ("i8", 128, 128, 4097),
+    ("i8", 512, 512, 4096), ("i8", 1024, 1024, 4096), ("i8", 128, 128, 16384)])
+def test_sums_of_the_farthest_residues(algo, M, N, K):
+    # constant rows a_i and columns b_j: C_ij = K a_i b_j, the integer product
+    # is exact, and the final rounding is at most 2^-48 |C_ij| (per chunk of
+    # 16384 k, and the sum of two chunks 2^-44).  Rows and columns repeat
+    # after 128, so that every tile and position sees the same 128 x 128.
+    _announce(f"[gpu] gemm farthest residues {M}x{N}x{K} ({algo})")
+    a, b = _residue_operand(128, 8500 + K), _residue_operand(128, 8501 + K)
+    a[:, ::3] *= -1
+    row, col = torch.arange(M) % 128, torch.arange(N) % 128
+    A = torch.from_numpy(a).cuda()[:, row, None].expand(2, M, K).contiguous()
+    B = torch.from_numpy(b).cuda()[:, None, col].expand(2, K, N).contiguous()
+    C = _ff().ff_gemm(A, B, algo=_algo(algo))
+    first = C[:, :128, :128].contiguous()
+    got = first.cpu().numpy()
+    fa = [K * (frac(a[0, i]) + frac(a[1, i])) for i in range(128)]
+    fb = [frac(b[0, j]) + frac(b[1, j]) for j in range(128)]
+    part = 1 << (48 if K <= 16384 else 44)
+    for i in range(128):
+        for j in range(128):
+            exact = fa[i] * fb[j]
+            err = abs(frac(got[0, i, j]) + frac(got[1, i, j]) - exact)
+            assert err * part <= abs(exact), (i, j, float(err / exact))
+    repeated = first.view(torch.int32)[:, row.cuda()][:, :, col.cuda()]
+    assert torch.equal(C.view(torch.int32), repeated)
