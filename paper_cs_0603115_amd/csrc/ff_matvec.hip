@@ -51,9 +51,16 @@ inline int64_t band_rows_of(int64_t M, int64_t N)
 // Fast forward: RT consecutive threads per group of R rows.  The rows share
 // each load of x, and each lane issues the loads of kRowUnroll float4 groups
 // (all rows' planes and x) before any arithmetic.
+//
+// SHORT, for rows of few rounds: the words after the last whole group are loaded
+// first, and the last round's second group, where it lies past the end, is the
+// last one loaded again and not added.  Loaded as they come they made a short
+// row wait for memory up to three times (64 x 1023: 4.5 us, 3.3 now; 1600 x 1030:
+// 7.2, 5.6); with many rounds, or two rows, the other loop has fewer operations
+// and registers (1536 x 2049 with two rows 6.8 us, 7.5 with the loads first).
 constexpr int kRowUnroll = 2;
 
-template <int BLOCK, int RT, int R>
+template <int BLOCK, int RT, int R, bool SHORT>
 __global__ __launch_bounds__(BLOCK) void matvec_rows(int64_t M, int64_t N,
                                                      const float *__restrict__ Ah,
                                                      const float *__restrict__ Al, int64_t lda,
@@ -86,47 +93,76 @@ __global__ __launch_bounds__(BLOCK) void matvec_rows(int64_t M, int64_t N,
     const int64_t ng = N >> 2;
     const f32x4 *xh4 = reinterpret_cast<const f32x4 *>(xh);
     const f32x4 *xl4 = reinterpret_cast<const f32x4 *>(xl);
-    int64_t g = t;
-    for (; g + (U - 1) * RT < ng; g += U * RT) {
-        f32x4 bh[U], bl[U], ah[R][U], al[R][U];
+    const int64_t j_last = 4 * ng + t;
+    if constexpr (SHORT) {
+        static_assert(R == 1, "one row");
+        float word_bh, word_bl, word_ah, word_al;
+        if (j_last < N) {
+            word_bh = xh[j_last];
+            word_bl = xl[j_last];
+            word_ah = rh[0][j_last];
+            word_al = rl[0][j_last];
+        }
+        for (int64_t g = t; g < ng; g += U * RT) {
+            f32x4 bh[U], bl[U], ah[U], al[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            bh[u] = xh4[g + u * RT];
-            bl[u] = xl4[g + u * RT];
+            for (int u = 0; u < U; ++u) {
+                const int64_t at = g + u * RT < ng ? g + u * RT : ng - 1;
+                bh[u] = xh4[at];
+                bl[u] = xl4[at];
+                ah[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(rh[0]) + at);
+                al[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(rl[0]) + at);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u == 0 || g + u * RT < ng)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        add_term(0, k, ah[u][k], al[u][k], bh[u][k], bl[u][k]);
+        }
+        if (j_last < N)
+            add_term(0, 0, word_ah, word_al, word_bh, word_bl);
+    } else {
+        int64_t g = t;
+        for (; g + (U - 1) * RT < ng; g += U * RT) {
+            f32x4 bh[U], bl[U], ah[R][U], al[R][U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                bh[u] = xh4[g + u * RT];
+                bl[u] = xl4[g + u * RT];
+#pragma unroll
+                for (int q = 0; q < R; ++q) {
+                    ah[q][u] = __builtin_nontemporal_load(
+                        reinterpret_cast<const f32x4 *>(rh[q]) + g + u * RT);
+                    al[q][u] = __builtin_nontemporal_load(
+                        reinterpret_cast<const f32x4 *>(rl[q]) + g + u * RT);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < R; ++q)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        add_term(q, k, ah[q][u][k], al[q][u][k], bh[u][k], bl[u][k]);
+        }
+        for (; g < ng; g += RT) {
+            const f32x4 bh = xh4[g], bl = xl4[g];
 #pragma unroll
             for (int q = 0; q < R; ++q) {
-                ah[q][u] = __builtin_nontemporal_load(
-                    reinterpret_cast<const f32x4 *>(rh[q]) + g + u * RT);
-                al[q][u] = __builtin_nontemporal_load(
-                    reinterpret_cast<const f32x4 *>(rl[q]) + g + u * RT);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int q = 0; q < R; ++q)
+                const f32x4 ah =
+                    __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(rh[q]) + g);
+                const f32x4 al =
+                    __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(rl[q]) + g);
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    add_term(q, k, ah[q][u][k], al[q][u][k], bh[u][k], bl[u][k]);
-    }
-    for (; g < ng; g += RT) {
-        const f32x4 bh = xh4[g], bl = xl4[g];
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            const f32x4 ah =
-                __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(rh[q]) + g);
-            const f32x4 al =
-                __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(rl[q]) + g);
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                add_term(q, k, ah[k], al[k], bh[k], bl[k]);
+                    add_term(q, k, ah[k], al[k], bh[k], bl[k]);
+            }
         }
-    }
-    if (4 * ng + t < N) {
-        const int64_t j = 4 * ng + t;
+        if (j_last < N)
 #pragma unroll
-        for (int q = 0; q < R; ++q)
-            add_term(q, 0, rh[q][j], rl[q][j], xh[j], xl[j]);
+            for (int q = 0; q < R; ++q)
+                add_term(q, 0, rh[q][j_last], rl[q][j_last], xh[j_last], xl[j_last]);
     }
     float h[R], l[R];
 #pragma unroll
@@ -665,21 +701,31 @@ ff_status ff_matvec(int64_t M, int64_t N, const float *A_hi, const float *A_lo, 
         };
         // As many threads per row as it feeds with a few float4 groups each, one
         // row per group of threads, two where there are rows enough for 512
-        // workgroups.  us, chosen against 256 threads by two rows: 16384 x 64
-        // 3.4 / 18.0, 16384 x 512 11.9 / 21.8 (16 threads); 1024 x 1024 3.8 /
-        // 4.2, 16384 x 1000 24.1 / 27.8 (64); 300 x 5000 5.9 / 7.1, 64 x 16384
-        // 7.4 / 13.5 (512); 1000 x 1531 5.2-5.7 / 5.3-5.7 (256, one row); and
-        // for two rows against one 1000 x 16384 23.9 / 27.3, 8192 x 8192 81 / 90.
-        if (N <= 128 || (N <= 512 && M >= 4096))
-            launch(matvec_rows<256, 16, 1>, 256, 16);
-        else if (N <= 1024 || (N <= 2048 && M >= 2048))
-            launch(matvec_rows<256, 64, 1>, 256, 4);
+        // workgroups.  From 2048 rows on, us against 256 threads by two rows: 16384
+        // x 64 3.4 / 18.0, 16384 x 512 11.9 / 21.8 (16 threads); 16384 x 1000 24.1 /
+        // 27.8 (64); and for two rows against one 1000 x 16384 23.9 / 27.3, 8192 x
+        // 8192 81 / 90.  Below, us with the matrix cached (from HBM) against the next
+        // best: 64 x 127 2.8 (2.5), 64 threads 3.0 (2.8); 500 x 257 3.2 (3.3), 128
+        // threads 3.3 (3.4); 500 x 511 3.4 (3.6), 256 threads 3.5 (3.7); 1600 x 3001
+        // 9.2 (9.5), 256 threads 10.7 (10.3); 768 x 1023 4.2 (4.3), 128 threads 4.4
+        // (4.5); 1000 x 8191 13.6 (14.3), 128 threads 15.6 (16.7); 64 x 16384 7.4
+        // with 512 threads, 13.5 with 256.
+        if (M < 2048 && N <= 128)
+            launch(matvec_rows<256, 32, 1, true>, 256, 8);
+        else if (M < 2048 && N <= 288)
+            launch(matvec_rows<256, 64, 1, true>, 256, 4);
+        else if (M < 1280 ? N <= 512 : M < 2048 && N > 512 && N <= 8192)
+            launch(matvec_rows<128, 128, 1, true>, 128, 1);
+        else if (M < 1280 && (N <= 1024 || (M >= 768 && N <= 8192)))
+            launch(matvec_rows<256, 256, 1, true>, 256, 1);
         else if (M < 768)
-            launch(matvec_rows<512, 512, 1>, 512, 1);
-        else if (M < 1536 && N <= 8192)
-            launch(matvec_rows<256, 256, 1>, 256, 1);
+            launch(matvec_rows<512, 512, 1, false>, 512, 1);
+        else if (M >= 2048 && (N <= 128 || (N <= 512 && M >= 4096)))
+            launch(matvec_rows<256, 16, 1, false>, 256, 16);
+        else if (N <= 512 || (M >= 2048 && N <= 2048))
+            launch(matvec_rows<256, 64, 1, false>, 256, 4);
         else
-            launch(matvec_rows<256, 256, 2>, 256, 2);
+            launch(matvec_rows<256, 256, 2, false>, 256, 2);
     }
     return ffh::launch_status();
 }

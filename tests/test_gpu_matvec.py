@@ -428,3 +428,29 @@ def test_backward_takes_every_row_once(M, N):
     assert torch.equal(dx[0].double(), (g[0].double()[:, None] * A[0].double()).sum(0))
     assert torch.equal(dA[0], g[0][:, None] * x[0][None, :])
     assert not dx[1].any() and not dA[1].any()
+
+
+# one shape on each side of every line between the forms of short rows, whose
+# last round loads past its end, and row lengths of every remainder mod 4
+@pytest.mark.parametrize("M,N", [
+    (1, 4), (3, 7), (9, 127), (70, 129), (33, 257), (33, 288), (50, 289), (1279, 512), (1280, 511),
+    (1281, 289), (1100, 767), (767, 1023), (767, 1025), (768, 1030), (1279, 1027), (1280, 513),
+    (1280, 1026), (2047, 1029), (2047, 130), (2048, 126), (2048, 515), (768, 8192), (60, 8195),
+    (1300, 8193)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_forward_at_the_edges_of_short_rows(M, N, shift):
+    # shift 1: planes and rows start 4 bytes past 16-byte alignment, rows are
+    # padded, and NaN fills what surrounds them, so that a word read past a row
+    # and used shows
+    ff = _ff()
+    _announce(f"[gpu] matvec short rows {M}x{N} shift {shift}")
+    A, x = fi.gaussian_ff((M, N), 6400 + M), fi.gaussian_ff((N,), 6401 + N)
+    wide = torch.full((2, M, N + 5 * shift), math.nan, device="cuda")
+    Ad = wide[:, :, shift:N + shift]
+    Ad.copy_(A)
+    xd = torch.full((2, N + 3), math.nan, device="cuda")[:, shift:N + shift]
+    xd.copy_(x)
+    y = ff.ff_matvec(Ad, xd)
+    rows = np.unique(np.linspace(0, M - 1, 24).astype(int))
+    check_rows_exact(A[:, rows], x, y[:, torch.from_numpy(rows).cuda()], f"y {M}x{N}")
+    assert torch.isfinite(y).all()
