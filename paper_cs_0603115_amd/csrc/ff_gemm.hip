@@ -757,18 +757,28 @@ __global__ __launch_bounds__(256, TM * TN == 16 ? 1 : 2) void gemm_residues(
     // (the empty assembly keeps the compiler from computing the part common to
     // the two reductions for all 256 sums ahead of the branch, which would
     // hold them in as many registers again)
-    if constexpr (Dg::kFoldStages > 0)
-        store([&](float c) { return residue_of_float(c, m, inv); });
-    else if (exact || m > 244)
+    if constexpr (Dg::kFoldStages > 0) {
+        if (m > 244)
+            store([&](float c) {
+                asm volatile("; two steps" : "+v"(c));
+                return residue_of_float_twice(c, m, inv);
+            });
+        else
+            store([&](float c) {
+                asm volatile("; one step" : "+v"(c));
+                return residue_of_float(c, m, inv);
+            });
+    } else if (exact || m > 244) {
         store([&](int c) {
             asm volatile("; two steps" : "+v"(c));
             return reduce_low_byte(reduce_once(c, m, inv), m, inv);
         });
-    else
+    } else {
         store([&](int c) {
             asm volatile("; one step" : "+v"(c));
             return reduce_low_byte(c, m, inv);
         });
+    }
 }
 
 // Transposes a register of each of four lane groups: on return r[w] of lane

@@ -142,15 +142,21 @@ __host__ __device__ __forceinline__ float reduce_float(float c, int m, float inv
     return __builtin_fmaf(n, -static_cast<float>(m), c);
 }
 
-// The residue of such a sum in the low byte.  Reduced twice: 1 / m in binary32
+// The residue of such a sum in the low byte, for m up to 244.  1 / m in binary32
 // is off by up to 2^-24 of itself, so that one reduction of a c above 2^23 can
-// take the quotient next to the nearest and leave 128 (255 = m, c = -8454907),
-// which no signed byte holds; of a difference that small the second is exact.
+// take the quotient next to the nearest; the difference then passes m / 2 by
+// less than 1, which a byte has room for.
 __host__ __device__ __forceinline__ uint32_t residue_of_float(float c, int m, float inv)
 {
-    c = reduce_float(c, m, inv);
     const float t = __builtin_fmaf(c, inv, kRoundMagic);
     return static_cast<uint32_t>(static_cast<int>(c)) + static_cast<uint32_t>(times24(t, -m));
+}
+
+// For every m: 255 has no room (c = -8454907 leaves 128), so the sum is reduced
+// before; of a difference that small the second quotient is the nearest.
+__host__ __device__ __forceinline__ uint32_t residue_of_float_twice(float c, int m, float inv)
+{
+    return residue_of_float(reduce_float(c, m, inv), m, inv);
 }
 
 // A sum s of digit products, |s| < 2^17, read from the integer that an

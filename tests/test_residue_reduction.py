@@ -33,7 +33,9 @@ int main(int argc, char **argv)
     if (!std::strcmp(argv[1], "float")) {         // FP32 sums, every one
         for (int s = -(1 << 24) + 1; s < 1 << 24; ++s) {
             const float c = static_cast<float>(s), f = reduce_float(c, m, inv);
-            check(holds(residue_of_float(c, m, inv), s, m), s);
+            check(holds(residue_of_float_twice(c, m, inv), s, m), s);
+            if (m <= 244)
+                check(holds(residue_of_float(c, m, inv), s, m), s);
             check(f >= -129.0f && f <= 129.0f && (static_cast<int64_t>(f) - s) % m == 0, s);
         }
     } else if (!std::strcmp(argv[1], "int")) {    // int32 sums next to the halves
