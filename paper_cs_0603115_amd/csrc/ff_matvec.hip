@@ -790,7 +790,14 @@ ff_status ff_matvec_backward(int64_t M, int64_t N, const float *A_hi, const floa
     const int64_t nbands = ffh::cdiv(M, band_rows);
     float2 *part = static_cast<float2 *>(ws);
     if (M > 0) {
-        const int cols = N >= 4 ? 4 : 1;
+        // One column per thread for dA alone off 16-byte alignment, 36 to 352 MiB
+        // of it (mostly held by the Infinity Cache), whole 256-byte stores there:
+        // us with one and four columns, 2500 x 2501 11.7 / 12.7, 4095 x 4095 27.5 /
+        // 36.4, 1000 x 32765 50 / 73, 6000 x 6001 55 / 84, 6700 x 6701 101 / 106; but
+        // 2000 x 2001 9.2 / 8.7, 7001 x 7001 126 / 116, 8191 x 8191 198 / 150.
+        const bool split = !want_dx && M * N > (int64_t(9) << 19) && M * N < (int64_t(11) << 22) &&
+                           !(all_aligned({dA_hi, dA_lo}, 16) && ldda % 4 == 0);
+        const int cols = N >= 4 && !split ? 4 : 1;
         int col_shift = 4;
         while ((1 << col_shift) < kColBlock && (int64_t(cols) << col_shift) < N)
             ++col_shift;

@@ -454,3 +454,23 @@ def test_forward_at_the_edges_of_short_rows(M, N, shift):
     rows = np.unique(np.linspace(0, M - 1, 24).astype(int))
     check_rows_exact(A[:, rows], x, y[:, torch.from_numpy(rows).cuda()], f"y {M}x{N}")
     assert torch.isfinite(y).all()
+
+
+@pytest.mark.parametrize("M,N", [(2049, 2303), (2049, 2305), (17, 300001), (1500000, 5), (6791, 6793)])
+def test_dA_alone_one_and_four_columns_per_thread(M, N):
+    # both sides of the sizes from which dA alone, off alignment, takes one
+    # column per thread: every entry equals Mul22(g_i, x_j) as computed with dx
+    ff = _ff()
+    _announce(f"[gpu] matvec dA alone {M}x{N}")
+    A, x, g = ff.ff_zeros((M, N)), fi.gaussian_ff((N,), 6501).cuda(), fi.gaussian_ff((M,), 6502).cuda()
+    buf = torch.full((2, M * N + 8), 7.0, device="cuda")
+    dA = buf[:, 1:M * N + 1].unflatten(1, (M, N))
+    ff.ff_matvec_backward(A, x, g, want_dx=False, dA_out=dA)
+    want, _ = ff.ff_matvec_backward(A, x, g)
+    assert torch.equal(dA.view(torch.int32), want.view(torch.int32))
+    assert torch.all(buf[:, 0] == 7.0) and torch.all(buf[:, M * N + 1:] == 7.0)
+    i, j = M // 2, N - 1
+    wh, wl = oracle.elementwise("mul", *(t.cpu().numpy() for t in (g[0, i:i + 1], g[1, i:i + 1],
+                                                                  x[0, j:j + 1], x[1, j:j + 1])))
+    assert same_bits(dA[0, i, j:j + 1].cpu().numpy(), wh)
+    assert same_bits(dA[1, i, j:j + 1].cpu().numpy(), wl)
