@@ -176,7 +176,7 @@ struct ResiduesBF16 {
     using Acc = f32x16;
     static constexpr int kEsize = 2;
     static constexpr int kFragK = 16;
-    static constexpr int kFoldStages = 20; // FP32 sums reduced every 640 k: |S| < 2^24
+    static constexpr int kFoldStages = 20; // FP32 sums reduced every 640 k: |S - 2^14 m| < 640 2^14
 };
 
 // Smallest e with |x| < 2^e for every x with |x| <= the value of bits ub.
@@ -530,7 +530,7 @@ __device__ __forceinline__ int modulus_of(int i)
 // reads and DMA are issued between MFMAs (an MFMA occupies the matrix core
 // for 32 cycles and the issue port for 4).  One barrier per stage.  Measured
 // at 4096^3 (int8): 0.88 ms, 2.50 POP/s, matrix cores busy 69 % of the
-// cycles at 1.68 GHz.  BF16: the FP32 sums have to be reduced every 1023 k at
+// cycles at 1.68 GHz.  BF16: the FP32 sums have to be reduced every 767 k at
 // the latest; one block of sixteen sums per stage, between its MFMAs of the two
 // K-steps and one sum per MFMA of the other blocks, is hidden by the matrix
 // core: 1.61 ms at 4096^3 (1.37 PFLOP/s), against 2.07 ms reduced between
@@ -610,6 +610,8 @@ __global__ __launch_bounds__(256, TM * TN == 16 ? 1 : 2) void gemm_residues(
                   lds_base + (st % kSlots) * kSlotBytes + (wave * kShare + c) * kChunk + h * kFragBytes);
     };
 
+    const int m = modulus_of(mod);
+    const float inv = 1.0f / static_cast<float>(m);
     Acc acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -617,10 +619,8 @@ __global__ __launch_bounds__(256, TM * TN == 16 ? 1 : 2) void gemm_residues(
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                acc[i][j][r] = 0;
+                acc[i][j][r] = Dg::kFoldStages > 0 ? kFoldUnits * m : 0;
 
-    const int m = modulus_of(mod);
-    const float inv = 1.0f / static_cast<float>(m);
     // BF16 residues: one FP32 sum reduced mod m
     auto fold = [&](int block, int r) {
         if constexpr (Dg::kFoldStages > 0) {
@@ -758,16 +758,7 @@ __global__ __launch_bounds__(256, TM * TN == 16 ? 1 : 2) void gemm_residues(
     // the two reductions for all 256 sums ahead of the branch, which would
     // hold them in as many registers again)
     if constexpr (Dg::kFoldStages > 0) {
-        if (m > 244)
-            store([&](float c) {
-                asm volatile("; two steps" : "+v"(c));
-                return residue_of_float_twice(c, m, inv);
-            });
-        else
-            store([&](float c) {
-                asm volatile("; one step" : "+v"(c));
-                return residue_of_float(c, m, inv);
-            });
+        store([&](float c) { return residue_of_float(c, m, inv); });
     } else if (exact || m > 244) {
         store([&](int c) {
             asm volatile("; two steps" : "+v"(c));

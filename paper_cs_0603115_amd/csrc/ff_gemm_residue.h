@@ -134,29 +134,27 @@ __host__ __device__ __forceinline__ int reduce_once(int s, int m, float inv)
     return static_cast<int>(reduce_low_byte(s, m, inv) + (static_cast<uint32_t>(m) << 22));
 }
 
-// The same for an integer c that a binary32 sum holds, |c| < 2^24: the
-// difference is exact in binary32 too.
+// FP32 sums start at kFoldUnits m and are brought back to the m integers around
+// it, exactly, before 640 products more can move them by 640 2^14.
+constexpr int kFoldUnits = 16384;
+
 __host__ __device__ __forceinline__ float reduce_float(float c, int m, float inv)
 {
-    const float n = __builtin_fmaf(c, inv, kRoundMagic) - kRoundMagic;
+    const float n = __builtin_fmaf(c, inv, kRoundMagic) - (kRoundMagic + kFoldUnits);
     return __builtin_fmaf(n, -static_cast<float>(m), c);
 }
 
-// The residue of such a sum in the low byte, for m up to 244.  1 / m in binary32
-// is off by up to 2^-24 of itself, so that one reduction of a c above 2^23 can
-// take the quotient next to the nearest; the difference then passes m / 2 by
-// less than 1, which a byte has room for.
+// The residue of such a sum in the low byte.  1 / m in binary32 is off by up to
+// 2^-24 of itself, so that the quotient of a sum beyond 2^23 can be the one next
+// to the nearest, and the difference pass m / 2 by less than 1.  Only for 255 has a
+// byte no room for that, above (128, at -8454907 and below); 1 / 255 rounds up,
+// which takes differences of positive sums down and of negative ones up, and the
+// sums lie above -6.4 10^6 because they start at 4.2 10^6.  (Up to 1.5 10^7, below
+// 2^24: all exact.)
 __host__ __device__ __forceinline__ uint32_t residue_of_float(float c, int m, float inv)
 {
     const float t = __builtin_fmaf(c, inv, kRoundMagic);
     return static_cast<uint32_t>(static_cast<int>(c)) + static_cast<uint32_t>(times24(t, -m));
-}
-
-// For every m: 255 has no room (c = -8454907 leaves 128), so the sum is reduced
-// before; of a difference that small the second quotient is the nearest.
-__host__ __device__ __forceinline__ uint32_t residue_of_float_twice(float c, int m, float inv)
-{
-    return residue_of_float(reduce_float(c, m, inv), m, inv);
 }
 
 // A sum s of digit products, |s| < 2^17, read from the integer that an

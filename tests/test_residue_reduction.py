@@ -30,13 +30,13 @@ int main(int argc, char **argv)
         if (!ok && ++wrong <= 3)
             std::printf("modulus %d sum %ld\n", m, s);
     };
-    if (!std::strcmp(argv[1], "float")) {         // FP32 sums, every one
-        for (int s = -(1 << 24) + 1; s < 1 << 24; ++s) {
+    if (!std::strcmp(argv[1], "float")) {         // FP32 sums, every one that 640 products reach
+        const int start = kFoldUnits * m, most = 640 * (1 << 14) + 130;
+        for (int s = start - most; s <= start + most; ++s) {
             const float c = static_cast<float>(s), f = reduce_float(c, m, inv);
-            check(holds(residue_of_float_twice(c, m, inv), s, m), s);
-            if (m <= 244)
-                check(holds(residue_of_float(c, m, inv), s, m), s);
-            check(f >= -129.0f && f <= 129.0f && (static_cast<int64_t>(f) - s) % m == 0, s);
+            check(static_cast<int>(c) == s && holds(residue_of_float(c, m, inv), s, m), s);
+            const int around = static_cast<int>(f) - start;
+            check(around >= -129 && around <= 129 && (static_cast<int>(f) - s) % m == 0, s);
         }
     } else if (!std::strcmp(argv[1], "int")) {    // int32 sums next to the halves
         for (int64_t q = -(int64_t(1) << 28) / m; q <= (int64_t(1) << 28) / m; ++q)
