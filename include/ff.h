@@ -466,9 +466,10 @@ ff_status ff_gradient_value(const float *g_hi, const float *g_lo, float *v_hi,
  * binades measured 2^-11.3 normwise, inside this bound; the FMA loop has no
  * such limit.
  * Inputs must be finite float-float numbers with |lo| <= ulp(hi).
- * Workspace: 0 bytes for the FMA loop; residue planes (16 (M+N) K bytes for
- * int8, twice that for BF16, and 16 M N bytes for the product, M, N and K
- * rounded up to tiles) plus scales for the sliced paths.
+ * Workspace: 0 bytes for the FMA loop; for the sliced paths scales and the
+ * residue planes of one panel (16 (m+n) k bytes for int8, twice that for BF16,
+ * and 16 m n bytes for the product, with m and n at most 16384, or 8192 where C
+ * has more than 2^32 entries, k at most 16384, rounded up to tiles).
  * Errors: FF_ERR_SIZE, FF_ERR_NULL, FF_ERR_ALIGN, FF_ERR_ARG (algo),
  * FF_ERR_WORKSPACE, FF_ERR_HIP.
  */

@@ -36,8 +36,8 @@
 // 0.91 ms against 1.55 ms for the digit pairs, and the other passes over the
 // planes 0.36 against 0.20 ms.
 //
-// Four launches per chunk of K: partial maxima, residue planes, products,
-// reconstruction (the first two once per call).
+// Four launches: partial maxima, and per chunk of K and panel of C residue planes,
+// products and reconstruction.
 
 #include <type_traits>
 
@@ -312,10 +312,10 @@ template <class Dg>
 __global__ __launch_bounds__(256, 4) void residue_planes(
     int64_t M, int64_t N, int64_t K, const float *__restrict__ Ah, const float *__restrict__ Al,
     int64_t lda, const float *__restrict__ Bh, const float *__restrict__ Bl, int64_t ldb, int nRB,
-    int nCB, int nKB, int spans, const uint32_t *__restrict__ rowpart,
-    const uint32_t *__restrict__ colpart, int nseg, int nband, int *__restrict__ rowexp,
-    int *__restrict__ colexp, uint8_t *__restrict__ Ap, uint8_t *__restrict__ Bp, int64_t plane_a,
-    int64_t plane_b)
+    int nCB, int nKB, int spans, const uint32_t *__restrict__ rowpart, int64_t rowpitch,
+    const uint32_t *__restrict__ colpart, int64_t colpitch, int nseg, int nband,
+    int *__restrict__ rowexp, int *__restrict__ colexp, uint8_t *__restrict__ Ap,
+    uint8_t *__restrict__ Bp, int64_t plane_a, int64_t plane_b)
 {
     constexpr int kPer = kResidueSpan * kBlk / 256;   // staged entries per thread and plane
     __shared__ alignas(16) float staged[2][kStaged];
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(256, 4) void residue_planes(
         uint32_t m = 0;
         if (r < limit)
             for (int s = t >> 5; s < n; s += 8)
-                m = max(m, src[s * limit + r]);
+                m = max(m, src[s * (is_a ? rowpitch : colpitch) + r]);
         part[t >> 5][t & 31] = m;
         __syncthreads();
         if (t < kBlk) {
@@ -549,8 +549,8 @@ __device__ __forceinline__ int modulus_of(int i)
 template <class Dg, int TM, int TN>
 __global__ __launch_bounds__(256, TM * TN == 16 ? 1 : 2) void gemm_residues(
     const uint8_t *__restrict__ Ap, const uint8_t *__restrict__ Bp, int64_t plane_a,
-    int64_t plane_b, int nKB, int kb0, int kb1, int nTI, int nTJ, uint8_t *__restrict__ Cr,
-    int64_t plane_c, int exact, int own_xcd)
+    int64_t plane_b, int nKB, int nTI, int nTJ, uint8_t *__restrict__ Cr, int64_t plane_c,
+    int exact, int own_xcd)
 {
     using Acc = typename Dg::Acc;
     constexpr int kChunk = kStageFrags * kFragBytes;      // a block's bytes per stage
@@ -596,9 +596,9 @@ __global__ __launch_bounds__(256, TM * TN == 16 ? 1 : 2) void gemm_residues(
         const bool of_a = n < 2 * TM;
         const int64_t blk = of_a ? static_cast<int64_t>(ti) * (2 * TM) + n
                                  : static_cast<int64_t>(tj) * (2 * TN) + n - 2 * TM;
-        src[c] = (of_a ? Ap + mod * plane_a : Bp + mod * plane_b) + (blk * nKB + kb0) * kFragBytes;
+        src[c] = (of_a ? Ap + mod * plane_a : Bp + mod * plane_b) + blk * nKB * kFragBytes;
     }
-    const int nst = (kb1 - kb0) / kStageFrags;
+    const int nst = nKB / kStageFrags;
     // DMA q of stage st; past the end the last stage again, so that every
     // stage sends the same number and the waits below need no cases
     const uint32_t lane16 = lane * 16;
@@ -906,8 +906,24 @@ __global__ __launch_bounds__(256) void zero_matrix(int64_t M, int64_t N, float *
 // the same memory channel (residue planes of 4096 x 4096: 292 us against 252).
 constexpr int64_t kPlaneSkew = 4096 + 256;
 
+// Planes are held for one panel of C at a time, and of K for the chunk that one
+// accumulation covers: 16384 x 16384 x 16384 at most, 12.9 GB of planes (21.5 in
+// BF16); for C beyond 2^32 entries, 34 GB itself, 8192 x 8192 x 16384, 5.4 GB (9.7).
+// Planes of whole operands took 206 GB at 65536^3, which the matrices (103 GB) left
+// no room for.  Where there are several panels both ways, A's planes are formed
+// anew for each panel of columns.  ms against planes of whole operands: 20000 x
+// 20000 x 1000 8.96 / 9.06 (BF16 13.0 / 13.4), 32768 x 32768 x 2048 37.2 / 37.4, 4096 x
+// 4096 x 40000 10.3 both; just past the line 16385 x 16385 x 1024 7.13 / 6.71.
+inline int64_t panel_size(int64_t n, int64_t most)
+{
+    if (n <= most)
+        return n;
+    return ffh::cdiv(ffh::cdiv(n, ffh::cdiv(n, most)), 256) * 256;   // whole tiles
+}
+
 struct ResidueGeom {
     int tm, tn;                // 32 x 32 blocks per wavefront: 1 x 1, 2 x 2, 4 x 2 or 4 x 4
+    int64_t rows, cols;        // of the largest panel, and its
     int64_t nTI, nTJ;          // tiles of 64 tm x 64 tn
     int64_t nRB, nCB, nKB;     // 32-row blocks, 32-column blocks, K-steps (padded)
     int64_t nseg, nband;       // partial maxima per row / column
@@ -917,9 +933,17 @@ struct ResidueGeom {
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
+inline int64_t padded_steps(int64_t K, int frag_k)
+{
+    return ffh::cdiv(K, static_cast<int64_t>(frag_k) * kStageFrags) * kStageFrags;
+}
+
 inline ResidueGeom residue_geom(int64_t M, int64_t N, int64_t K, int frag_k)
 {
     ResidueGeom g;
+    const int64_t most = M * N > (int64_t(1) << 32) ? 8192 : 16384;
+    g.rows = panel_size(M, most);
+    g.cols = panel_size(N, most);
     // The tile of the least estimated time: the rounds of one workgroup per
     // compute unit that the tiles of a die make, times the cost of a round in
     // units of half a 256 x 128 one.  The costs were fitted to per-call times of
@@ -932,7 +956,7 @@ inline ResidueGeom residue_geom(int64_t M, int64_t N, int64_t K, int frag_k)
     // start and end of a tile to one workgroup per compute unit and so pays
     // only from 96 K-steps on: 1166 against 1182 us at 4096^3 and 311 against
     // 315 at 2048^3 in BF16, but 690 against 675 at 4096 x 4096 x 2048.
-    const int64_t nkb = ffh::cdiv(K, static_cast<int64_t>(frag_k) * kStageFrags) * kStageFrags;
+    const int64_t nkb = padded_steps(K < kMaxKChunk ? K : kMaxKChunk, frag_k);
     constexpr struct {
         int tm, tn;
         double round;
@@ -942,7 +966,7 @@ inline ResidueGeom residue_geom(int64_t M, int64_t N, int64_t K, int frag_k)
         if (t.tn == 4 && nkb < 96)
             break;
         const int64_t per_die =
-            ffh::cdiv(M, 64 * t.tm) * ffh::cdiv(N, 64 * t.tn) * (kModuli / kXcds);
+            ffh::cdiv(g.rows, 64 * t.tm) * ffh::cdiv(g.cols, 64 * t.tn) * (kModuli / kXcds);
         const double cost = t.round * static_cast<double>(ffh::cdiv(per_die, 32));
         if (best == 0 || cost <= best) {
             best = cost;
@@ -950,8 +974,8 @@ inline ResidueGeom residue_geom(int64_t M, int64_t N, int64_t K, int frag_k)
             g.tn = t.tn;
         }
     }
-    g.nTI = ffh::cdiv(M, 64 * g.tm);
-    g.nTJ = ffh::cdiv(N, 64 * g.tn);
+    g.nTI = ffh::cdiv(g.rows, 64 * g.tm);
+    g.nTJ = ffh::cdiv(g.cols, 64 * g.tn);
     g.nRB = g.nTI * 2 * g.tm;
     g.nCB = g.nTJ * 2 * g.tn;
     g.nKB = nkb;
@@ -992,17 +1016,7 @@ ff_status sliced_gemm(int64_t M, int64_t N, int64_t K, const float *Ah, const fl
         return FF_ERR_SIZE;
     const int64_t row_groups = ffh::cdiv(M, 4), col_groups = ffh::cdiv(N, 64);
     const int64_t max_grid = row_groups * g.nseg + col_groups * g.nband;
-    // up to 8 spans per workgroup, as long as that leaves four per compute unit
-    const int64_t all_spans = ffh::cdiv(g.nKB * Dg::kFragK, kResidueSpan);
-    int spans = 8;
-    while (spans > 1 && (g.nRB + g.nCB) * ffh::cdiv(all_spans, spans) < 1024)
-        spans /= 2;
-    const int64_t res_grid = (g.nRB + g.nCB) * ffh::cdiv(all_spans, spans);
-    const int64_t gemm_grid = kModuli * g.nTI * g.nTJ;
-    const int64_t nBJ = ffh::cdiv(N, kBlk);
-    const int64_t out_grid = ffh::cdiv(M, kBlk) * nBJ;
-    if (max_grid > INT32_MAX || res_grid > INT32_MAX || gemm_grid > INT32_MAX ||
-        out_grid > INT32_MAX)
+    if (max_grid > INT32_MAX)
         return FF_ERR_SIZE;
     if (K == 0) {
         const int64_t blocks = ffh::cdiv(M * N, 256);
@@ -1020,11 +1034,6 @@ ff_status sliced_gemm(int64_t M, int64_t N, int64_t K, const float *Ah, const fl
     uint8_t *Cr = reinterpret_cast<uint8_t *>(base + g.off_c);
     hipLaunchKernelGGL(absmax_partials, dim3(static_cast<unsigned>(max_grid)), dim3(256), 0, st, M, N, K,
                        Ah, lda, Bh, ldb, row_groups, col_groups, rowpart, colpart);
-    hipLaunchKernelGGL(residue_planes<Dg>, dim3(static_cast<unsigned>(res_grid)), dim3(256), 0, st, M, N, K,
-                       Ah, Al, lda, Bh, Bl, ldb, static_cast<int>(g.nRB),
-                       static_cast<int>(g.nCB), static_cast<int>(g.nKB), spans, rowpart, colpart,
-                       static_cast<int>(g.nseg), static_cast<int>(g.nband), rowexp, colexp, Ap,
-                       Bp, g.plane_a, g.plane_b);
     auto product = g.tn == 4   ? gemm_residues<Dg, 4, 4>
                    : g.tm == 4 ? gemm_residues<Dg, 4, 2>
                    : g.tm == 2 ? gemm_residues<Dg, 2, 2>
@@ -1034,20 +1043,46 @@ ff_status sliced_gemm(int64_t M, int64_t N, int64_t K, const float *Ah, const fl
     // 5000 x 5000 x 512, 97 against 100 at 2500 x 2500 x 300), with fewer it
     // would fetch nearly all of both operands (57.6 against 45.4 us at 1024^3,
     // 18.5 against 16.8 at 200 x 300 x 257, 143 against 139 at 1700^3).
-    const int own_xcd = g.nTI * g.nTJ <= 128 ? 1 : 0;
-    const int64_t chunk = kMaxKChunk / Dg::kFragK;
-    for (int64_t kb0 = 0; kb0 < g.nKB; kb0 += chunk) {
-        const int64_t kb1 = kb0 + chunk < g.nKB ? kb0 + chunk : g.nKB;
-        hipLaunchKernelGGL(product, dim3(static_cast<unsigned>(gemm_grid)), dim3(256), 0, st, Ap,
-                           Bp, g.plane_a, g.plane_b, static_cast<int>(g.nKB),
-                           static_cast<int>(kb0), static_cast<int>(kb1),
-                           static_cast<int>(g.nTI), static_cast<int>(g.nTJ), Cr, g.plane_c,
-                           (kb1 - kb0) * Dg::kFragK > 4096 ? 1 : 0,
-                           own_xcd);
-        hipLaunchKernelGGL(combine_residues, dim3(static_cast<unsigned>(out_grid)), dim3(256), 0,
-                           st, M, N, nBJ, Cr, g.nCB, g.plane_c, rowexp, colexp, Ch, Cl, ldc,
-                           kb0 > 0 ? 1 : 0);
-    }
+    auto panel = [&](int64_t i0, int64_t j0, int64_t k0) {
+        const int64_t rows = M - i0 < g.rows ? M - i0 : g.rows;
+        const int64_t cols = N - j0 < g.cols ? N - j0 : g.cols;
+        const int64_t depth = K - k0 < kMaxKChunk ? K - k0 : kMaxKChunk;
+        const int nKB = static_cast<int>(padded_steps(depth, Dg::kFragK));
+        const int nTI = static_cast<int>(ffh::cdiv(rows, 64 * g.tm));
+        const int nTJ = static_cast<int>(ffh::cdiv(cols, 64 * g.tn));
+        const int nCB = nTJ * 2 * g.tn;
+        // planes that an earlier panel left are used again
+        const int form_rb = j0 == 0 || M > g.rows ? nTI * 2 * g.tm : 0;
+        const int form_cb = i0 == 0 ? nCB : 0;
+        if (form_rb + form_cb > 0) {
+            // up to 8 spans per workgroup, as long as that leaves four per compute unit
+            const int64_t all_spans = ffh::cdiv(nKB * Dg::kFragK, kResidueSpan);
+            int spans = 8;
+            while (spans > 1 && (form_rb + form_cb) * ffh::cdiv(all_spans, spans) < 1024)
+                spans /= 2;
+            const int64_t grid = (form_rb + form_cb) * ffh::cdiv(all_spans, spans);
+            hipLaunchKernelGGL(residue_planes<Dg>, dim3(static_cast<unsigned>(grid)), dim3(256), 0,
+                               st, rows, cols, depth, Ah + i0 * lda + k0, Al + i0 * lda + k0, lda,
+                               Bh + k0 * ldb + j0, Bl + k0 * ldb + j0, ldb, form_rb, form_cb, nKB,
+                               spans, rowpart + i0, M, colpart + j0, N, static_cast<int>(g.nseg),
+                               static_cast<int>(g.nband), rowexp + i0, colexp + j0, Ap, Bp,
+                               g.plane_a, g.plane_b);
+        }
+        const int own_xcd = nTI * nTJ <= 128 ? 1 : 0;
+        hipLaunchKernelGGL(product, dim3(static_cast<unsigned>(kModuli * nTI * nTJ)), dim3(256), 0,
+                           st, Ap, Bp, g.plane_a, g.plane_b, nKB, nTI, nTJ, Cr, g.plane_c,
+                           nKB * Dg::kFragK > 4096 ? 1 : 0, own_xcd);
+        const int64_t nBJ = ffh::cdiv(cols, kBlk);
+        hipLaunchKernelGGL(combine_residues,
+                           dim3(static_cast<unsigned>(ffh::cdiv(rows, kBlk) * nBJ)), dim3(256), 0,
+                           st, rows, cols, nBJ, Cr, static_cast<int64_t>(nCB), g.plane_c,
+                           rowexp + i0, colexp + j0, Ch + i0 * ldc + j0, Cl + i0 * ldc + j0, ldc,
+                           k0 > 0 ? 1 : 0);
+    };
+    for (int64_t k0 = 0; k0 < K; k0 += kMaxKChunk)
+        for (int64_t j0 = 0; j0 < N; j0 += g.cols)
+            for (int64_t i0 = 0; i0 < M; i0 += g.rows)
+                panel(i0, j0, k0);
     return ffh::launch_status();
 }
 

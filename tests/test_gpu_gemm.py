@@ -418,3 +418,42 @@ def test_sums_of_the_farthest_residues(algo, M, N, K):
             assert err * part <= abs(exact), (i, j, float(err / exact))
     repeated = first.view(torch.int32)[:, row.cuda()][:, :, col.cuda()]
     assert torch.equal(C.view(torch.int32), repeated)
+
+
+@pytest.mark.parametrize("algo,M,N,K", [
+    # panels of rows, of columns, of both, with one chunk of K and with two
+    ("i8", 16500, 70, 40), ("i8", 70, 16500, 40), ("i8", 16500, 16700, 33),
+    ("bf16", 33000, 16500, 20), ("i8", 16500, 300, 16390), ("bf16", 200, 16500, 16390),
+    # beyond 2^32 entries
+    ("i8", 262140, 16500, 3)])
+def test_panels_of_a_large_product(algo, M, N, K):
+    # rows and columns repeat after 127, which no panel or tile is a multiple of,
+    # and are scaled by powers of two of their own, so that an entry formed with
+    # another panel's rows, columns or scales differs from the 127 x 127 product
+    _announce(f"[gpu] gemm panels {M}x{N}x{K} ({algo})")
+    ff = _ff()
+    a, b = fi.gaussian_ff((127, K), 8700 + K), fi.gaussian_ff((K, 127), 8701 + K)
+    a *= torch.exp2((torch.arange(127) % 31 - 15.0))[None, :, None]
+    b *= torch.exp2((torch.arange(127) % 29 - 14.0))[None, None, :]
+    want = ff.ff_gemm(a.cuda(), b.cuda(), algo=_algo(algo))
+    check_entries(a, b, want, range(0, 127, 9), range(0, 127, 9), "panel", TWO_M44)
+    A, B = ff.ff_empty((M, K)), ff.ff_empty((K, N))
+    A.copy_(a.cuda()[:, torch.arange(M) % 127])
+    B.copy_(b.cuda()[:, :, torch.arange(N) % 127])
+    C = ff.ff_gemm(A, B, algo=_algo(algo))
+    wide = want.view(torch.int32)[:, :, (torch.arange(N) % 127).cuda()]
+    for r in range(0, M, 127 * 64):
+        rows = min(127 * 64, M - r)
+        assert torch.equal(C[:, r:r + rows].view(torch.int32),
+                           wide[:, (torch.arange(rows) % 127).cuda()]), r
+    del A, B, C, wide
+    torch.cuda.empty_cache()
+
+
+def test_workspace_of_a_large_product_is_bounded():
+    size = _ff().ff_gemm_workspace_size
+    for n, algo in ((65536, "i8"), (65536, "bf16"), (200000, "i8")):
+        assert size(n, n, n, _algo(algo)) < 25 << 30
+    assert size(4096, 4096, 1 << 21, _algo("i8")) < 4 << 30
+    planes = 16 * (2 * 4096 * 4096 + 4096 * 4096)      # those of 4096^3, all held
+    assert planes <= size(4096, 4096, 4096, _algo("i8")) < planes + (1 << 20)
