@@ -468,8 +468,8 @@ ff_status ff_gradient_value(const float *g_hi, const float *g_lo, float *v_hi,
  * Inputs must be finite float-float numbers with |lo| <= ulp(hi).
  * Workspace: 0 bytes for the FMA loop; for the sliced paths scales and the
  * residue planes of one panel (16 (m+n) k bytes for int8, twice that for BF16,
- * and 16 m n bytes for the product, with m and n at most 16384, or 8192 where C
- * has more than 2^32 entries, k at most 16384, rounded up to tiles).
+ * and 16 m n bytes for the product, with m, n and k at most 16384 and m and n
+ * rounded up to 256).  A size queried for some M, N and K serves any smaller.
  * Errors: FF_ERR_SIZE, FF_ERR_NULL, FF_ERR_ALIGN, FF_ERR_ARG (algo),
  * FF_ERR_WORKSPACE, FF_ERR_HIP.
  */

@@ -906,26 +906,18 @@ __global__ __launch_bounds__(256) void zero_matrix(int64_t M, int64_t N, float *
 // the same memory channel (residue planes of 4096 x 4096: 292 us against 252).
 constexpr int64_t kPlaneSkew = 4096 + 256;
 
-// Planes are held for one panel of C at a time, and of K for the chunk that one
-// accumulation covers: 16384 x 16384 x 16384 at most, 12.9 GB of planes (21.5 in
-// BF16); for C beyond 2^32 entries, 34 GB itself, 8192 x 8192 x 16384, 5.4 GB (9.7).
-// Planes of whole operands took 206 GB at 65536^3, which the matrices (103 GB) left
-// no room for.  Where there are several panels both ways, A's planes are formed
-// anew for each panel of columns.  ms against planes of whole operands: 20000 x
-// 20000 x 1000 8.96 / 9.06 (BF16 13.0 / 13.4), 32768 x 32768 x 2048 37.2 / 37.4, 4096 x
-// 4096 x 40000 10.3 both; just past the line 16385 x 16385 x 1024 7.13 / 6.71.
-inline int64_t panel_size(int64_t n, int64_t most)
-{
-    if (n <= most)
-        return n;
-    return ffh::cdiv(ffh::cdiv(n, ffh::cdiv(n, most)), 256) * 256;   // whole tiles
-}
+// Planes are held for one panel of C at a time, at most this many rows by columns,
+// and of K for the chunk that one accumulation covers: 12.9 GB of them at most
+// (21.5 in BF16).  Planes of whole operands took 206 GB at 65536^3, which the
+// matrices (103 GB) left no room for.  Where there are several panels both ways,
+// A's planes are formed anew for each panel of columns.  ms against planes of
+// whole operands: 20000 x 20000 x 1000 8.96 / 9.06 (BF16 13.0 / 13.4), 32768 x 32768 x
+// 2048 37.2 / 37.4, 4096 x 4096 x 40000 10.3 both.
+constexpr int64_t kPanel = 16384;
 
 struct ResidueGeom {
     int tm, tn;                // 32 x 32 blocks per wavefront: 1 x 1, 2 x 2, 4 x 2 or 4 x 4
-    int64_t rows, cols;        // of the largest panel, and its
-    int64_t nTI, nTJ;          // tiles of 64 tm x 64 tn
-    int64_t nRB, nCB, nKB;     // 32-row blocks, 32-column blocks, K-steps (padded)
+    int64_t rows, cols;        // of a panel
     int64_t nseg, nband;       // partial maxima per row / column
     int64_t plane_a, plane_b, plane_c;
     size_t off_colpart, off_rowexp, off_colexp, off_a, off_b, off_c, total;
@@ -941,9 +933,8 @@ inline int64_t padded_steps(int64_t K, int frag_k)
 inline ResidueGeom residue_geom(int64_t M, int64_t N, int64_t K, int frag_k)
 {
     ResidueGeom g;
-    const int64_t most = M * N > (int64_t(1) << 32) ? 8192 : 16384;
-    g.rows = panel_size(M, most);
-    g.cols = panel_size(N, most);
+    g.rows = M < kPanel ? M : kPanel;
+    g.cols = N < kPanel ? N : kPanel;
     // The tile of the least estimated time: the rounds of one workgroup per
     // compute unit that the tiles of a die make, times the cost of a round in
     // units of half a 256 x 128 one.  The costs were fitted to per-call times of
@@ -974,16 +965,14 @@ inline ResidueGeom residue_geom(int64_t M, int64_t N, int64_t K, int frag_k)
             g.tn = t.tn;
         }
     }
-    g.nTI = ffh::cdiv(g.rows, 64 * g.tm);
-    g.nTJ = ffh::cdiv(g.cols, 64 * g.tn);
-    g.nRB = g.nTI * 2 * g.tm;
-    g.nCB = g.nTJ * 2 * g.tn;
-    g.nKB = nkb;
+    // The workspace holds whole 256 x 256 tiles whatever the tile, so that it grows
+    // with every dimension and one for a caller's largest product serves the others.
+    const int64_t blocks_a = ffh::cdiv(g.rows, 256) * 8, blocks_b = ffh::cdiv(g.cols, 256) * 8;
     g.nseg = ffh::cdiv(K, kRowSegment);
     g.nband = ffh::cdiv(K, kColBand);
-    g.plane_a = g.nRB * g.nKB * kFragBytes + kPlaneSkew;
-    g.plane_b = g.nCB * g.nKB * kFragBytes + kPlaneSkew;
-    g.plane_c = g.nRB * g.nCB * kFragBytes + kPlaneSkew;
+    g.plane_a = blocks_a * nkb * kFragBytes + kPlaneSkew;
+    g.plane_b = blocks_b * nkb * kFragBytes + kPlaneSkew;
+    g.plane_c = blocks_a * blocks_b * kFragBytes + kPlaneSkew;
     size_t off = align256(sizeof(uint32_t) * g.nseg * M);
     auto take = [&](size_t bytes) {
         const size_t at = off;

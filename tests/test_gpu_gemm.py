@@ -424,7 +424,7 @@ def test_sums_of_the_farthest_residues(algo, M, N, K):
     # panels of rows, of columns, of both, with one chunk of K and with two
     ("i8", 16500, 70, 40), ("i8", 70, 16500, 40), ("i8", 16500, 16700, 33),
     ("bf16", 33000, 16500, 20), ("i8", 16500, 300, 16390), ("bf16", 200, 16500, 16390),
-    # beyond 2^32 entries
+    # as many rows as the library takes
     ("i8", 262140, 16500, 3)])
 def test_panels_of_a_large_product(algo, M, N, K):
     # rows and columns repeat after 127, which no panel or tile is a multiple of,
