@@ -363,9 +363,11 @@ ff_status ff_matvec(int64_t M, int64_t N, const float *A_hi, const float *A_lo,
                     float *y_hi, float *y_lo, int32_t algo, void *stream);
 
 /* Workspace bytes of ff_matvec_backward (partial column sums of the fast
- * algorithm, one row of N per band of 4 to 128 rows; 0 for the plain one).  A
- * workspace that only holds the sums of longer bands, up to 128 rows, is
- * accepted and used for those. */
+ * algorithm, one row of N per band of 4 to 128 rows; 0 for the plain one),
+ * enough for this matrix and any of fewer rows and columns.  A workspace that
+ * only holds the sums of longer bands, up to 128 rows, is
+ * accepted and used for those; dx is then summed in their order, so that its
+ * last bits may differ from those of a workspace of at least this size. */
 size_t ff_matvec_backward_workspace_size(int64_t M, int64_t N, int32_t algo);
 
 /* Backward pass of y = A x for an upstream gradient g = dL/dy (M values):

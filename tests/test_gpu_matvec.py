@@ -474,3 +474,16 @@ def test_dA_alone_one_and_four_columns_per_thread(M, N):
                                                                   x[0, j:j + 1], x[1, j:j + 1])))
     assert same_bits(dA[0, i, j:j + 1].cpu().numpy(), wh)
     assert same_bits(dA[1, i, j:j + 1].cpu().numpy(), wl)
+
+
+def test_backward_workspace_of_the_largest_matrix_serves_smaller_ones():
+    ff = _ff()
+    ws = torch.empty(ff.ff_matvec_backward_workspace_size(8192, 8192), dtype=torch.uint8,
+                     device="cuda")
+    for M, N in ((8192, 8000), (8190, 64), (5389, 1145), (300, 8191), (4096, 63)):
+        A, x = ff.ff_zeros((M, N)), ff.ff_zeros((N,))
+        A[0] = torch.arange(M * N, device="cuda").remainder(7).view(M, N).float()
+        g = fi.gaussian_ff((M,), 6600 + N).cuda()
+        _, want = ff.ff_matvec_backward(A, x, g, want_dA=False)
+        _, got = ff.ff_matvec_backward(A, x, g, want_dA=False, workspace=ws)
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), (M, N)

@@ -32,3 +32,10 @@ def test_product_workspace_never_falls(algo):
     for m, n in itertools.product((64, 65, 128, 129, 256, 257, 512, 16384, 16385), repeat=2):
         assert ff.ff_gemm_workspace_size(m, n, 500, algo) <= \
             ff.ff_gemm_workspace_size(m + 1, n + 1, 500, algo)
+
+
+def test_matvec_backward_workspace_never_falls():
+    _never_falls(lambda m, n: ff.ff_matvec_backward_workspace_size(m, n), [(1, 200000), (1, 70000)], 12)
+    # 8192 x 8000 makes more bands than 8192 x 8192
+    size = ff.ff_matvec_backward_workspace_size
+    assert size(8192, 8000) <= size(8192, 8192)
