@@ -224,9 +224,8 @@ typedef struct ff_dot_cfg {
 } ff_dot_cfg;
 
 /* Bytes of device workspace the batched reductions need for nvec vectors
- * holding total_len elements in all, with this cfg (for the default shape:
- * enough for this total and any smaller one).  Returns 0 for invalid
- * arguments. */
+ * holding total_len elements in all, with this cfg: enough for these and for
+ * any smaller total and number of vectors.  Returns 0 for invalid arguments. */
 size_t ff_dot_batched_workspace_size(int64_t total_len, int32_t nvec,
                                      const ff_dot_cfg *cfg);
 

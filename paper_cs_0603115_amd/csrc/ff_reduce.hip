@@ -608,17 +608,16 @@ bool short_chunks(int64_t total, int32_t nvec, int planes)
 }
 
 // Workspace of the default shape: enough for either chunk length at this
-// total or any smaller one, so that a workspace sized for a caller's largest
-// batch serves its smaller ones.
+// total and number of vectors or any smaller ones, so that a workspace sized for
+// a caller's largest batch serves its smaller ones.
 size_t default_workspace_bytes(int64_t total, int32_t nvec)
 {
-    int64_t chunks = total / (int64_t(kDefaultBlock) * kDefaultUnroll);
-    if (nvec <= kShortVectors) {
-        const int64_t most =
-            (total < kShortTotalMost ? total : kShortTotalMost) / kShortChunk;
-        chunks = chunks > most ? chunks : most;
-    }
-    return workspace_bytes_for(chunks + nvec, nvec);
+    const int64_t long_chunks =
+        chunk_capacity(total, nvec, int64_t(kDefaultBlock) * kDefaultUnroll);
+    const int64_t short_chunks =
+        chunk_capacity(total < kShortTotalMost ? total : kShortTotalMost,
+                       nvec < kShortVectors ? nvec : kShortVectors, kShortChunk);
+    return workspace_bytes_for(long_chunks > short_chunks ? long_chunks : short_chunks, nvec);
 }
 
 bool valid_unroll(int u)

@@ -39,3 +39,11 @@ def test_matvec_backward_workspace_never_falls():
     # 8192 x 8000 makes more bands than 8192 x 8192
     size = ff.ff_matvec_backward_workspace_size
     assert size(8192, 8000) <= size(8192, 8192)
+
+
+@pytest.mark.parametrize("cfg", [None, (256, 8192, 0, 32), (64, 0, 0, 1)])
+def test_reduction_workspace_never_falls(cfg):
+    _never_falls(lambda total, nvec: ff.ff_dot_batched_workspace_size(total, nvec, cfg),
+                 [(1, 1 << 31), (1, 300000)], 13)
+    size = ff.ff_dot_batched_workspace_size
+    assert size(1 << 25, 65536, cfg) <= size(1 << 25, 65537, cfg)
