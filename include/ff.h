@@ -201,8 +201,11 @@ ff_status ff_div_accurate(const float *a_hi, const float *a_lo,
  * index order give the chunk's float-float partial -- and one combining
  * each vector's partials (one wavefront per vector, an Add22 tree of fixed
  * shape).  No atomics are used: for a given cfg the result is bitwise
- * reproducible run to run.  Different cfg values may give different
- * (equally valid) last bits.  Any 4-byte alignment of the inputs.
+ * reproducible run to run, from any workspace of at least the queried size.
+ * Different cfg values may give different (equally valid) last bits, and so
+ * may, with the default cfg, a workspace below the queried size that is still
+ * accepted (one that holds only chunks of 8192, below).  Any 4-byte alignment
+ * of the inputs.
  *
  * Accuracy: |result - exact| is bounded by (tree depth) * 2^-44 * sum|x_i y_i|
  * in the worst case; on random data it is far smaller (2^-47.1 sum|x_i y_i|
@@ -213,7 +216,9 @@ ff_status ff_div_accurate(const float *a_hi, const float *a_lo,
  * 256 threads by 32 elements per thread (chunks of 8192 elements); with no
  * field set, batches of few elements take 8 per thread (chunks of 2048): up
  * to 2^21 elements, and for dots and float-float sums up to 2^25 if vectors
- * average at most 2^17 elements, as long as ws_bytes holds their chunks. */
+ * average at most 2^17 elements.  A workspace that only holds the chunks of
+ * 8192 is accepted there too and gets those, so the order of the sums is then
+ * that of cfg {256, 8192, 0, 32}. */
 typedef struct ff_dot_cfg {
     int32_t block;  /* threads per workgroup: 64, 128, 256 or 512            */
     int32_t chunk;  /* elements per chunk: 0 or block * unroll (with unroll
@@ -299,8 +304,9 @@ ff_status ff_sum2_batched(const float *x, const int64_t *offsets, int32_t nvec,
 
 /* ff_dot_batched without a workspace argument, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc).  Same kernels, results (bit for bit for
- * the same cfg), arguments and errors as ff_dot_batched; its scratch is a
+ * harnesses that forbid hipMalloc).  Same kernels, results (bit for bit those
+ * of the same cfg with a workspace of the queried size), arguments and errors
+ * as ff_dot_batched; its scratch is a
  * static device array of FF_NOALLOC_SCRATCH_BYTES inside the library, one
  * copy per device, held until the process ends (its device address is looked
  * up once per device on the first call there).  No allocation of any kind.

@@ -349,3 +349,20 @@ def test_default_shape_by_size_and_workspace():
     assert torch.equal(got.view(torch.int32), want.view(torch.int32))
     sizes = [ff.ff_dot_batched_workspace_size(1 << b, 40) for b in range(10, 33)]
     assert sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("nvec,log2_max", [(1, 10), (40, 14), (1, 21), (500, 15), (3, 22)])
+def test_every_workspace_of_the_queried_size_gives_the_same_bits(nvec, log2_max):
+    # the default shape follows the batch alone: at the queried size, with more,
+    # and from the library's own scratch
+    ff = _ff()
+    x, y, offs = fi.batched_dot(4741 + nvec, device="cuda", nvec=nvec, log2_min=log2_max - 1,
+                                log2_max=log2_max)
+    size = ff.ff_dot_batched_workspace_size(x.numel(), nvec)
+    want = ff.ff_dot_batched_noalloc(x, y, offs)
+    for nbytes in (size, size + 256, 4 * size, 16 << 20):
+        if nbytes < size:
+            continue
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        got = ff.ff_dot_batched(x, y, offs, workspace=ws)
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), nbytes
