@@ -84,3 +84,36 @@ def test_contraction_is_off(assembly):
     assert len(horner) == 8, sorted(poly)
     for k in horner:
         assert not fused.findall(poly[k]), k
+
+
+@pytest.fixture(scope="module")
+def shipped(tmp_path_factory):
+    """Assembly of the sources that are built with flags of their own, with
+    those flags, as the library holds them."""
+    out = tmp_path_factory.mktemp("shipped")
+    assert B.SOURCE_FLAGS and all(os.path.exists(os.path.join(B.CSRC, n)) for n in B.SOURCE_FLAGS)
+    texts = {}
+    for name in B.SOURCE_FLAGS:
+        dst = B.device_asm(os.path.join(B.CSRC, name), os.path.join(out, name + ".s"))
+        with open(dst) as f:
+            texts[name] = f.read()
+    return texts
+
+
+def test_sources_with_flags_of_their_own_keep_the_numerics(shipped):
+    for name, text in shipped.items():
+        kernels = len(re.findall(r"^\s*\.amdhsa_kernel\s", text, re.M))
+        denorm = re.findall(r"\.amdhsa_float_denorm_mode_32\s+(\d+)", text)
+        rounding = re.findall(r"\.amdhsa_float_round_mode_32\s+(\d+)", text)
+        assert kernels > 0 and len(denorm) == kernels and len(rounding) == kernels, name
+        assert set(denorm) == {"3"} and set(rounding) == {"0"}, (name, set(denorm), set(rounding))
+    test_no_packed_binary32_instructions(shipped)
+
+
+def test_sources_with_flags_of_their_own_do_not_spill(shipped):
+    # what the flags are there for: the accumulators stay in their registers
+    for name, text in shipped.items():
+        spills = re.findall(r"^\s*\.vgpr_spill_count:\s*(\d+)", text, re.M)
+        scratch = re.findall(r"^\s*\.private_segment_fixed_size:\s*(\d+)", text, re.M)
+        assert spills and set(spills) == {"0"}, (name, spills)
+        assert scratch and set(scratch) == {"0"}, (name, scratch)
