@@ -30,8 +30,10 @@ __all__ = ["FFMatVec", "FFDot", "FFDotBatched", "ff_one"]
 
 def _value_gradient(g: torch.Tensor) -> torch.Tensor:
     """The incoming gradient as a float-float value (ff_gradient_value);
-    gradients of other layouts (expanded ones, for example) are copied first."""
-    g = g.detach()
+    gradients of other layouts (expanded ones, for example) are copied first,
+    and so are negated views (the imaginary part of a conjugate), whose memory
+    holds the numbers of the other sign."""
+    g = g.detach().resolve_neg()
     if not _dense(g.shape, g.stride(), 1):
         g = g.contiguous()
     return ff_gradient_value(g)

@@ -315,3 +315,29 @@ def test_gradient_value_selects_the_plane(n):
     assert torch.equal(got.view(torch.int32), want.view(torch.int32))
     one = _value_gradient(torch.ones((), device="cuda").expand(2, n)).cpu()
     assert torch.all(one[0] == 1) and torch.all(one[1] == 0)
+
+
+@pytest.mark.parametrize("which", ["dot", "batched", "matvec"])
+def test_gradient_that_is_a_negated_view(which):
+    # the imaginary part of a conjugated complex number is a view that torch
+    # negates when it reads it; a gradient that autograd hands over as such a view
+    # keeps its sign
+    from paper_cs_0603115_amd import autograd as ffa
+
+    u, v = (fi.gaussian_ff((300,), 9201 + k).cuda() for k in range(2))
+    results = []
+    for negate in (False, True):
+        x = u.clone().requires_grad_()
+        if which == "dot":
+            s = ffa.FFDot.apply(x, v)
+        elif which == "batched":
+            s = ffa.FFDotBatched.apply(x, v, torch.tensor([0, 300], device="cuda"))
+        else:
+            s = ffa.FFMatVec.apply(x.reshape(2, 1, 300), v)
+        if negate:
+            s = torch.complex(torch.zeros_like(s), s).conj()   # -s i
+        s.abs().sum().backward()
+        results.append(x.grad)
+    assert torch.equal(results[0].view(torch.int32), results[1].view(torch.int32))
+    g = fi.gaussian_ff((5,), 9203).cuda()
+    assert torch.equal(ffa._value_gradient(torch._neg_view(g)), ffa._value_gradient(-g))
