@@ -137,7 +137,7 @@ def _plane_layout(shape):
     unless n is a multiple of 64 every such access straddles two segments,
     which cost the streaming kernels up to 8 % of their rate on MI355X.)"""
     size, strides, acc = [], [], 1
-    for d in reversed(shape):
+    for d in reversed(tuple(shape)):
         d = int(d)
         size.append(d)
         strides.append(acc)

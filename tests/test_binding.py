@@ -44,6 +44,13 @@ def test_ff_empty_and_zeros_share_a_layout(shape):
     assert float(a.sum()) == a.numel()
 
 
+def test_ff_empty_takes_any_iterable_of_sizes():
+    for shape in ([3, 5], (3, 5), torch.Size((3, 5)), (d for d in (3, 5)), map(int, "35"),
+                  {3: "rows", 5: "columns"}, torch.tensor([3, 5])):
+        assert ff.ff_empty(shape, device="cpu").shape == (2, 3, 5)
+    assert ff.ff_zeros(iter([4]), device="cpu").shape == (2, 4)
+
+
 def test_stream_argument_by_position_and_keyword(monkeypatch):
     # the wrapper finds the stream wherever the caller put it
     seen = []
