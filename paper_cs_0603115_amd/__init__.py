@@ -49,6 +49,12 @@ def build_info() -> str:
 # of its planes), the raw handle of the current stream is read directly, and
 # the device is switched only when it has to be.
 
+# torch's own short cuts to both, where it has them; the public calls otherwise.
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
+                              lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
 def _torch_stream(stream):
     if isinstance(stream, torch.cuda.Stream):
         return stream
@@ -77,12 +83,12 @@ def _enqueue(name: str, device: torch.device, stream, *args) -> None:
     """Call entry point ``name`` with ``args`` and, last, the stream: the
     current one of ``device`` unless given."""
     index = device.index
-    if index != torch._C._cuda_getDevice():
+    if index != _current_device():
         with torch.cuda.device(device):
             _enqueue(name, device, stream, *args)
         return
     if stream is None:
-        handle = torch._C._cuda_getCurrentRawStream(index)
+        handle = _current_raw_stream(index)
     else:
         handle = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
     status = getattr(lib, name)(*args, handle)

@@ -79,3 +79,35 @@ def test_stream_argument_by_position_and_keyword(monkeypatch):
 def test_product_workspace_of_empty_sizes(algo):
     for shape in itertools.product((0, 1, 5), repeat=3):
         assert ff.ff_gemm_workspace_size(*shape, algo) >= 0
+
+
+def test_binding_without_torchs_short_cuts(monkeypatch):
+    # a torch without the private names: the public calls serve
+    import importlib
+    import sys
+
+    class Stream:
+        cuda_stream = 1234
+
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda index: Stream)
+    spec = importlib.util.spec_from_file_location(
+        "ff_without_short_cuts", ff.__file__, submodule_search_locations=list(ff.__path__))
+    mod = importlib.util.module_from_spec(spec)
+    monkeypatch.setitem(sys.modules, spec.name, mod)
+    spec.loader.exec_module(mod)
+    assert mod._current_device() == 3 and mod._current_raw_stream(3) == 1234
+    seen = []
+
+    class Lib:
+        @staticmethod
+        def ff_entry(*args):
+            seen.append(args)
+            return 0
+
+    monkeypatch.setattr(mod, "lib", Lib)
+    mod._enqueue("ff_entry", torch.device("cuda", 3), None, 7, 8)
+    mod._enqueue("ff_entry", torch.device("cuda", 3), Stream, 9)
+    assert seen == [(7, 8, 1234), (9, 1234)]
