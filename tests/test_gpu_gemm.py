@@ -457,3 +457,30 @@ def test_workspace_of_a_large_product_is_bounded():
     assert size(4096, 4096, 1 << 21, _algo("i8")) < 4 << 30
     planes = 16 * (2 * 4096 * 4096 + 4096 * 4096)      # those of 4096^3, all held
     assert planes <= size(4096, 4096, 4096, _algo("i8")) < planes + (1 << 20)
+
+
+@pytest.mark.parametrize("algo", ALGOS)
+@pytest.mark.parametrize("M,K,N", [(32, 2048, 32), (40, 17000, 36)])
+def test_fixed_point_and_final_rounding_are_the_only_errors(algo, M, K, N):
+    # the header's bound as it stands, with 2^e_i the power of two above row i's
+    # largest |hi| and 2^f_j above column j's: no digit product is dropped, so
+    # rows and columns spanning 40 binades meet it without a term in K; each
+    # further chunk of 16384 k adds its own rounding and one Add22 (2^-44)
+    _announce(f"[gpu] gemm documented bound {M}x{K}x{N} ({algo})")
+    A, B = _wide_range_operands(M, K, N, 7501)
+    C = _ff().ff_gemm(A.cuda(), B.cuda(), algo=_algo(algo)).cpu().numpy()
+    An, Bn = A.numpy(), B.numpy()
+    Av, Bv = An.astype(np.float64).sum(0), Bn.astype(np.float64).sum(0)
+    e = np.frexp(np.abs(An[0]).max(axis=1))[1]
+    f = np.frexp(np.abs(Bn[0]).max(axis=0))[1]
+    ri, ci = (t.ravel() for t in np.meshgrid(np.arange(0, M, 3), np.arange(0, N, 3), indexing="ij"))
+    exact = oracle.exact_gemm_entries(An[0], An[1], Bn[0], Bn[1], ri, ci)
+    scale = oracle.exact_absgemm_entries(An[0], An[1], Bn[0], Bn[1], ri, ci)
+    sumA, sumB = np.abs(Av).sum(axis=1), np.abs(Bv).sum(axis=0)
+    for t, (i, j) in enumerate(zip(ri, ci)):
+        err = abs(frac(C[0, i, j]) + frac(C[1, i, j]) - exact[t])
+        bound = Fraction(math.ldexp(sumB[j], int(e[i]) - 54)
+                         + math.ldexp(sumA[i] + K * math.ldexp(1.0, int(e[i]) - 54),
+                                      int(f[j]) - 54)) * Fraction(1000001, 1000000)
+        bound += abs(exact[t]) / (1 << 47) + (scale[t] / (1 << 44) if K > 16384 else 0)
+        assert err <= bound, (i, j, float(err / bound))
