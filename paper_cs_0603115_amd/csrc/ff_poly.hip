@@ -215,13 +215,24 @@ __global__ __launch_bounds__(kPolyBlock) void horner_scalar(PolyArgs a, int64_t 
 template <class Alg, bool CLO, bool XLO>
 ff_status launch_horner(PolyArgs a, int64_t n, bool vec, hipStream_t st)
 {
-    const int64_t blocks = vec ? ffh::cdiv(n, 4 * kPolyBlock) : ffh::cdiv(n, kPolyBlock);
     if (vec) {
-        if (blocks > INT32_MAX)
-            return FF_ERR_SIZE;
-        hipLaunchKernelGGL((horner_vec<Alg, CLO, XLO>), dim3(static_cast<unsigned>(blocks)),
-                           dim3(kPolyBlock), 0, st, a, n);
+        // (a launch holds fewer than 2^32 threads)
+        constexpr int64_t kMost = int64_t(1) << 33;
+        for (int64_t done = 0; done < n; done += kMost) {
+            PolyArgs part = a;
+            part.xh += done;
+            if (XLO)
+                part.xl += done;
+            part.yh += done;
+            if (Alg::kFF)
+                part.yl += done;
+            const int64_t points = n - done < kMost ? n - done : kMost;
+            hipLaunchKernelGGL((horner_vec<Alg, CLO, XLO>),
+                               dim3(static_cast<unsigned>(ffh::cdiv(points, 4 * kPolyBlock))),
+                               dim3(kPolyBlock), 0, st, part, points);
+        }
     } else {
+        const int64_t blocks = ffh::cdiv(n, kPolyBlock);
         hipLaunchKernelGGL((horner_scalar<Alg, CLO, XLO>),
                            dim3(static_cast<unsigned>(blocks < 65536 ? blocks : 65536)),
                            dim3(kPolyBlock), 0, st, a, n);

@@ -239,3 +239,29 @@ def test_stream_operators_and_copy_beyond_2p31():
     del a, dst
     _free()
     assert np.array_equal(ds, as_)
+
+
+def test_horner_beyond_one_launch():
+    # more points than one launch has threads for four of each, off 16-byte
+    # alignment and in place (69 GB): both parts against torch's two roundings
+    import paper_cs_0603115_amd as ff
+
+    n = (1 << 34) + 5
+    print(f"[gpu] horner {n} points", flush=True)
+    base = torch.full((n + 2,), 7.0, device="cuda")
+    x = base[1:n + 1]
+    step = 1 << 30
+    pattern = torch.arange(step, device="cuda", dtype=torch.float32).remainder_(8191.0).div_(4096.0)
+    for at in range(0, n, step):
+        m = min(step, n - at)
+        x[at:at + m] = pattern[:m] + (at // step)
+    coef = torch.tensor([0.3, 1.7], device="cuda")
+    ff.ff_horner_f32(coef, x, out=x)
+    torch.cuda.synchronize()
+    for at in range(0, n, step):
+        m = min(step, n - at)
+        want = (pattern[:m] + (at // step)).mul_(coef[1]).add_(coef[0])
+        assert torch.equal(x[at:at + m], want), at
+    assert float(base[0]) == 7.0 and float(base[n + 1]) == 7.0
+    del base, x, pattern, want
+    torch.cuda.empty_cache()
