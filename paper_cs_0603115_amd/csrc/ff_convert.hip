@@ -108,11 +108,13 @@ ff_status ff_from_f64(const double *x, float *hi, float *lo, int64_t n, void *st
     const ff_status st = check_planes(x, hi, lo, n);
     if (st != FF_OK || n == 0)
         return st;
-    const int64_t blocks = ffh::cdiv(n, int64_t(kFromThreads) * kFromPer);
-    if (blocks > INT32_MAX)
+    if (ffh::cdiv(n, int64_t(kFromThreads) * kFromPer) > INT32_MAX)
         return FF_ERR_SIZE;
-    hipLaunchKernelGGL(from_f64_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kFromThreads), 0,
-                       ffh::as_stream(stream), x, hi, lo, n);
+    ffh::in_parts(n, ffh::kMostThreads, [&](int64_t at, int64_t count) {
+        const int64_t blocks = ffh::cdiv(count, int64_t(kFromThreads) * kFromPer);
+        hipLaunchKernelGGL(from_f64_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kFromThreads),
+                           0, ffh::as_stream(stream), x + at, hi + at, lo + at, count);
+    });
     return ffh::launch_status();
 }
 
@@ -121,11 +123,13 @@ ff_status ff_to_f64(const float *hi, const float *lo, double *x, int64_t n, void
     const ff_status st = check_planes(x, hi, lo, n);
     if (st != FF_OK || n == 0)
         return st;
-    const int64_t blocks = ffh::cdiv(n, int64_t(kToThreads) * kToPer);
-    if (blocks > INT32_MAX)
+    if (ffh::cdiv(n, int64_t(kToThreads) * kToPer) > INT32_MAX)
         return FF_ERR_SIZE;
-    hipLaunchKernelGGL(to_f64_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kToThreads), 0,
-                       ffh::as_stream(stream), hi, lo, x, n);
+    ffh::in_parts(n, ffh::kMostThreads, [&](int64_t at, int64_t count) {
+        const int64_t blocks = ffh::cdiv(count, int64_t(kToThreads) * kToPer);
+        hipLaunchKernelGGL(to_f64_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kToThreads), 0,
+                           ffh::as_stream(stream), hi + at, lo + at, x + at, count);
+    });
     return ffh::launch_status();
 }
 

@@ -199,15 +199,17 @@ ff_status elementwise(const float *ah, const float *al, const float *bh, const f
             return FF_ERR_ALIGN;
     hipStream_t stream = ffh::as_stream(stream_ptr);
     const bool vec = n < kSmallN;
-    const int64_t blocks = vec ? ffh::cdiv(n, 4 * kVecBlock) : ffh::cdiv(n, kSpan);
-    if (blocks > INT32_MAX)
+    if (ffh::cdiv(n, kSpan) > INT32_MAX)
         return FF_ERR_SIZE;
     if (vec)
-        hipLaunchKernelGGL(ew_vec<Tag>, dim3(static_cast<unsigned>(blocks)), dim3(kVecBlock), 0,
-                           stream, ah, al, bh, bl, rh, rl, n);
+        hipLaunchKernelGGL(ew_vec<Tag>, dim3(static_cast<unsigned>(ffh::cdiv(n, 4 * kVecBlock))),
+                           dim3(kVecBlock), 0, stream, ah, al, bh, bl, rh, rl, n);
     else
-        hipLaunchKernelGGL(ew_stream<Tag>, dim3(static_cast<unsigned>(blocks)), dim3(kBlock), 0,
-                           stream, ah, al, bh, bl, rh, rl, n);
+        ffh::in_parts(n, ffh::kMostThreads, [&](int64_t at, int64_t count) {
+            hipLaunchKernelGGL(ew_stream<Tag>, dim3(static_cast<unsigned>(ffh::cdiv(count, kSpan))),
+                               dim3(kBlock), 0, stream, ah + at, al + at, bh + at, bl + at, rh + at,
+                               rl + at, count);
+        });
     return ffh::launch_status();
 }
 
@@ -281,11 +283,13 @@ ff_status ff_copy(const float *src, float *dst, int64_t n, void *stream_ptr)
         return FF_ERR_NULL;
     if (!ffh::aligned(src, 4) || !ffh::aligned(dst, 4))
         return FF_ERR_ALIGN;
-    const int64_t blocks = ffh::cdiv(n, int64_t(kCopyThreads) * kCopyPer);
-    if (blocks > INT32_MAX)
+    if (ffh::cdiv(n, int64_t(kCopyThreads) * kCopyPer) > INT32_MAX)
         return FF_ERR_SIZE;
-    hipLaunchKernelGGL(copy_stream, dim3(static_cast<unsigned>(blocks)), dim3(kCopyThreads), 0,
-                       ffh::as_stream(stream_ptr), src, dst, n);
+    ffh::in_parts(n, ffh::kMostThreads, [&](int64_t at, int64_t count) {
+        const int64_t blocks = ffh::cdiv(count, int64_t(kCopyThreads) * kCopyPer);
+        hipLaunchKernelGGL(copy_stream, dim3(static_cast<unsigned>(blocks)), dim3(kCopyThreads), 0,
+                           ffh::as_stream(stream_ptr), src + at, dst + at, count);
+    });
     return ffh::launch_status();
 }
 

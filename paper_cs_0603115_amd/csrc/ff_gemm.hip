@@ -1117,11 +1117,13 @@ ff_status ff_gemm(int64_t M, int64_t N, int64_t K, const float *A_hi, const floa
     case FF_GEMM_FMA_LOOP:
     {
         auto launch = [&](auto kernel, int tile) {
-            hipLaunchKernelGGL(kernel,
-                               dim3(static_cast<unsigned>(ffh::cdiv(N, tile)),
-                                    static_cast<unsigned>(ffh::cdiv(M, tile))),
-                               dim3(256), 0, st, M, N, K, A_hi, A_lo, lda, B_hi, B_lo, ldb, C_hi,
-                               C_lo, ldc);
+            ffh::in_parts(N, ffh::kMostThreads / 256 * tile, [&](int64_t at, int64_t cols) {
+                hipLaunchKernelGGL(kernel,
+                                   dim3(static_cast<unsigned>(ffh::cdiv(cols, tile)),
+                                        static_cast<unsigned>(ffh::cdiv(M, tile))),
+                                   dim3(256), 0, st, M, cols, K, A_hi, A_lo, lda, B_hi + at,
+                                   B_lo + at, ldb, C_hi + at, C_lo + at, ldc);
+            });
         };
         // as many outputs per thread (less LDS traffic each) as leave four
         // workgroups per compute unit; us with 1, 4 and 16: 1024^3 530 / 516 /

@@ -32,4 +32,16 @@ inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s);
 // Ceiling division for non-negative values.
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// HIP counts the threads of a launch in 32 bits: of more it launches their
+// number modulo 2^32 and reports no error.  launch(first, count) for ranges of at
+// most `most` of n items, one range for all but the largest calls.
+constexpr int64_t kMostThreads = int64_t(1) << 31;
+
+template <class Launch>
+inline void in_parts(int64_t n, int64_t most, Launch launch)
+{
+    for (int64_t first = 0; first < n; first += most)
+        launch(first, n - first < most ? n - first : most);
+}
+
 } // namespace ffh

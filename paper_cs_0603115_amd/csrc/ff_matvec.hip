@@ -333,11 +333,11 @@ __global__ __launch_bounds__(BLOCK) void matvec_bwd_band(
 template <int COLS, int GROUPS>
 __global__ __launch_bounds__(COLS * GROUPS) void matvec_bwd_combine(
     int64_t N, int64_t nbands, const float2 *__restrict__ part, float *__restrict__ dxh,
-    float *__restrict__ dxl)
+    float *__restrict__ dxl, int64_t first)
 {
     __shared__ float2 sums[GROUPS][COLS];
     const int col = threadIdx.x % COLS, grp = threadIdx.x / COLS;
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * COLS + col;
+    const int64_t j = (first + blockIdx.x) * COLS + col;
     float h = 0.0f, l = 0.0f;
     if (j < N) {
         int64_t b = grp;
@@ -545,13 +545,13 @@ template <bool XLO, bool YLO, bool DX, bool DY>
 __global__ __launch_bounds__(kBwdThreads) void dot_batched_bwd(
     const float *__restrict__ g_hi, const float *__restrict__ g_lo,
     const int64_t *__restrict__ offsets, int32_t nvec, int64_t total,
-    const int4 *__restrict__ records,
+    const int4 *__restrict__ records, int64_t first,
     const float *__restrict__ xh, const float *__restrict__ xl, const float *__restrict__ yh,
     const float *__restrict__ yl, float *__restrict__ dxh, float *__restrict__ dxl,
     float *__restrict__ dyh, float *__restrict__ dyl)
 {
     const int t = threadIdx.x;
-    const int64_t b0 = static_cast<int64_t>(blockIdx.x) * kBwdBlock;
+    const int64_t block = first + blockIdx.x, b0 = block * kBwdBlock;
     // all of this thread's operands first
     int64_t idx[kBwdPer];
     float ox[kBwdPer], oxl[kBwdPer], oy[kBwdPer], oyl[kBwdPer];
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(kBwdThreads) void dot_batched_bwd(
         oy[k] = (DX && in) ? yh[i] : 0.0f;
         oyl[k] = (DX && YLO && in) ? yl[i] : 0.0f;
     }
-    const int4 r = records[blockIdx.x];
+    const int4 r = records[block];
     // the wavefront's first and last element, the same on every lane
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int64_t w0 = b0 + 64 * wave;
@@ -706,12 +706,18 @@ ff_status ff_matvec(int64_t M, int64_t N, const float *A_hi, const float *A_lo, 
         return FF_ERR_SIZE;
     hipStream_t st = ffh::as_stream(stream);
     if (algo == FF_MATVEC_PLAIN) {
-        hipLaunchKernelGGL(matvec_plain, dim3(static_cast<unsigned>(ffh::cdiv(M, 256))), dim3(256),
-                           0, st, M, N, A_hi, A_lo, lda, x_hi, x_lo, y_hi, y_lo);
+        ffh::in_parts(M, ffh::kMostThreads, [&](int64_t at, int64_t count) {
+            hipLaunchKernelGGL(matvec_plain, dim3(static_cast<unsigned>(ffh::cdiv(count, 256))),
+                               dim3(256), 0, st, count, N, A_hi + at * lda, A_lo + at * lda, lda,
+                               x_hi, x_lo, y_hi + at, y_lo + at);
+        });
     } else {
         auto launch = [&](auto kernel, int block, int rows) {
-            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(ffh::cdiv(M, rows))), dim3(block),
-                               0, st, M, N, A_hi, A_lo, lda, x_hi, x_lo, y_hi, y_lo);
+            ffh::in_parts(M, ffh::kMostThreads / block * rows, [&](int64_t at, int64_t count) {
+                hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(ffh::cdiv(count, rows))),
+                                   dim3(block), 0, st, count, N, A_hi + at * lda, A_lo + at * lda,
+                                   lda, x_hi, x_lo, y_hi + at, y_lo + at);
+            });
         };
         // As many threads per row as it feeds with a few float4 groups each, one
         // row per group of threads, two where there are rows enough for 512
@@ -840,13 +846,14 @@ ff_status ff_matvec_backward(int64_t M, int64_t N, const float *A_hi, const floa
         }
     }
     if (want_dx && N >= 4096)
-        hipLaunchKernelGGL((matvec_bwd_combine<64, 8>),
-                           dim3(static_cast<unsigned>(ffh::cdiv(N, 64))), dim3(64 * 8), 0, st, N,
-                           nbands, part, dx_hi, dx_lo);
+        ffh::in_parts(ffh::cdiv(N, 64), ffh::kMostThreads / 512, [&](int64_t first, int64_t count) {
+            hipLaunchKernelGGL((matvec_bwd_combine<64, 8>), dim3(static_cast<unsigned>(count)),
+                               dim3(64 * 8), 0, st, N, nbands, part, dx_hi, dx_lo, first);
+        });
     else if (want_dx)
         hipLaunchKernelGGL((matvec_bwd_combine<16, 64>),
                            dim3(static_cast<unsigned>(ffh::cdiv(N, 16))), dim3(16 * 64), 0, st, N,
-                           nbands, part, dx_hi, dx_lo);
+                           nbands, part, dx_hi, dx_lo, int64_t(0));
     return ffh::launch_status();
 }
 
@@ -865,12 +872,18 @@ ff_status ff_dot_backward(const float *g_hi, const float *g_lo, const float *x_h
         return FF_ERR_NULL;
     if (!all_aligned({g_hi, g_lo, x_hi, x_lo, y_hi, y_lo, dx_hi, dx_lo, dy_hi, dy_lo}, 4))
         return FF_ERR_ALIGN;
-    const int64_t blocks = ffh::cdiv(n, int64_t(kDotBwdThreads) * kDotBwdPer);
-    if (blocks > INT32_MAX)
+    if (ffh::cdiv(n, int64_t(kDotBwdThreads) * kDotBwdPer) > INT32_MAX)
         return FF_ERR_SIZE;
-    hipLaunchKernelGGL(dot_backward, dim3(static_cast<unsigned>(blocks)), dim3(kDotBwdThreads), 0,
-                       ffh::as_stream(stream), g_hi, g_lo, x_hi, x_lo, y_hi, y_lo,
-                       want_dx ? dx_hi : nullptr, dx_lo, want_dy ? dy_hi : nullptr, dy_lo, n);
+    // (planes that may be null are only moved along where they are read or written)
+    ffh::in_parts(n, ffh::kMostThreads, [&](int64_t at, int64_t count) {
+        const int64_t blocks = ffh::cdiv(count, int64_t(kDotBwdThreads) * kDotBwdPer);
+        auto from = [&](auto *plane, bool used) { return used ? plane + at : nullptr; };
+        hipLaunchKernelGGL(dot_backward, dim3(static_cast<unsigned>(blocks)), dim3(kDotBwdThreads),
+                           0, ffh::as_stream(stream), g_hi, g_lo, from(x_hi, want_dy),
+                           from(x_lo, want_dy), from(y_hi, want_dx), from(y_lo, want_dx),
+                           from(dx_hi, want_dx), from(dx_lo, want_dx), from(dy_hi, want_dy),
+                           from(dy_lo, want_dy), count);
+    });
     return ffh::launch_status();
 }
 
@@ -885,12 +898,14 @@ ff_status ff_gradient_value(const float *g_hi, const float *g_lo, float *v_hi, f
         return FF_ERR_NULL;
     if (!all_aligned({g_hi, g_lo, v_hi, v_lo}, 4))
         return FF_ERR_ALIGN;
-    const int64_t blocks = ffh::cdiv(n, int64_t(kGradientThreads));
-    if (blocks > INT32_MAX)
+    if (ffh::cdiv(n, int64_t(kGradientThreads)) > INT32_MAX)
         return FF_ERR_SIZE;
-    hipLaunchKernelGGL(gradient_value, dim3(static_cast<unsigned>(blocks)),
-                       dim3(kGradientThreads), 0, ffh::as_stream(stream), g_hi, g_lo, v_hi, v_lo,
-                       n);
+    ffh::in_parts(n, ffh::kMostThreads, [&](int64_t at, int64_t count) {
+        const int64_t blocks = ffh::cdiv(count, int64_t(kGradientThreads));
+        hipLaunchKernelGGL(gradient_value, dim3(static_cast<unsigned>(blocks)),
+                           dim3(kGradientThreads), 0, ffh::as_stream(stream), g_hi + at, g_lo + at,
+                           v_hi + at, v_lo + at, count);
+    });
     return ffh::launch_status();
 }
 
@@ -933,10 +948,12 @@ ff_status ff_dot_batched_backward(const float *g_hi, const float *g_lo, const in
                        nvec, total_len, blocks, records);
     const bool xlo = want_dy && x_lo, ylo = want_dx && y_lo;
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kBwdThreads), 0,
-                           ffh::as_stream(stream), g_hi, g_lo, offsets, nvec, total_len,
-                           static_cast<const int4 *>(records), x_hi, x_lo, y_hi, y_lo, dx_hi,
-                           dx_lo, dy_hi, dy_lo);
+        ffh::in_parts(blocks, ffh::kMostThreads / kBwdThreads, [&](int64_t first, int64_t count) {
+            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(count)), dim3(kBwdThreads), 0,
+                               ffh::as_stream(stream), g_hi, g_lo, offsets, nvec, total_len,
+                               static_cast<const int4 *>(records), first, x_hi, x_lo, y_hi, y_lo,
+                               dx_hi, dx_lo, dy_hi, dy_lo);
+        });
     };
     // one instantiation per (low words present, outputs wanted)
     if (want_dx && want_dy) {

@@ -200,16 +200,23 @@ ff_status stream_op(StreamPlanes<Op::kIn, Op::kOut> p, int64_t n, void *stream_p
     }
     hipStream_t st = ffh::as_stream(stream_ptr);
     const bool vec = n < kStreamSmallN;
-    const int64_t blocks = vec ? ffh::cdiv(n, 4 * kStreamBlock)
-                               : ffh::cdiv(n, StreamShape<Op>::kSpan);
-    if (blocks > INT32_MAX)
+    if (ffh::cdiv(n, StreamShape<Op>::kSpan) > INT32_MAX)
         return FF_ERR_SIZE;
     if (vec)
-        hipLaunchKernelGGL(stream_vec<Op>, dim3(static_cast<unsigned>(blocks)), dim3(kStreamBlock),
-                           0, st, p, n);
+        hipLaunchKernelGGL(stream_vec<Op>,
+                           dim3(static_cast<unsigned>(ffh::cdiv(n, 4 * kStreamBlock))),
+                           dim3(kStreamBlock), 0, st, p, n);
     else
-        hipLaunchKernelGGL(stream_op_kernel<Op>, dim3(static_cast<unsigned>(blocks)),
-                           dim3(StreamShape<Op>::kBlock), 0, st, p, n);
+        ffh::in_parts(n, ffh::kMostThreads, [&](int64_t at, int64_t count) {
+            StreamPlanes<Op::kIn, Op::kOut> part = p;
+            for (int k = 0; k < Op::kIn; ++k)
+                part.in[k] += at;
+            for (int k = 0; k < Op::kOut; ++k)
+                part.out[k] += at;
+            const int64_t blocks = ffh::cdiv(count, StreamShape<Op>::kSpan);
+            hipLaunchKernelGGL(stream_op_kernel<Op>, dim3(static_cast<unsigned>(blocks)),
+                               dim3(StreamShape<Op>::kBlock), 0, st, part, count);
+        });
     return ffh::launch_status();
 }
 

@@ -216,21 +216,20 @@ template <class Alg, bool CLO, bool XLO>
 ff_status launch_horner(PolyArgs a, int64_t n, bool vec, hipStream_t st)
 {
     if (vec) {
-        // (a launch holds fewer than 2^32 threads)
-        constexpr int64_t kMost = int64_t(1) << 33;
-        for (int64_t done = 0; done < n; done += kMost) {
+        if (ffh::cdiv(n, 4 * kPolyBlock) > INT32_MAX)
+            return FF_ERR_SIZE;
+        ffh::in_parts(n, 4 * ffh::kMostThreads, [&](int64_t at, int64_t count) {
             PolyArgs part = a;
-            part.xh += done;
+            part.xh += at;
             if (XLO)
-                part.xl += done;
-            part.yh += done;
+                part.xl += at;
+            part.yh += at;
             if (Alg::kFF)
-                part.yl += done;
-            const int64_t points = n - done < kMost ? n - done : kMost;
+                part.yl += at;
             hipLaunchKernelGGL((horner_vec<Alg, CLO, XLO>),
-                               dim3(static_cast<unsigned>(ffh::cdiv(points, 4 * kPolyBlock))),
-                               dim3(kPolyBlock), 0, st, part, points);
-        }
+                               dim3(static_cast<unsigned>(ffh::cdiv(count, 4 * kPolyBlock))),
+                               dim3(kPolyBlock), 0, st, part, count);
+        });
     } else {
         const int64_t blocks = ffh::cdiv(n, kPolyBlock);
         hipLaunchKernelGGL((horner_scalar<Alg, CLO, XLO>),

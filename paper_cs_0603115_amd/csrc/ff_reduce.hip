@@ -167,9 +167,9 @@ __global__ __launch_bounds__(kPlanBlock) void dot_plan(const int64_t *__restrict
 // Chunks beyond the workspace capacity are never recorded.
 __global__ __launch_bounds__(256) void dot_ranges(const int64_t *__restrict__ offsets,
                                                   int32_t nvec, int64_t total, int64_t chunk,
-                                                  Workspace w)
+                                                  Workspace w, int64_t first)
 {
-    const int64_t v = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int64_t v = (first + blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (v >= nvec)
         return;
@@ -376,9 +376,9 @@ __device__ __forceinline__ void wave_allreduce(float &h, float &l)
 template <class Acc>
 __global__ __launch_bounds__(256) void dot_combine(int32_t nvec, Workspace w,
                                                    float *__restrict__ out_hi,
-                                                   float *__restrict__ out_lo)
+                                                   float *__restrict__ out_lo, int64_t first)
 {
-    const int64_t v = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int64_t v = (first + blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (v >= nvec)
         return;
@@ -536,11 +536,12 @@ __device__ __forceinline__ void accumulate(const In &in, int64_t s, int64_t e, f
 // records of the plan launches.
 template <class In, class Acc, int BLOCK, int PER, bool INLINE>
 __global__ __launch_bounds__(BLOCK) void dot_chunks(In in, const int64_t *__restrict__ offsets,
-                                                    int32_t nvec, int64_t total, Workspace w)
+                                                    int32_t nvec, int64_t total, Workspace w,
+                                                    int64_t first)
 {
     constexpr int kWaves = BLOCK / 64;
     __shared__ float2 wave_part[kWaves];
-    const int64_t c = blockIdx.x;
+    const int64_t c = first + blockIdx.x;
     int64_t s, e;   // s < e: recorded chunks are not empty
     if constexpr (INLINE) {
         if (!inline_plan<BLOCK>(offsets, nvec, total, __builtin_ctz(BLOCK * PER), w, s, e))
@@ -656,20 +657,20 @@ ff_status resolve_cfg(const ff_dot_cfg *cfg, Cfg &out)
 }
 
 template <class In, class Acc, int BLOCK, int PER>
-void launch_partials(bool inlined, unsigned grid, hipStream_t st, const In &in,
-                     const int64_t *offsets, int32_t nvec, int64_t total, const Workspace &w)
+void launch_partials(bool inlined, hipStream_t st, const In &in, const int64_t *offsets,
+                     int32_t nvec, int64_t total, const Workspace &w)
 {
-    if (inlined)
-        hipLaunchKernelGGL((dot_chunks<In, Acc, BLOCK, PER, true>), dim3(grid), dim3(BLOCK), 0, st,
-                           in, offsets, nvec, total, w);
-    else
-        hipLaunchKernelGGL((dot_chunks<In, Acc, BLOCK, PER, false>), dim3(grid), dim3(BLOCK), 0,
-                           st, in, offsets, nvec, total, w);
+    auto kernel =
+        inlined ? dot_chunks<In, Acc, BLOCK, PER, true> : dot_chunks<In, Acc, BLOCK, PER, false>;
+    ffh::in_parts(w.cap, ffh::kMostThreads / BLOCK, [&](int64_t first, int64_t count) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(count)), dim3(BLOCK), 0, st, in,
+                           offsets, nvec, total, w, first);
+    });
 }
 
 template <class In, class Acc, int BLOCK>
-void launch_chunks(int unroll, bool inlined, unsigned grid, hipStream_t st, const In &in,
-                   const int64_t *offsets, int32_t nvec, int64_t total, const Workspace &w)
+void launch_chunks(int unroll, bool inlined, hipStream_t st, const In &in, const int64_t *offsets,
+                   int32_t nvec, int64_t total, const Workspace &w)
 {
     auto launch = unroll == 1    ? launch_partials<In, Acc, BLOCK, 1>
                   : unroll == 2  ? launch_partials<In, Acc, BLOCK, 2>
@@ -677,7 +678,7 @@ void launch_chunks(int unroll, bool inlined, unsigned grid, hipStream_t st, cons
                   : unroll == 8  ? launch_partials<In, Acc, BLOCK, 8>
                   : unroll == 16 ? launch_partials<In, Acc, BLOCK, 16>
                                  : launch_partials<In, Acc, BLOCK, 32>;
-    launch(inlined, grid, st, in, offsets, nvec, total, w);
+    launch(inlined, st, in, offsets, nvec, total, w);
 }
 
 template <class In, class Acc = AccFF>
@@ -708,8 +709,9 @@ ff_status dot_batched_entry(const In &in, const int64_t *offsets, int32_t nvec, 
     if (w.cap > INT32_MAX)
         return FF_ERR_SIZE;
     hipStream_t st = ffh::as_stream(stream_ptr);
-    const unsigned wave_blocks = static_cast<unsigned>(ffh::cdiv(nvec, 4));
-    const unsigned grid = static_cast<unsigned>(w.cap);
+    auto four_vectors_each = [&](auto launch) {
+        ffh::in_parts(ffh::cdiv(nvec, 4), ffh::kMostThreads / 256, launch);
+    };
     const bool inlined = nvec <= kInlinePlanVectors && w.cap <= kInlinePlanChunks &&
                          nvec * w.cap <= kInlinePlanWork;
     if (!inlined && nvec <= kMergedPlanMax) {
@@ -719,16 +721,20 @@ ff_status dot_batched_entry(const In &in, const int64_t *offsets, int32_t nvec, 
     } else if (!inlined) {
         hipLaunchKernelGGL(dot_plan, dim3(1), dim3(kPlanBlock), 0, st, offsets, nvec, total,
                            cfg.chunk, w);
-        hipLaunchKernelGGL(dot_ranges, dim3(wave_blocks), dim3(256), 0, st, offsets, nvec, total,
-                           cfg.chunk, w);
+        four_vectors_each([&](int64_t first, int64_t count) {
+            hipLaunchKernelGGL(dot_ranges, dim3(static_cast<unsigned>(count)), dim3(256), 0, st,
+                               offsets, nvec, total, cfg.chunk, w, first);
+        });
     }
     auto chunks = cfg.block == 64    ? launch_chunks<In, Acc, 64>
                   : cfg.block == 128 ? launch_chunks<In, Acc, 128>
                   : cfg.block == 256 ? launch_chunks<In, Acc, 256>
                                      : launch_chunks<In, Acc, 512>;
-    chunks(cfg.unroll, inlined, grid, st, in, offsets, nvec, total, w);
-    hipLaunchKernelGGL(dot_combine<Acc>, dim3(wave_blocks), dim3(256), 0, st, nvec, w, out_hi,
-                       out_lo);
+    chunks(cfg.unroll, inlined, st, in, offsets, nvec, total, w);
+    four_vectors_each([&](int64_t first, int64_t count) {
+        hipLaunchKernelGGL(dot_combine<Acc>, dim3(static_cast<unsigned>(count)), dim3(256), 0, st,
+                           nvec, w, out_hi, out_lo, first);
+    });
     return ffh::launch_status();
 }
 

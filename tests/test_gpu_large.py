@@ -265,3 +265,165 @@ def test_horner_beyond_one_launch():
     assert float(base[0]) == 7.0 and float(base[n + 1]) == 7.0
     del base, x, pattern, want
     torch.cuda.empty_cache()
+
+
+# Calls whose launches would have 2^32 threads or more, which HIP takes modulo
+# 2^32: small integers make every result exact, checked whole in pieces.
+STEP = 1 << 30
+
+
+def _pieces(n):
+    for at in range(0, n, STEP):
+        yield at, min(STEP, n - at)
+
+
+def _pattern(period):
+    return torch.arange(STEP, device="cuda", dtype=torch.int32).remainder_(period).float()
+
+
+def test_elementwise_beyond_2p33():
+    n = (1 << 33) + 9
+    _announce(f"[gpu] large: ff_add in place at n={n}")
+    ff = _ff()
+    a, b = (torch.zeros((2, n), device="cuda") for _ in range(2))
+    p, q = _pattern(1021), _pattern(4093)
+    for at, m in _pieces(n):
+        a[0, at:at + m], b[0, at:at + m] = p[:m], q[:m]
+    ff.ff_add(a, b, out=a)
+    for at, m in _pieces(n):
+        assert torch.equal(a[0, at:at + m], p[:m] + q[:m]), at
+        assert not a[1, at:at + m].any(), at
+    del a, b, p, q
+    _free()
+
+
+def test_stream_operator_and_copy_beyond_2p34():
+    n = (1 << 34) + 5
+    _announce(f"[gpu] large: binary32 add in place and the copy probe at n={n}")
+    ff = _ff()
+    a, b = torch.empty(n, device="cuda"), torch.empty(n, device="cuda")
+    p, q = _pattern(1021), _pattern(4093)
+    for at, m in _pieces(n):
+        a[at:at + m], b[at:at + m] = p[:m], q[:m]
+    ff.f32_add(a, b, out=a)
+    for at, m in _pieces(n):
+        assert torch.equal(a[at:at + m], p[:m] + q[:m]), at
+    ff.ff_copy(a, b)
+    assert torch.equal(a[-4096:], b[-4096:]) and torch.equal(a[:STEP], b[:STEP])
+    for at, m in _pieces(n):
+        assert torch.equal(b[at:at + m], a[at:at + m]), at
+    del a, b, p, q
+    _free()
+
+
+def test_conversions_beyond_2p33():
+    n = (1 << 33) + 3
+    _announce(f"[gpu] large: conversions at n={n}")
+    ff = _ff()
+    x = torch.empty(n, dtype=torch.float64, device="cuda")
+    p = _pattern(1021).double().add_(2.0 ** -30)
+    for at, m in _pieces(n):
+        x[at:at + m] = p[:m]
+    pair = ff.ff_from_f64(x)
+    hi = p.float()
+    for at, m in _pieces(n):
+        assert torch.equal(pair[0, at:at + m], hi[:m]), at
+        assert torch.equal(pair[1, at:at + m].double(), p[:m] - hi[:m].double()), at
+        x[at:at + m] = -1.0
+    ff.ff_to_f64(pair, out=x)
+    for at, m in _pieces(n):
+        assert torch.equal(x[at:at + m], p[:m]), at
+    del x, pair, p, hi
+    _free()
+
+
+def test_matvec_of_2p28_rows():
+    M, N = (1 << 28) + 5, 3
+    _announce(f"[gpu] large: matvec {M} x {N}")
+    ff = _ff()
+    A, x = ff.ff_zeros((M, N)), ff.ff_zeros((N,))
+    A[0] = torch.arange(M, device="cuda", dtype=torch.int32).remainder_(1021).float()[:, None]
+    x[0] = torch.tensor([1.0, 2.0, 4.0])
+    want = A[0, :, 0] * 7
+    for algo in (ff.MATVEC_FAST, ff.MATVEC_PLAIN):
+        y = ff.ff_matvec(A, x, algo=algo)
+        assert torch.equal(y[0], want) and not y[1].any()
+    del A, x, y, want
+    _free()
+
+
+@pytest.mark.parametrize("nvec,cfg", [((1 << 24) + 77, None), ((1 << 23) + 5, (512, 0, 0, 1)),
+                                      ((1 << 26) + 5, (64, 0, 0, 1))])
+def test_reductions_of_many_vectors(nvec, cfg):
+    # vectors of 0, 1 and 2 elements in turn
+    _announce(f"[gpu] large: reductions of {nvec} vectors, cfg {cfg}")
+    ff = _ff()
+    lengths = torch.arange(nvec, device="cuda").remainder_(3)
+    offs = torch.zeros(nvec + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(lengths, 0, out=offs[1:])
+    total = int(offs[-1])
+    x = torch.arange(total, device="cuda", dtype=torch.int32).remainder_(1021).float()
+    first = torch.where(lengths > 0, x[offs[:-1].clamp(max=total - 1)], 0)
+    second = torch.where(lengths > 1, x[(offs[:-1] + 1).clamp(max=total - 1)], 0)
+    s = ff.ff_sum_batched(x, offs, cfg=cfg)
+    assert torch.equal(s[0], first + second) and not s[1].any()
+    d = ff.ff_dot_batched(x, x, offs, cfg=cfg)
+    assert torch.equal(d[0], first * first + second * second) and not d[1].any()
+    del lengths, offs, x, first, second, s, d
+    _free()
+
+
+def test_dot_backward_beyond_2p32_threads():
+    total, cut = (1 << 32) + 300, (1 << 32) - 1000
+    _announce(f"[gpu] large: batched dot backward, total {total}")
+    ff = _ff()
+    x = torch.empty(total, device="cuda")
+    p = _pattern(1021)
+    for at, m in _pieces(total):
+        x[at:at + m] = p[:m]
+    offs = torch.tensor([3, cut, total - 2], device="cuda")
+    g = torch.tensor([[2.0, -3.0], [0.0, 0.0]], device="cuda")
+    dx, _ = ff.ff_dot_batched_backward(g, x, x, offs, want_dy=False)
+    for at, m in _pieces(total):
+        i = torch.arange(at, at + m, device="cuda")
+        want = torch.where(i < 3, 0.0, torch.where(i < cut, 2.0 * p[:m],
+                                                   torch.where(i < total - 2, -3.0 * p[:m], 0.0)))
+        assert torch.equal(dx[0, at:at + m], want), at
+        assert not dx[1, at:at + m].any(), at
+        del i, want
+    del x, dx, p
+    _free()
+    n = (1 << 33) + 77
+    _announce(f"[gpu] large: dot backward, n {n}")
+    u = torch.zeros((2, n), device="cuda")
+    p = _pattern(1021)
+    for at, m in _pieces(n):
+        u[0, at:at + m] = p[:m]
+    dx, _ = ff.ff_dot_backward(torch.tensor([3.0, 0.0], device="cuda"), u, u, want_dy=False)
+    for at, m in _pieces(n):
+        assert torch.equal(dx[0, at:at + m], 3.0 * p[:m]), at
+        assert not dx[1, at:at + m].any(), at
+    del u, dx, p
+    _free()
+
+
+def test_rows_of_2p29_and_2p30_columns():
+    M, N = 2, (1 << 29) + 5
+    _announce(f"[gpu] large: matvec backward {M} x {N}")
+    ff = _ff()
+    A, x = ff.ff_zeros((M, N)), ff.ff_zeros((N,))
+    row = torch.arange(N, device="cuda", dtype=torch.int32).remainder_(1021).float()
+    A[0, 0], A[0, 1] = row, 5.0
+    g = torch.tensor([[2.0, 3.0], [0.0, 0.0]], device="cuda")
+    _, dx = ff.ff_matvec_backward(A, x, g, want_dA=False)
+    assert torch.equal(dx[0], 2.0 * row + 15.0) and not dx[1].any()
+    del A, x, row, dx
+    _free()
+    N = (1 << 30) + 3
+    _announce(f"[gpu] large: plain product 1 x {N} x 1")
+    B = ff.ff_zeros((1, N))
+    B[0, 0] = torch.arange(N, device="cuda", dtype=torch.int32).remainder_(1021).float()
+    C = ff.ff_gemm(torch.tensor([[[3.0]], [[0.0]]], device="cuda"), B, algo=ff.GEMM_FMA_LOOP)
+    assert torch.equal(C[0, 0], 3.0 * B[0, 0]) and not C[1].any()
+    del B, C
+    _free()
