@@ -231,7 +231,8 @@ __global__ __launch_bounds__(256) void matvec_plain(int64_t M, int64_t N,
 // planes together: with adjacent rows per band every band kept pages of its
 // own open (14271 x 4110: 263 us, 234 now; 14336 x 4096: 218, 171; 4096 x 4096:
 // 57, 51; 8191 x 8191: 235, 220; 8192 x 8192: 172, 169, 6.3 TB/s; of 30 shapes
-// two lost, 4096 x 16384 181 to 196 and 2048 x 32768 193 to 215).  Loading two
+// the two that lost, 4096 x 16384 and 2048 x 32768, follow the planes' placement:
+// 170-198 us against 172-182, and 184-212 against 190-193, over four).  Loading two
 // pairs ahead of the stores, or four rows at once, gave nothing.
 template <int BLOCK, int COLS, bool WANT_DA, bool WANT_DX>
 __global__ __launch_bounds__(BLOCK) void matvec_bwd_band(
@@ -725,12 +726,15 @@ ff_status ff_matvec(int64_t M, int64_t N, const float *A_hi, const float *A_lo, 
         // x 64 3.4 / 18.0, 16384 x 512 11.9 / 21.8 (16 threads); 16384 x 1000 24.1 /
         // 27.8 (64); and for two rows against one 1000 x 16384 23.9 / 27.3, 8192 x
         // 8192 81 / 90.  Below, us with the matrix cached (from HBM) against the next
-        // best: 64 x 127 2.8 (2.5), 64 threads 3.0 (2.8); 500 x 257 3.2 (3.3), 128
+        // best: 64 x 63 2.7, the other loop 2.8, and 64 x 64 2.5, this one 2.7; 64 x 127 2.8
+        // (2.5), 64 threads 3.0 (2.8); 500 x 257 3.2 (3.3), 128
         // threads 3.3 (3.4); 500 x 511 3.4 (3.6), 256 threads 3.5 (3.7); 1600 x 3001
         // 9.2 (9.5), 256 threads 10.7 (10.3); 768 x 1023 4.2 (4.3), 128 threads 4.4
         // (4.5); 1000 x 8191 13.6 (14.3), 128 threads 15.6 (16.7); 64 x 16384 7.4
         // with 512 threads, 13.5 with 256.
-        if (M < 2048 && N <= 128)
+        if (M < 2048 && N <= 64)
+            launch(N % 4 ? matvec_rows<256, 16, 1, true> : matvec_rows<256, 16, 1, false>, 256, 16);
+        else if (M < 2048 && N <= 128)
             launch(matvec_rows<256, 32, 1, true>, 256, 8);
         else if (M < 2048 && N <= 288)
             launch(matvec_rows<256, 64, 1, true>, 256, 4);

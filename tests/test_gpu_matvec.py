@@ -433,7 +433,7 @@ def test_backward_takes_every_row_once(M, N):
 # one shape on each side of every line between the forms of short rows, whose
 # last round loads past its end, and row lengths of every remainder mod 4
 @pytest.mark.parametrize("M,N", [
-    (1, 4), (3, 7), (9, 127), (70, 129), (33, 257), (33, 288), (50, 289), (1279, 512), (1280, 511),
+    (1, 4), (3, 7), (40, 61), (40, 64), (9, 127), (70, 129), (33, 257), (33, 288), (50, 289), (1279, 512), (1280, 511),
     (1281, 289), (1100, 767), (767, 1023), (767, 1025), (768, 1030), (1279, 1027), (1280, 513),
     (1280, 1026), (2047, 1029), (2047, 130), (2048, 126), (2048, 515), (768, 8192), (60, 8195),
     (1300, 8193)])
